@@ -389,11 +389,11 @@ __global__ __launch_bounds__(256) void k_bwd_post_dots(const TG* dXn, const TS* 
 // flight.  Per token a wave sums its lanes' products through an LDS transpose
 // (lane i adds column i) and lanes i < ND write them: part[w][t][i] with w the
 // wave's 256-channel slice of C (workgroups of 256 or 64 threads).
-constexpr int kDotRun = 64;
+constexpr int kDotRun = 64;   // at most
 template <typename TS, typename TG>
 __global__ __launch_bounds__(256) void k_bwd_post_dots_run(const TG* dXn, const TS* __restrict__ Xact,
                                                            const TS* __restrict__ F, int64_t T, int64_t S, int N,
-                                                           int C, int k, const float* __restrict__ conv_w,
+                                                           int C, int k, int rl, const float* __restrict__ conv_w,
                                                            const int32_t* __restrict__ idx, float* __restrict__ part) {
   using CG = ConvGroup<4, 8, 12>;
   using PD = PostDots<4, 4>;
@@ -404,8 +404,8 @@ __global__ __launch_bounds__(256) void k_bwd_post_dots_run(const TG* dXn, const 
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int g = (int)(blockIdx.y * blockDim.x + threadIdx.x);   // C % (4 blockDim.x) == 0
   const int c = g * 4, slice = g / kWave;
-  const int64_t t0 = (int64_t)blockIdx.x * kDotRun;
-  const int nt = (int)((T - t0 < kDotRun) ? T - t0 : kDotRun);
+  const int64_t t0 = (int64_t)blockIdx.x * rl;
+  const int nt = (int)((T - t0 < rl) ? T - t0 : rl);
   for (int i = threadIdx.x; i < nt * KM; i += blockDim.x) {   // (workgroups of 64 or 256 threads)
     const int j = i % KM < k ? i % KM : k - 1;   // unused slots repeat the last one (in bounds)
     s_idx[i / KM][i % KM] = idx[(t0 + i / KM) * k + j];
@@ -880,7 +880,7 @@ __global__ __launch_bounds__(256) void k_bwd_conv_run(const float* __restrict__ 
 
 // The element pass and the conv reverse of the post backward fused, for the
 // paper's branches (kappa = 4, 8, 12; K_r = 4) and k <= 4: one channel per
-// thread over a run of kConvRun tokens, nothing but the gradients leaving
+// thread over a run of rl tokens (16 .. kConvRun), nothing but the gradients leaving
 // registers.  Per token u of the run:
 //   dX[u, I_l] = sum_j H^res[j][l] dY_j          (mixing gradient of the active rows)
 //   X[u, I_l]  = Xact[u, l]                        (restore, when X is given)
@@ -897,7 +897,7 @@ __global__ __launch_bounds__(256) void k_bwd_conv_run(const float* __restrict__ 
 template <typename TS, typename TG, bool RESTORE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_bwd_post_run(const TG* dXn, TS* __restrict__ X, const TS* __restrict__ Xact,
                                                       const TS* __restrict__ F, int64_t T, int64_t S, int N, int C,
-                                                      int k, const float* __restrict__ conv_w,
+                                                      int k, int rl, const float* __restrict__ conv_w,
                                                       const int32_t* __restrict__ idx, const float* __restrict__ Hres,
                                                       const float* __restrict__ coef, TG* dX, TS* __restrict__ dF,
                                                       float* __restrict__ part, float* __restrict__ rb,
@@ -911,8 +911,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   __shared__ float s_cf[kConvRun][NCF];
   const int c = blockIdx.x * 256 + threadIdx.x;   // C % 256 == 0: every thread has a channel
   const int64_t run = blockIdx.y;
-  const int64_t t0 = run * kConvRun;
-  const int64_t t1 = t0 + kConvRun < T ? t0 + kConvRun : T;
+  const int64_t t0 = run * rl;
+  const int64_t t1 = t0 + rl < T ? t0 + rl : T;
   const int nt = (int)(t1 - t0);
   const bool last = t1 == T;
   for (int i = threadIdx.x; i < nt * KM; i += 256) {
@@ -1085,17 +1085,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   for (int r = 0; r < kConvRows; ++r) dst[(int64_t)r * C] = acc[r];
 }
 
-// dF of the 11 tokens before each run boundary t1 = b kConvRun (b = 1 ..
+// dF of the 11 tokens before each run boundary t1 = b rl (b = 1 ..
 // nruns - 1): the earlier run's part (rb) plus the later run's (lb), for the
 // tokens in the sequence of t1 - 1 (the others were stored complete).
 template <typename TS>
 __global__ __launch_bounds__(256) void k_bwd_post_fix(const float* __restrict__ rb, const float* __restrict__ lb,
-                                                      int64_t T, int64_t S, int C, TS* __restrict__ dF) {
+                                                      int64_t T, int64_t S, int C, int rl, TS* __restrict__ dF) {
   const int c = blockIdx.x * 256 + threadIdx.x;
   if (c >= C) return;
   const int64_t b = blockIdx.y + 1;
   const int i = blockIdx.z;
-  const int64_t t1 = b * kConvRun;
+  const int64_t t1 = b * rl;
   const int64_t v = t1 - 11 + i;
   const int64_t s_end = (t1 - 1) - (t1 - 1) % S;
   if (t1 >= T || v < s_end) return;
@@ -1876,6 +1876,19 @@ static bool post_run_ok(const xhc_dims* d) {
          (int64_t)kConvRun * d->N * d->C < ((int64_t)1 << 31);   // 32-bit row offsets within a run
 }
 
+// Tokens per run of the two run kernels: the longest, unless the chip (512
+// workgroups resident) would then be left partly idle.  A workgroup's time is
+// that of its tokens in sequence, so shorter runs finish sooner there: forward
+// and backward of a sublayer at T = 512, N = 8, C = 1024 took 654 us with the
+// full lengths (16 and 8 workgroups), 295 us with these.  The conv reverse needs 11 tokens a run at least (a token's dF may reach one run
+// back, no further).
+static int halve_to_fill(int rl, int least, int64_t T, int64_t blocks) {
+  while (rl > least && (T + rl - 1) / rl * blocks < 512) rl /= 2;
+  return rl;
+}
+static int conv_run_len(const xhc_dims* d) { return halve_to_fill(kConvRun, 16, d->T, d->C / 256); }
+static int dot_run_len(const xhc_dims* d, int nthr) { return halve_to_fill(kDotRun, 4, d->T, d->C / (4 * nthr)); }
+
 #define XHC_TS_DISPATCH(dt, ...) \
   if ((dt) == XHC_BF16) { using TS = uint16_t; __VA_ARGS__; } else { using TS = float; __VA_ARGS__; }
 
@@ -1892,7 +1905,8 @@ hipError_t launch_bwd_post(const xhc_dims* d, const void* dXn, void* X, const vo
   const int km = k <= 4 ? 4 : 8;
   const int nd = km * km + km * Kr + Kr * (Kr + 1) / 2;
   const bool fused = post_run_ok(d);
-  const int64_t nruns = (T + kConvRun - 1) / kConvRun;
+  const int crl = conv_run_len(d);   // fused: tokens per run
+  const int64_t nruns = (T + crl - 1) / crl;
   float* part = reinterpret_cast<float*>(ws);
   // dots partials: [post_chunks(C)][nd][T], or, fused, [C / 256][T][nd]
   float* coef = part + (fused ? (int64_t)(C / 256) : ncb) * nd * T;
@@ -1904,10 +1918,11 @@ hipError_t launch_bwd_post(const xhc_dims* d, const void* dXn, void* X, const vo
   const int* kap = d->kappa;
 #define XHC_BWD_POST_TG(KRV, KMV)                                                                                \
     if (fused) {                                                                                                 \
-      const int nthr = C % 1024 == 0 ? 256 : 64;                                                                 \
-      k_bwd_post_dots_run<TS, TG><<<dim3((unsigned)((T + kDotRun - 1) / kDotRun), (unsigned)(C / (4 * nthr))),  \
+      const int nthr = C % 1024 == 0 ? 256 : 64, drl = dot_run_len(d, nthr);                                     \
+      k_bwd_post_dots_run<TS, TG><<<dim3((unsigned)((T + drl - 1) / drl), (unsigned)(C / (4 * nthr))),          \
                                     dim3(nthr), 0, s>>>(reinterpret_cast<const TG*>(dXn),                        \
-          reinterpret_cast<const TS*>(Xact), reinterpret_cast<const TS*>(F), T, S, N, C, k, conv_w, idx, part);   \
+          reinterpret_cast<const TS*>(Xact), reinterpret_cast<const TS*>(F), T, S, N, C, k, drl, conv_w, idx,     \
+          part);                                                                                                 \
       k_colsum_rows<<<dim3((unsigned)((T * nd + 255) / 256)), dim3(256), 0, s>>>(part, C / 256, T * nd, dsum);     \
       k_bwd_post_token<KRV, KMV><<<dim3((unsigned)((T + 127) / 128)), dim3(128), 0, s>>>(dsum, 1, T * nd, 1, nd,    \
           T, k, d->gram_schmidt, p, Hpost, dHres, dHpost, dp, coef);                                              \
@@ -1940,16 +1955,16 @@ hipError_t launch_bwd_post(const xhc_dims* d, const void* dXn, void* X, const vo
       if (X)                                                                                                     \
         k_bwd_post_run<TS, TG, true><<<dim3((unsigned)((C + 255) / 256), (unsigned)nruns), dim3(256), 0, s>>>(   \
             reinterpret_cast<const TG*>(dXn), reinterpret_cast<TS*>(X), reinterpret_cast<const TS*>(Xact),        \
-            reinterpret_cast<const TS*>(F), T, S, N, C, k, conv_w, idx, Hres, coef, reinterpret_cast<TG*>(dX),   \
+            reinterpret_cast<const TS*>(F), T, S, N, C, k, crl, conv_w, idx, Hres, coef, reinterpret_cast<TG*>(dX), \
             reinterpret_cast<TS*>(dF), cpart, rb, lb);                                                            \
       else                                                                                                       \
         k_bwd_post_run<TS, TG, false><<<dim3((unsigned)((C + 255) / 256), (unsigned)nruns), dim3(256), 0, s>>>(  \
             reinterpret_cast<const TG*>(dXn), nullptr, reinterpret_cast<const TS*>(Xact),                         \
-            reinterpret_cast<const TS*>(F), T, S, N, C, k, conv_w, idx, Hres, coef, reinterpret_cast<TG*>(dX),   \
+            reinterpret_cast<const TS*>(F), T, S, N, C, k, crl, conv_w, idx, Hres, coef, reinterpret_cast<TG*>(dX), \
             reinterpret_cast<TS*>(dF), cpart, rb, lb);                                                            \
       if (nruns > 1)                                                                                             \
         k_bwd_post_fix<TS><<<dim3((unsigned)((C + 255) / 256), (unsigned)(nruns - 1), 11u), dim3(256), 0, s>>>(   \
-            rb, lb, T, S, C, reinterpret_cast<TS*>(dF));                                                         \
+            rb, lb, T, S, C, crl, reinterpret_cast<TS*>(dF));                                                     \
     } else if constexpr (KRV != 1)                                                                              \
     k_bwd_post_elem<TS, TG, KRV, KMV><<<grid, dim3(256), 0, s>>>(reinterpret_cast<const TG*>(dXn),              \
         reinterpret_cast<TS*>(X), reinterpret_cast<const TS*>(Xact), reinterpret_cast<const TS*>(F), T, S, N, C, \
@@ -2010,7 +2025,8 @@ size_t bwd_post_ws_bytes(const xhc_dims* d) {
     int nrows = 0;
     for (int j = 0; j < Kr - 1; ++j) nrows += d->kappa[j];
     const size_t chunked = (size_t)((T + kConvChunk - 1) / kConvChunk) * nrows * C;
-    const size_t nruns = (size_t)((T + kConvRun - 1) / kConvRun);
+    const int crl = post_run_ok(d) ? conv_run_len(d) : kConvRun;
+    const size_t nruns = (size_t)((T + crl - 1) / crl);
     const size_t runs = conv_run_ok(d) ? nruns * kConvRows * C : 0;
     // fused: only the run boundary parts instead of de
     n += (post_run_ok(d) ? 2 * nruns * 11 * (size_t)C + (size_t)nd * T : (size_t)Kr * T * C) +

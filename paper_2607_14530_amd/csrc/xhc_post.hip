@@ -126,14 +126,25 @@ __global__ __launch_bounds__(128) void k_post_coef(const float* __restrict__ gpa
 // is read once per kernel and the taps once per run.  Sequence starts fall on
 // group starts (S % G == 0), where the history is cleared.
 
-constexpr int kRun = 64;
+constexpr int kRun = 64;   // tokens of a run, at most
+
+// Tokens per run.  A run's workgroup walks its tokens one group after the
+// other, so its time is about that of its tokens in sequence; with fewer
+// workgroups than the chip holds (two per CU at these register counts, 512)
+// shorter runs finish sooner, until the set-up (24 taps and 12 rows of
+// history a channel) is as long as the walk: 4 tokens, one group.
+static int run_len(int64_t T, int64_t chunks) {
+  int rl = kRun;
+  while (rl > 4 && (T + rl - 1) / rl * chunks < 512) rl /= 2;
+  return rl;
+}
 
 // Gram partials per 1024-channel chunk.  Each lane forms its 4-channel
 // products for G tokens; a wave sums them over its 64 lanes through an LDS
 // transpose (lane v adds column v), and the waves' sums are added at the end.
 template <typename TS, int K1, int K2, int K3>
 __global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F, int64_t T, int64_t S, int C,
-                                                       const float* __restrict__ conv_w,
+                                                       const float* __restrict__ conv_w, int rl,
                                                        float* __restrict__ gpart) {
   using CG = ConvGroup<K1, K2, K3>;
   constexpr int KR = CG::KR, NP = KR * (KR + 1) / 2;
@@ -145,8 +156,8 @@ __global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F,
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int64_t cb = blockIdx.y;
   const int c = (int)(cb * blockDim.x + threadIdx.x) * 4;
-  const int64_t t0 = (int64_t)blockIdx.x * kRun;
-  const int nt = (int)((T - t0 < kRun) ? T - t0 : kRun);
+  const int64_t t0 = (int64_t)blockIdx.x * rl;
+  const int nt = (int)((T - t0 < rl) ? T - t0 : rl);
   CG cg;
   cg.load_taps(conv_w, C, c);
   cg.init(F, t0, S, C, c);
@@ -233,7 +244,7 @@ __global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F,
 // loads of a group of G tokens are issued together.  T is a multiple of G.
 template <typename TS, int KK, int G, bool RES, bool SAVE, bool NEXT>
 __global__ __launch_bounds__(256) void k_post_apply_run(TS* __restrict__ X, const TS* __restrict__ F, int64_t T,
-                                                        int64_t S, int N, int C,
+                                                        int64_t S, int N, int C, int rl,
                                                         const float* __restrict__ conv_w,
                                                         const int32_t* __restrict__ idx,
                                                         const float* __restrict__ Hres,
@@ -251,8 +262,8 @@ __global__ __launch_bounds__(256) void k_post_apply_run(TS* __restrict__ X, cons
   __shared__ int32_t s_idx[kRun * KK];
   __shared__ float s_hn[NEXT ? kRun * kMaxN : 1];
   const int c = (int)(blockIdx.y * blockDim.x + threadIdx.x) * 4;
-  const int64_t t0 = (int64_t)blockIdx.x * kRun;
-  const int nt = (int)((T - t0 < kRun) ? T - t0 : kRun);
+  const int64_t t0 = (int64_t)blockIdx.x * rl;
+  const int nt = (int)((T - t0 < rl) ? T - t0 : rl);
   for (int i = threadIdx.x; i < nt * KK; i += blockDim.x) s_idx[i] = idx[t0 * KK + i];
   // write-back weights of the run's tokens from their Gram partials (the same
   // per-token arithmetic as k_post_coef; every channel chunk of a run forms them)
@@ -354,14 +365,14 @@ hipError_t launch_post_gram(int state_dtype, const void* F, int64_t T, int64_t S
                             const int32_t* kappa, const float* conv_w, float* gpart, hipStream_t s) {
   if (T == 0) return hipSuccess;
   if (run_ok(C, S, Kr, kappa)) {
-    const int nthr = run_threads(C);
-    const dim3 grid((unsigned)((T + kRun - 1) / kRun), (unsigned)(C / (nthr * 4)));
+    const int nthr = run_threads(C), rl = run_len(T, C / (nthr * 4));
+    const dim3 grid((unsigned)((T + rl - 1) / rl), (unsigned)(C / (nthr * 4)));
     if (state_dtype == XHC_BF16)
       k_post_gram_run<uint16_t, 4, 8, 12><<<grid, dim3(nthr), 0, s>>>(reinterpret_cast<const uint16_t*>(F), T, S, C,
-                                                                      conv_w, gpart);
+                                                                      conv_w, rl, gpart);
     else
       k_post_gram_run<float, 4, 8, 12><<<grid, dim3(nthr), 0, s>>>(reinterpret_cast<const float*>(F), T, S, C,
-                                                                   conv_w, gpart);
+                                                                   conv_w, rl, gpart);
     return hipGetLastError();
   }
   const dim3 grid((unsigned)(T * post_chunks(C)));
@@ -474,11 +485,11 @@ hipError_t launch_post_apply(int state_dtype, void* X, const void* F, int64_t T,
   if (T == 0) return hipSuccess;
   if (gpart && run_ok(C, S, Kr, kappa) && T % 4 == 0 && (k == 4 || k == 8) &&
       !(Hres && input_next) && !(Xact_save && (input_next || !Hres))) {
-    const int nthr = run_threads(C);
-    const dim3 grid((unsigned)((T + kRun - 1) / kRun), (unsigned)(C / (nthr * 4)));
+    const int nthr = run_threads(C), rl = run_len(T, C / (nthr * 4));
+    const dim3 grid((unsigned)((T + rl - 1) / rl), (unsigned)(C / (nthr * 4)));
 #define XHC_APPLY_RUN(TS, KK, G, RES, SAVE, NEXT)                                                                  \
   k_post_apply_run<TS, KK, G, RES, SAVE, NEXT><<<grid, dim3(nthr), 0, s>>>(                                      \
-      reinterpret_cast<TS*>(X), reinterpret_cast<const TS*>(F), T, S, N, C, conv_w, idx, Hres, gpart, nchunk,    \
+      reinterpret_cast<TS*>(X), reinterpret_cast<const TS*>(F), T, S, N, C, rl, conv_w, idx, Hres, gpart, nchunk, \
       gram_schmidt, p, Hpost, Hpre_next,                                                                         \
       reinterpret_cast<const TS*>(base_next), reinterpret_cast<TS*>(input_next), reinterpret_cast<TS*>(Xact_save))
 #define XHC_APPLY_MODES(TS, KK, G)                                              \
