@@ -44,7 +44,7 @@ TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "traffic_xhc_pre_T16384_N16_C40
 
 # the sources whose device code one xhc_pre call runs (k_zero2, k_pre_fused,
 # k_pre_coef_sum and the helpers they inline)
-PRE_SOURCES = ("xhc_device.h", "xhc_pre.hip", "xhc_pre_fused.hip")
+PRE_SOURCES = ("xhc_device.h", "xhc_pre.hip", "xhc_pre_fused.h", "xhc_pre_fused.hip")
 
 
 def sources_digest():

@@ -88,7 +88,7 @@ size_t pre_ws_multi(const xhc_dims* d) {
 size_t pre_ws(const xhc_dims* d) {
   size_t need = 0;
   if (d->impl != XHC_IMPL_FUSED) need = pre_ws_multi(d);
-  if (d->impl != XHC_IMPL_MULTI && fused_pre_supported(d)) {
+  if (d->impl == XHC_IMPL_AUTO ? fused_pre_auto(d) : (d->impl == XHC_IMPL_FUSED && fused_pre_supported(d))) {
     const size_t f = fused_pre_ws_bytes(d);
     need = need > f ? need : f;
   }
@@ -446,7 +446,7 @@ xhc_status xhc_pre(const xhc_dims* d, const void* X, const void* packed_full, co
   if (workspace_bytes < pre_ws(d)) return XHC_EWORKSPACE;
   // AUTO takes the single-pass kernel where it applies (it reads X once) and
   // the multi-kernel path elsewhere
-  if (d->impl == XHC_IMPL_AUTO && !fused_pre_supported(d)) {
+  if (d->impl == XHC_IMPL_AUTO && !fused_pre_auto(d)) {
     xhc_dims m = *d;
     m.impl = XHC_IMPL_MULTI;
     return xhc_pre(&m, X, packed_full, packed_act, alpha, b_pre, b_res, b_post, input, idx, p, Hpre, Hres, Hpost,

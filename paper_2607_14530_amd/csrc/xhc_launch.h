@@ -103,7 +103,10 @@ hipError_t launch_stream_sum(int state_dtype, const void* X, int64_t T, int N, i
 hipError_t launch_stream_bcast(int state_dtype, const void* dout, int64_t T, int N, int C, int accumulate, void* dX,
                                hipStream_t s);
 
-// ---- pre (fused single-pass path: bf16 state, N = 16, k = 4, C % 128 == 0)
+// ---- pre (fused single-pass path: bf16 state, N = 16, k = 4, C % 32 == 0, C <= 4096).
+// fused_pre_auto: shapes AUTO takes it for; fused_pre_supported: those of
+// impl = FUSED (C = 128 G with G dividing 32)
+bool fused_pre_auto(const xhc_dims* d);
 bool fused_pre_supported(const xhc_dims* d);
 size_t fused_pre_ws_bytes(const xhc_dims* d);
 hipError_t launch_pre_fused(const xhc_dims* d, const void* X, const void* packed_full, const float* colsum,
