@@ -89,7 +89,7 @@ typedef struct xhc_dims {
 typedef enum { XHC_ROUTER_SIGMOID = 0, XHC_ROUTER_SOFTMAX = 1 } xhc_router;
 
 /* Kernel selection for xhc_pre.  AUTO takes the single-pass cooperative
- * kernel where it applies (bf16 state, N = 16, k = 4, 128 <= C <= 4096) and the
+ * kernel where it applies (bf16 state, N = 16, k = 4, C <= 4096) and the
  * multi-kernel path elsewhere, or when the device cannot hold the single-pass
  * grid.  MULTI forces the multi-kernel path.  FUSED forces the single-pass
  * kernel at C = 128 G with G dividing 32 and returns XHC_EUNSUPPORTED

@@ -1,5 +1,5 @@
 // Single-pass mapping generation + dense read of a full xHC sublayer
-// (bf16 state, N = 16, k = 4, K_r <= 4, C a multiple of 32, 128 .. 4096).
+// (bf16 state, N = 16, k = 4, K_r <= 4, C a multiple of 32, up to 4096).
 //
 // The state X is read from HBM exactly once.  A 16-token tile of X
 // ([16 tokens, 16 streams, C] = 2 MiB at C = 4096) is split over a team of G
@@ -36,9 +36,12 @@
 // so when wave 4 is the only reducer it neither polls nor publishes the
 // partials of A after S3 (it stores the active partials before S3, where it
 // would otherwise wait), and wave 0, which shares its SIMD, does not publish
-// either.  The kernel is launched
-// cooperatively, so every member of a team is resident; every wait is
-// bounded, so every wave exits.
+// either.  Teams form in the
+// order in which workgroups start (a ticket), so a launch has at most one team
+// that waits for members not yet started; the others run to their end and
+// free their CUs, and the last team then starts (see plain_launch for when
+// the launch is cooperative instead).  Every wait is bounded, so every wave
+// exits.
 //
 // SHORT: C is no multiple of 128 or the team is larger than the width needs
 // (an instance of its own: the exact one then has no trace of the zero
@@ -105,6 +108,7 @@ struct FusedArgs {
   uint64_t* rec1;         // [teams][RING][G][FM][NV1]
   uint64_t* rec2;         // [teams][RING][FM][NV2]
   int* err;
+  int* ticket;            // start order of the workgroups (cleared with err), or null: blockIdx order
   float* part2;           // [G][NV1][T] active partials
   int64_t T;
   int C;
@@ -248,7 +252,9 @@ __device__ __forceinline__ float lane_value(float v, int i) {
 template <int G, bool SHORT>
 __global__ __launch_bounds__(FNT, 1) void k_pre_fused(FusedArgs a) {
   constexpr int BREC = poll_recs(G);
-  extern __shared__ unsigned char tbuf[];   // [BUFB]; dynamic, as the LDS copy needs it
+  // [BUFB]; dynamic, as the LDS copy needs it (4 bytes off a 16-byte boundary
+  // its reads and copies cost 30 %: C = 4096 800 against 610 us)
+  extern __shared__ __align__(128) unsigned char tbuf[];
   __shared__ Smem<G> sm;
   __shared__ uint4 wal[KBAW][NOBA][FNW][kWave];
   __shared__ uint4 stage[FNW][FM][FK][2];   // routed rows of a tile per wave: [token][slot][channel half]
@@ -257,7 +263,19 @@ __global__ __launch_bounds__(FNT, 1) void k_pre_fused(FusedArgs a) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
   const int tl = lane % 16, grp = lane / 16;
   const int par = grp >> 1, half = grp & 1;   // stream parity and channel half of this lane
-  const int team = blockIdx.x / G, s = blockIdx.x % G;
+  // Members are numbered in the order in which workgroups start, so every team
+  // but the last started one is whole whatever else holds CUs (a cooperative
+  // launch numbers them by blockIdx).
+  // (unsigned, so that s < G is known and the roles fold to constants)
+  uint32_t member = blockIdx.x;
+  if (a.ticket) {
+    if (tid == 0)
+      sm.poff[0][0] = __hip_atomic_fetch_add(a.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    member = (uint32_t)__builtin_amdgcn_readfirstlane(sm.poff[0][0]);
+    __syncthreads();   // (poff is filled below)
+  }
+  const int team = member / G, s = member % G;
   if (team >= a.teams) return;
   const int C = a.C;
   const int T = (int)a.T;   // the launcher keeps T G NV1 below 2^31

@@ -1,5 +1,7 @@
 // Launch of the single-pass pre (xhc_pre_fused.h), and its instances for widths
 // that fill their team.
+#include <stdlib.h>
+
 #include "xhc_pre_fused.h"
 
 namespace xhc {
@@ -60,16 +62,36 @@ DeviceInfo device_info(int C) {
   return slot;
 }
 
+// Whether the launch may be a plain one.  A team waits for its members, so
+// launches in flight together must not fill the chip with unfinished teams
+// only: each has at most one (G - 1 workgroups), and HIP runs at most one
+// kernel per hardware queue at a time, 4 queues unless GPU_MAX_HW_QUEUES says
+// otherwise (streams of another priority have queues of their own).  With room
+// for 8 such teams beside one more workgroup the launch is plain; else it is
+// cooperative, which costs about 20 us more (T = 16, C = 4096: 54 against 36 us a
+// call, of which the kernels are 35).
+bool plain_launch(int G, int slots, hipStream_t s) {
+  constexpr int kQueues = 8;
+  static const int queues = [] {
+    const char* v = getenv("GPU_MAX_HW_QUEUES");
+    return v && *v ? atoi(v) : 4;
+  }();
+  if (queues < 1 || queues > kQueues || kQueues * (G - 1) >= slots) return false;
+  int prio = 0;
+  if (s && hipStreamGetPriority(s, &prio) != hipSuccess) return false;
+  return prio == 0;
+}
+
 }  // namespace
 
-// Where AUTO takes the single pass: it reads the state once where the
-// multi-kernel path reads it twice and needs three launches instead of seven.
-// Measured multi / single pass, K_r = 4: T = 8192 C = 2560 388 / 261 us, T =
-// 2048 C = 2112 157 / 101 us, T = 16 C = 2560 64 / 52 us; at C = 96 (one
-// member, a quarter of it padding) 46 / 56 us, hence the bound at one slice.
+// Where AUTO takes the single pass: at every width it has a team for.  It reads
+// the state once where the multi-kernel path reads it twice and needs three
+// launches instead of seven.  Measured multi / single pass, K_r = 4: T = 8192
+// C = 2560 387 / 243 us, T = 2048 C = 2112 157 / 83 us, T = 16 C = 2560 64 / 30
+// us, T = 16 C = 160 (one and a quarter slices) 48 / 30 us.
 bool fused_pre_auto(const xhc_dims* d) {
   return d->state_dtype == XHC_BF16 && d->N == FN && d->k == FK && d->Kr >= 1 &&
-         FK * d->Kr + FK * FK <= 16 * NOBA && d->C % 32 == 0 && d->C >= FCS && team_size(d->C) <= kMaxG &&
+         FK * d->Kr + FK * FK <= 16 * NOBA && d->C % 32 == 0 && team_size(d->C) <= kMaxG &&
          d->T * team_size(d->C) * NV1 < ((int64_t)1 << 31);   // 32-bit token and partial indices
 }
 
@@ -122,6 +144,8 @@ hipError_t launch_pre_fused(const xhc_dims* d, const void* X, const void* packed
   a.saved = saved;
   a.nsave = saved_floats(FN, FK, d->Kr);
   a.err = reinterpret_cast<int*>(w);
+  const bool plain = plain_launch(G, di.cus * di.per_cu, s);
+  a.ticket = plain ? reinterpret_cast<int*>(w + 128) : nullptr;
   a.rec1 = reinterpret_cast<uint64_t*>(w + 256);
   a.rec2 = reinterpret_cast<uint64_t*>(w + 256 + align256(rec1_words(d) * 8));
   a.part2 = reinterpret_cast<float*>(w + 256 + align256(rec1_words(d) * 8) + align256(rec2_words(d) * 8));
@@ -132,8 +156,8 @@ hipError_t launch_pre_fused(const xhc_dims* d, const void* X, const void* packed
   a.m = d->m;
   a.eps = d->eps;
   a.softmax = d->router == XHC_ROUTER_SOFTMAX ? 1 : 0;
-  // records start untagged: clear the error counter (with the first 256
-  // bytes) and the record slots in use, both whole 16-byte words
+  // records start untagged: clear the error counter and the ticket (the first
+  // 256 bytes) and the record slots in use, both whole 16-byte words
   const size_t used1 = (size_t)teams * RING * G * FM * NV1, used2 = (size_t)teams * RING * FM * NV2;
   const int64_t n1 = (int64_t)((256 + used1 * 8) / 16), n2 = (int64_t)((used2 * 8 + 15) / 16);
   k_zero2<<<dim3((unsigned)((n1 + n2 + 255) / 256)), dim3(256), 0, s>>>(reinterpret_cast<uint4*>(w), n1,
@@ -141,8 +165,9 @@ hipError_t launch_pre_fused(const xhc_dims* d, const void* X, const void* packed
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   void* args[] = {&a};
-  e = hipLaunchCooperativeKernel(fused_kernel(d->C), dim3(teams * G), dim3(FNT), args,
-                                 kTileLds, s);
+  const void* f = fused_kernel(d->C);
+  e = plain ? hipLaunchKernel(f, dim3(teams * G), dim3(FNT), args, kTileLds, s)
+            : hipLaunchCooperativeKernel(f, dim3(teams * G), dim3(FNT), args, kTileLds, s);
   if (e != hipSuccess) return e;
   // active partials -> H^post, H^res (Sinkhorn + clamp)
   return launch_pre_coef(a.part2, G, (int64_t)FK * d->Kr + FK * FK, d->T, FK, d->Kr, 1, d->C, alpha + 2, alpha + 1,

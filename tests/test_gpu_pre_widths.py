@@ -39,3 +39,27 @@ def test_single_pass_widths(C, T, Kr):
     same = same.to("cuda")
     n = saved.shape[1] - 1      # the last float is padding
     assert float((saved[same, :n] - ref[same, :n]).abs().max()) < 2e-4
+
+
+@pytest.mark.parametrize("C", [4096, 2112])
+def test_single_pass_on_several_streams(C):
+    """Single-pass calls in flight on several streams at once (a plain launch each, whose
+    last team may wait for CUs the others hold): the results of the calls one by one."""
+    w = synth.Workload(T=600, N=16, k=4, m=2, C=C, Kr=4, name=f"streams-C{C}")
+    inps = [synth.sublayer_inputs(w, 80 + i, device="cuda") for i in range(3)]
+    subs = [X.Sublayer(X.dims_for(w), inp, "cuda") for inp in inps]
+    names = ("input", "idx", "p", "Hpre", "Hres", "Hpost")
+    refs = []
+    for sub, inp in zip(subs, inps):
+        sub.pre(inp["X"])
+        torch.cuda.synchronize()
+        refs.append({n: getattr(sub, n).clone() for n in names})
+    streams = [torch.cuda.Stream() for _ in subs]
+    for _ in range(6):
+        for sub, inp, st in zip(subs, inps, streams):
+            sub.pre(inp["X"], stream=st)
+    torch.cuda.synchronize()
+    for sub, ref in zip(subs, refs):
+        assert sub.pre_failures() == 0
+        for n in names:
+            assert torch.equal(getattr(sub, n), ref[n]), n
