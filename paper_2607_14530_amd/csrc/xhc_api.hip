@@ -173,7 +173,7 @@ xhc_dims dims_rows32(const xhc_dims* d, int Kq) {
 
 struct FlashPostBwdWs {
   size_t post, pre, part, sums, idx_id, hres_id, hsel, da_out, dhpost, dhres, dp,
-      saved, hpost_re, hres_re, w0, colsum0, wres0, bres0, alpha2, dwr, dwpre, dbpre, dwres, dbres, dalpha2, total;
+      saved, hpost_re, hres_re, wres0, bres0, alpha2, dwr, dwpre, dbpre, dwres, dbres, dalpha2, total;
 };
 
 FlashPostBwdWs flash_post_bwd_ws(const xhc_dims* d, int Q, int q) {
@@ -198,8 +198,6 @@ FlashPostBwdWs flash_post_bwd_ws(const xhc_dims* d, int Q, int q) {
   w.saved = c.take((size_t)T * saved_floats(k, k, Kq) * f);
   w.hpost_re = c.take((size_t)T * k * Kq * f);
   w.hres_re = c.take((size_t)T * k * k * f);
-  w.w0 = c.take((size_t)kC * k * f);
-  w.colsum0 = c.take((size_t)k * f);
   w.wres0 = c.take((size_t)kC * k * k * f);
   w.bres0 = c.take((size_t)k * k * f);
   w.alpha2 = c.take(3 * f);
@@ -217,8 +215,7 @@ struct FlashPreBwdWs {
   size_t pre_slice;   // one pre-map reverse's workspace (Q of them when the row passes are fused)
   bool fused;
   size_t multi;       // the fused row pass's per-token inputs
-  size_t pre, part, sums, saved, idx_s, p_s, hpre_s, hmask, wpost0, wres0, bres0, hpost0, dhpost0, dhres0, dp0,
-      alpha_e, dwr, dwres, dwpost, dalpha, dbres, dbpost, total;
+  size_t pre, part, sums, saved, idx_s, p_s, hpre_s, hmask, alpha_e, dwr, dwres, dwpost, dalpha, dbres, dbpost, total;
 };
 
 FlashPreBwdWs flash_pre_bwd_ws(const xhc_dims* d, int Q) {
@@ -239,13 +236,6 @@ FlashPreBwdWs flash_pre_bwd_ws(const xhc_dims* d, int Q) {
   w.p_s = c.take((size_t)T * k * f);
   w.hpre_s = c.take((size_t)Q * T * N * f);
   w.hmask = c.take((size_t)Q * T * N * f);   // [Q][T, N]: the masked dense-read weights of pre-map q >= 1
-  w.wpost0 = c.take((size_t)kC * k * f);
-  w.wres0 = c.take((size_t)kC * k * k * f);
-  w.bres0 = c.take((size_t)k * k * f);
-  w.hpost0 = c.take((size_t)T * k * f);
-  w.dhpost0 = c.take((size_t)T * k * f);
-  w.dhres0 = c.take((size_t)T * k * k * f);
-  w.dp0 = c.take((size_t)T * k * f);
   w.alpha_e = c.take(3 * f);
   w.dwr = c.take((size_t)NC * N * f);
   w.dwres = c.take((size_t)kC * k * k * f);
@@ -747,12 +737,10 @@ xhc_status xhc_flash_post_bwd(const xhc_dims* d, int32_t Q, int32_t q, const voi
   int32_t* idx_id = reinterpret_cast<int32_t*>(ws + w.idx_id);
   float* hres_use = last ? const_cast<float*>(Hres) : F32(w.hres_id);
   hipError_t e = hipSuccess;
-  // zero the dummy operands (weights of the absent pre-map and router, the
-  // saved logits the recompute leaves empty), and for q < Q the residual
-  // mapping that sublayer does not have
+  // zero the saved logits the recompute leaves empty, and for q < Q the weights
+  // of the residual mapping that sublayer does not have
   if (!saved_act)
     XHC_STEP("fbwd_zero", launch_fill0(ws + w.saved, (size_t)T * saved_floats(k, k, Kq) * sizeof(float), s));
-  XHC_STEP("fbwd_zero", launch_fill0(ws + w.w0, w.wres0 - w.w0, s));   // w0, colsum0
   if (!last) XHC_STEP("fbwd_zero", launch_fill0(ws + w.wres0, w.alpha2 - w.wres0, s));   // wres0, bres0
   // slot map, identity mixing, pre-map weights of the active streams, <d input_q, a_j>
   XHC_STEP("fbwd_token", launch_fbwd_token(d->state_dtype, T, d->N, (int)k, (int)C, idx, Hpre_q, d_input, Xact,
@@ -769,7 +757,6 @@ xhc_status xhc_flash_post_bwd(const xhc_dims* d, int32_t Q, int32_t q, const voi
                                         dF, F32(w.dhres), F32(w.dhpost), F32(w.dp), dconv_w, ws + w.post, s,
                                         /*grad_f32=*/true));
   XHC_STEP("fbwd_dp", launch_fbwd_add(dp, F32(w.dp), T * k, s));
-  if (!last) XHC_STEP("fbwd_zero", launch_fill0(ws + w.dhres, (size_t)T * k * k * sizeof(float), s));
   // the mapping logits of sublayer q: saved by the forward, or recomputed
   // from a^(q-1) (same kernels and operands as the forward)
   const int64_t na = act_outs(d, Kq, last);
@@ -789,10 +776,10 @@ xhc_status xhc_flash_post_bwd(const xhc_dims* d, int32_t Q, int32_t q, const voi
   // no router or pre-map weights)
   // (the fp32 view's own row pass reads Xact only for an fp32 state; a bf16
   // state goes through the MFMA pass on Xact as saved)
-  XHC_STEP("fbwd_pre", launch_bwd_pre(&r, Xact, F32(w.colsum0), F32(w.w0), F32(w.w0),
+  XHC_STEP("fbwd_pre", launch_bwd_pre(&r, Xact, nullptr, nullptr, nullptr,
                                       last ? W_res : F32(w.wres0), W_post, F32(w.alpha2),
                                       last ? b_res : F32(w.bres0), rec, idx_id, p, F32(w.hsel), Hpost,
-                                      nullptr, F32(w.dhres), F32(w.dhpost), F32(w.dp), dA_out,
+                                      nullptr, last ? F32(w.dhres) : nullptr, F32(w.dhpost), F32(w.dp), dA_out,
                                       F32(w.dwr), F32(w.dwpre), last ? dW_res : F32(w.dwres), dW_post,
                                       F32(w.dalpha2), F32(w.dbpre), last ? db_res : F32(w.dbres), db_post,
                                       ws + w.pre, s, nullptr, nullptr, /*dense_rows=*/false,
@@ -843,7 +830,6 @@ xhc_status xhc_flash_pre_bwd(const xhc_dims* d, int32_t Q, const void* X, const 
                                                        packed_frag_bytes(NC, nf));
   hipError_t e = hipSuccess;
   if (!saved) XHC_STEP("fpbwd_zero", launch_fill0(ws + w.saved, (size_t)T * nsave * sizeof(float), s));
-  XHC_STEP("fpbwd_zero", launch_fill0(ws + w.wpost0, w.alpha_e - w.wpost0, s));   // zero operands
   // the group-entry logits and statistics: saved by the forward, or
   // recomputed as the forward made them
   if (!saved)
@@ -879,10 +865,10 @@ xhc_status xhc_flash_pre_bwd(const xhc_dims* d, int32_t Q, const void* X, const 
     }
     hrd[q] = q >= 1 ? hm : Hpre;
     wsq[q] = wq;
-    return launch_bwd_pre(&en, X, colsum, W_r, W_pre + (int64_t)q * NC * N, F32(w.wres0), F32(w.wpost0),
-                          F32(w.alpha_e), F32(w.bres0), rec, idx, p, Hpre + (int64_t)q * T * N,
-                          F32(w.hpost0), reinterpret_cast<const char*>(d_input) + (size_t)q * T * C * es,
-                          F32(w.dhres0), F32(w.dhpost0), q == 0 ? dp : F32(w.dp0), dX, q == 0 ? dW_r : F32(w.dwr),
+    return launch_bwd_pre(&en, X, colsum, W_r, W_pre + (int64_t)q * NC * N, nullptr, nullptr,
+                          F32(w.alpha_e), nullptr, rec, idx, p, Hpre + (int64_t)q * T * N,
+                          nullptr, reinterpret_cast<const char*>(d_input) + (size_t)q * T * C * es,
+                          nullptr, nullptr, q == 0 ? dp : nullptr, dX, q == 0 ? dW_r : F32(w.dwr),
                           dW_pre + (int64_t)q * NC * N, F32(w.dwres), F32(w.dwpost), F32(w.dalpha),
                           db_pre + (int64_t)q * N, F32(w.dbres), F32(w.dbpost), wq, s,
                           q >= 1 ? dHpre_act + (int64_t)(q - 1) * T * k : nullptr, q >= 1 ? hm : nullptr,

@@ -83,168 +83,61 @@ __device__ inline void gram_schmidt_basis_reverse(const double (&G)[kMaxKr][kMax
   }
 }
 
-// Forward Sinkhorn state after `steps` normalisations (rows first) of exp(L - rowmax).
-__device__ inline void sinkhorn_steps(const float (&L)[kMaxK * kMaxK], int k, int steps, float (&M)[kMaxK * kMaxK]) {
-  for (int j = 0; j < k; ++j) {
-    float mx = L[j * kMaxK];
-    for (int l = 1; l < k; ++l) mx = fmaxf(mx, L[j * kMaxK + l]);
-    for (int l = 0; l < k; ++l) M[j * kMaxK + l] = __expf(L[j * kMaxK + l] - mx);
-  }
-  for (int s = 0; s < steps; ++s) {
-    if ((s & 1) == 0) {
-      for (int j = 0; j < k; ++j) {
-        float sum = 0.f;
-        for (int l = 0; l < k; ++l) sum += M[j * kMaxK + l];
-        const float r = 1.0f / sum;
-        for (int l = 0; l < k; ++l) M[j * kMaxK + l] *= r;
-      }
-    } else {
-      for (int l = 0; l < k; ++l) {
-        float sum = 0.f;
-        for (int j = 0; j < k; ++j) sum += M[j * kMaxK + l];
-        const float r = 1.0f / sum;
-        for (int j = 0; j < k; ++j) M[j * kMaxK + l] *= r;
-      }
-    }
-  }
-}
-
-// dL of H = clamp(SK_iters(exp(L))) given dH; the forward iterates are recomputed.
-__device__ inline void sinkhorn_clamp_reverse(const float (&L)[kMaxK * kMaxK], int k, int iters, float delta,
-                                              const float (&dH)[kMaxK * kMaxK], float (&dL)[kMaxK * kMaxK]) {
-  float M[kMaxK * kMaxK], g[kMaxK * kMaxK];
+// dL of H = clamp(SK_iters(exp(L))) given dH, one element per lane (the layout
+// of sinkhorn_clamp_lanes).  The normaliser of every step and its reciprocal
+// are kept in LDS for kSkSeg steps at a time (norm[step][line of this token],
+// stride elements apart) and the reverse walks back through them, undoing each
+// normalisation on the iterate; more steps take segments of kSkSeg, the last
+// first, each with the iterate at its start formed again.  Every lane of the
+// wave takes part.
+constexpr int kSkSeg = 40;   // the paper's 20 iterations
+template <int KP>
+__device__ __forceinline__ float sinkhorn_clamp_reverse_lanes(float L, bool used, int iters, float delta, float dH,
+                                                              int j, int l, float2* norm, int stride) {
+  const float E = mix_exp<KP>(L, used);
   const int steps = 2 * iters;
-  sinkhorn_steps(L, k, steps, M);
+  float M = E, g = 0.f;
+  // steps s0 .. s1 - 1 forward from M (rows first), kept when keep is set
+  auto forward = [&](int s0, int s1, bool keep) {
+    for (int st = s0; st < s1; ++st) {
+      const bool row = (st & 1) == 0;
+      const float sum = row ? mix_row_sum<KP>(M) : mix_col_sum<KP>(M);
+      const float r = 1.0f / sum;
+      M = used ? M * r : 0.f;
+      if (keep && used && (row ? l : j) == 0) norm[((st - s0) * KP + (row ? j : l)) * stride] = make_float2(sum, r);
+    }
+  };
+  int s0 = steps > 0 ? (steps - 1) / kSkSeg * kSkSeg : 0;
+  forward(0, s0, false);
+  forward(s0, steps, true);
   // row clamp
-  for (int j = 0; j < k; ++j) {
-    float s = 0.f;
-    for (int l = 0; l < k; ++l) s += M[j * kMaxK + l];
-    if (s > 1.0f + delta) {
-      float dot = 0.f;
-      for (int l = 0; l < k; ++l) dot += dH[j * kMaxK + l] * (M[j * kMaxK + l] / s);
-      for (int l = 0; l < k; ++l) g[j * kMaxK + l] = (dH[j * kMaxK + l] - dot) / s;
-    } else {
-      for (int l = 0; l < k; ++l) g[j * kMaxK + l] = dH[j * kMaxK + l];
+  {
+    const float s = mix_row_sum<KP>(M);
+    const float dot = mix_row_sum<KP>(dH * M);
+    g = s > 1.0f + delta ? (dH - dot / s) / s : dH;
+    if (!used) g = 0.f;
+  }
+  for (int s1 = steps; s1 > 0; s1 = s0, s0 -= kSkSeg) {
+    if (s1 != steps) {
+      M = E;
+      forward(0, s0, false);
+      forward(s0, s1, true);
     }
-  }
-  for (int s = steps - 1; s >= 0; --s) {
-    sinkhorn_steps(L, k, s, M);   // input of normalisation step s
-    if ((s & 1) == 0) {           // row normalisation: y = m / sum_l m
-      for (int j = 0; j < k; ++j) {
-        float sum = 0.f;
-        for (int l = 0; l < k; ++l) sum += M[j * kMaxK + l];
-        float dot = 0.f;
-        for (int l = 0; l < k; ++l) dot += g[j * kMaxK + l] * (M[j * kMaxK + l] / sum);
-        for (int l = 0; l < k; ++l) g[j * kMaxK + l] = (g[j * kMaxK + l] - dot) / sum;
-      }
-    } else {                      // column normalisation
-      for (int l = 0; l < k; ++l) {
-        float sum = 0.f;
-        for (int j = 0; j < k; ++j) sum += M[j * kMaxK + l];
-        float dot = 0.f;
-        for (int j = 0; j < k; ++j) dot += g[j * kMaxK + l] * (M[j * kMaxK + l] / sum);
-        for (int j = 0; j < k; ++j) g[j * kMaxK + l] = (g[j * kMaxK + l] - dot) / sum;
-      }
+    // the lanes of a wave read what other lanes of it wrote
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // M holds the output of step st; its input is M times the step's normaliser
+    for (int st = s1 - 1; st >= s0; --st) {
+      const bool row = (st & 1) == 0;
+      const float2 n = used ? norm[((st - s0) * KP + (row ? j : l)) * stride] : make_float2(0.f, 0.f);
+      const float dot = row ? mix_row_sum<KP>(g * M) : mix_col_sum<KP>(g * M);
+      g = (g - dot) * n.y;
+      M *= n.x;
     }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
-  sinkhorn_steps(L, k, 0, M);     // exp(L - rowmax); the shift does not change H
-  for (int j = 0; j < k; ++j)
-    for (int l = 0; l < k; ++l) dL[j * kMaxK + l] = g[j * kMaxK + l] * M[j * kMaxK + l];
-}
-
-// The same for a compile-time k: the forward normaliser of every step is kept
-// (sk[step][j] at sk[(step * K + j) * stride], LDS), so the reverse walks back
-// step by step, undoing each normalisation on the iterate instead of
-// recomputing it from the start.
-constexpr int kSkMaxSteps = 64;   // 2 x sinkhorn_iters handled by the fast reverse
-template <int K>
-__device__ inline void sinkhorn_clamp_reverse_fast(const float (&L)[K * K], int iters, float delta,
-                                                   const float (&dH)[K * K], float (&dL)[K * K], float* sk,
-                                                   int stride) {
-  float E[K * K], M[K * K], g[K * K];
-#pragma unroll
-  for (int j = 0; j < K; ++j) {
-    float mx = L[j * K];
-#pragma unroll
-    for (int l = 1; l < K; ++l) mx = fmaxf(mx, L[j * K + l]);
-#pragma unroll
-    for (int l = 0; l < K; ++l) M[j * K + l] = E[j * K + l] = __expf(L[j * K + l] - mx);
-  }
-  const int steps = 2 * iters;
-  for (int st = 0; st < steps; ++st) {
-    if ((st & 1) == 0) {
-#pragma unroll
-      for (int j = 0; j < K; ++j) {
-        float sum = 0.f;
-#pragma unroll
-        for (int l = 0; l < K; ++l) sum += M[j * K + l];
-        sk[(st * K + j) * stride] = sum;
-        const float r = 1.0f / sum;
-#pragma unroll
-        for (int l = 0; l < K; ++l) M[j * K + l] *= r;
-      }
-    } else {
-#pragma unroll
-      for (int l = 0; l < K; ++l) {
-        float sum = 0.f;
-#pragma unroll
-        for (int j = 0; j < K; ++j) sum += M[j * K + l];
-        sk[(st * K + l) * stride] = sum;
-        const float r = 1.0f / sum;
-#pragma unroll
-        for (int j = 0; j < K; ++j) M[j * K + l] *= r;
-      }
-    }
-  }
-  // row clamp
-#pragma unroll
-  for (int j = 0; j < K; ++j) {
-    float sum = 0.f;
-#pragma unroll
-    for (int l = 0; l < K; ++l) sum += M[j * K + l];
-    if (sum > 1.0f + delta) {
-      float dot = 0.f;
-#pragma unroll
-      for (int l = 0; l < K; ++l) dot += dH[j * K + l] * (M[j * K + l] / sum);
-#pragma unroll
-      for (int l = 0; l < K; ++l) g[j * K + l] = (dH[j * K + l] - dot) / sum;
-    } else {
-#pragma unroll
-      for (int l = 0; l < K; ++l) g[j * K + l] = dH[j * K + l];
-    }
-  }
-  // M holds the output of step st; its input is M times the step's normaliser
-  for (int st = steps - 1; st >= 0; --st) {
-    if ((st & 1) == 0) {
-#pragma unroll
-      for (int j = 0; j < K; ++j) {
-        const float sum = sk[(st * K + j) * stride];
-        float dot = 0.f;
-#pragma unroll
-        for (int l = 0; l < K; ++l) dot += g[j * K + l] * M[j * K + l];
-#pragma unroll
-        for (int l = 0; l < K; ++l) {
-          g[j * K + l] = (g[j * K + l] - dot) / sum;
-          M[j * K + l] *= sum;
-        }
-      }
-    } else {
-#pragma unroll
-      for (int l = 0; l < K; ++l) {
-        const float sum = sk[(st * K + l) * stride];
-        float dot = 0.f;
-#pragma unroll
-        for (int j = 0; j < K; ++j) dot += g[j * K + l] * M[j * K + l];
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-          g[j * K + l] = (g[j * K + l] - dot) / sum;
-          M[j * K + l] *= sum;
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < K * K; ++i) dL[i] = g[i] * E[i];
+  return g * E;   // (the row maximum's shift does not change H)
 }
 
 // ------------------------------------------------------------ post backward
@@ -1211,153 +1104,143 @@ __global__ __launch_bounds__(256) void k_bwd_dhpre_multi(const TS* __restrict__ 
 //   [dz_r (N) | dz_pre (N) | dz_act (NA) | r | r_ln | mu | beta_pre | m1 | m2 | r_a | beta_a]
 // and per-token gating/bias gradients pg: [dalpha_pre, dalpha_res, dalpha_post | db_pre (N) |
 // db_res (k*k) | db_post (k*Kr)].
-// dL/dH^pre of the active streams given per slot: the chunk partials of
-// <d input, x_i> at i = idx[t, j] become dhact[t, j] (first chunk) and 0.
-__global__ __launch_bounds__(256) void k_bwd_dhpre_override(const float* __restrict__ dhact,
-                                                            const int32_t* __restrict__ idx, int64_t T, int N, int k,
-                                                            int64_t nchunk, float* __restrict__ part) {
-  const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= T * k) return;
-  const int64_t t = u / k;
-  const int i = idx[u];
-  for (int64_t c = 0; c < nchunk; ++c) part[(c * N + i) * T + t] = c == 0 ? dhact[u] : 0.0f;
-}
 
 __host__ __device__ inline int tok_floats(int N, int NA) { return 2 * N + NA + 8; }
 __host__ __device__ inline int pg_floats(int N, int k, int Kr) { return 3 + N + k * k + k * Kr; }
 
-// KC > 0: k == KC at compile time, Sinkhorn reversed with kept normalisers;
-// KC == 0: any k, Sinkhorn reversed by recomputing the forward iterates.
-constexpr int kPreTokThreads = 64;
-template <int KC>
-__global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(
-    const float* __restrict__ part, int64_t nchunk, int64_t T, int N, int m, int k_rt, int Kr, int C,
-    const float* __restrict__ saved, const float* __restrict__ colsum, const float* __restrict__ alpha,
-    const float* __restrict__ b_res, const int32_t* __restrict__ idx, const float* __restrict__ p,
-    const float* __restrict__ Hpre, const float* __restrict__ Hpost, const float* __restrict__ dHres,
-    const float* __restrict__ dHpost, const float* __restrict__ dp, float eps, int iters, float delta,
-    float* __restrict__ tok, float* __restrict__ pg, int softmax) {
-  __shared__ float sk[KC > 0 ? kSkMaxSteps * KC * kPreTokThreads : 1];
-  const int k = KC > 0 ? KC : k_rt;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= T) return;
+struct PreTokArgs {
+  const float* part;     // <d input, x_i> partials [nchunk][N][T], or null: no pre-map term
+  int64_t nchunk;
+  int64_t T;
+  int N, m, k, Kr, C;
+  const float *saved, *colsum, *alpha, *b_res;
+  const int32_t* idx;
+  const float *p, *Hpre, *Hpost;
+  const float* dHres;    // null: no residual mapping (its gradients are zero)
+  const float* dHpost;   // null: no active-row outputs at all
+  const float* dp;       // null: no router gradient
+  const float* dhact;    // [T, k] or null: replaces <d input, x_i> of the active streams
+  float eps;
+  int iters;
+  float delta;
+  float *tok, *pg;
+  int softmax;
+};
+
+// Per-token reverses, mix_lanes(KP) lanes a token (k <= KP): streams, outputs
+// and the elements of the mixing matrix are spread over the lanes.  Bound by
+// the chain of the Sinkhorn reverse, not by its data: with one thread per
+// token it took 40 us at any T at k = 4 and 790 us at k = 2, where every step
+// back recomputed the iterate (T = 13608).
+constexpr int kPreTokThreads = 256;
+template <int KP>
+__global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(PreTokArgs a) {
+  constexpr int GL = mix_lanes(KP), NT = kPreTokThreads / GL;   // lanes a token, tokens a workgroup
+  __shared__ float sdh[kMaxN][NT];
+  __shared__ float2 norm[kSkSeg * KP * NT];
+  const int N = a.N, m = a.m, k = a.k, Kr = a.Kr;
+  const int64_t T = a.T, tb = (int64_t)blockIdx.x * NT;
+  const int u = threadIdx.x / GL, e = threadIdx.x % GL;
+  const bool in = tb + u < T;
+  const int64_t t = in ? tb + u : T - 1;   // (a token past the end works on the last one and writes nothing)
+  // the inner products of the workgroup's tokens: chunk sums in the order
+  // chunk 0, 1, ..., then the given ones of the active streams
+  if (a.part) {
+    for (int i = threadIdx.x; i < N * NT; i += kPreTokThreads) {
+      const int64_t tt = tb + i % NT < T ? tb + i % NT : T - 1;
+      const float* pc = a.part + (int64_t)(i / NT) * T + tt;
+      float v = 0.f;
+      for (int64_t c = 0; c < a.nchunk; ++c) v += pc[c * N * T];
+      sdh[i / NT][i % NT] = v;
+    }
+    __syncthreads();
+    if (a.dhact && e < k) sdh[a.idx[t * k + e]][u] = a.dhact[t * k + e];
+    __syncthreads();
+  }
   const int NA = k * Kr + k * k, ns = saved_floats(N, k, Kr);
-  const float* sv = saved + t * ns;
-  float* tk = tok + t * tok_floats(N, NA);
-  float* g = pg + t * pg_floats(N, k, Kr);
+  const float* sv = a.saved + t * ns;
+  float* tk = a.tok + t * tok_floats(N, NA);
+  float* g = a.pg + t * pg_floats(N, k, Kr);
   const float mu = sv[ns - 4], nu = sv[ns - 3], nu_a = sv[ns - 2];
-  const float NC = (float)N * (float)C, kC = (float)k * (float)C;
-  const float r = 1.0f / sqrtf(nu + eps), r_ln = 1.0f / sqrtf(ln_variance(mu, nu) + eps);
-  const float r_a = 1.0f / sqrtf(nu_a + eps);
-  const float a_pre = alpha[0], a_res = alpha[1], a_post = alpha[2];
+  const float NC = (float)N * (float)a.C, kC = (float)k * (float)a.C;
+  const float r = 1.0f / sqrtf(nu + a.eps), r_ln = 1.0f / sqrtf(ln_variance(mu, nu) + a.eps);
+  const float r_a = 1.0f / sqrtf(nu_a + a.eps);
+  const float a_pre = a.alpha[0], a_res = a.alpha[1], a_post = a.alpha[2];
   // pre-map: H = sigma(a z + b)
-  float da_pre = 0.f, bp = 0.f;
-  for (int i0 = 0; i0 < N; i0 += 16) {
-    // 16 streams at a time: each chunk's 16 partials loaded together (streams
-    // past N read stream i0 and are not used), summed in the order chunk 0, 1, ...
-    float dh[16], hv[16], zv[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) dh[u] = 0.f;
-    for (int64_t c = 0; c < nchunk; ++c) {
-      float v[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = part[(c * N + (i0 + u < N ? i0 + u : i0)) * T + t];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) dh[u] += v[u];
+  float da_pre = 0.f;
+  for (int i = e; i < N; i += GL) {
+    float ds = 0.f;
+    if (a.part) {
+      const float hv = a.Hpre[t * N + i];
+      ds = sdh[i][u] * hv * (1.0f - hv);
+      da_pre += ds * sv[N + i];
     }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int i = i0 + u < N ? i0 + u : i0;
-      hv[u] = Hpre[t * N + i];
-      zv[u] = sv[N + i];
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int i = i0 + u;
-      if (i >= N) break;
-      const float ds = dh[u] * hv[u] * (1.0f - hv[u]);
+    if (in) {
       tk[N + i] = a_pre * ds;
-      da_pre += ds * zv[u];
       g[3 + i] = ds;
-      bp += a_pre * ds * zv[u];
     }
   }
-  const float beta_pre = r * r * bp / NC;
+  da_pre = mix_group_sum<KP>(da_pre);
+  const float beta_pre = r * r * (a_pre * da_pre) / NC;
   // router: only routed slots carry gradient, through p = sigma(z_r); with the
   // softmax router p = s_i of s = softmax(z_r) over the N streams, so every
   // logit gets dz_i = s_i (g_i - sum_l s_l g_l), g_i = dp of the slot of i
-  for (int i = 0; i < N; ++i) tk[i] = 0.f;
   float m1 = 0.f, m2 = 0.f;
-  if (!softmax) {
-    for (int j = m; j < k; ++j) {
-      const int i = idx[t * k + j];
-      const float pj = p[t * k + j];
-      const float dz = dp[t * k + j] * pj * (1.0f - pj);
-      tk[i] = dz;
-      m1 += colsum[i] * dz;
+  const bool route = a.dp && k > m;
+  float mx = 0.f, den = 1.f, dot = 0.f;
+  if (route && a.softmax) {
+    mx = sv[0];
+    for (int i = 1; i < N; ++i) mx = fmaxf(mx, sv[i]);
+    den = 0.f;
+    for (int i = 0; i < N; ++i) den += __expf(sv[i] - mx);
+    for (int j = m; j < k; ++j) dot += a.p[t * k + j] * a.dp[t * k + j];
+  }
+  for (int i = e; i < N; i += GL) {
+    float dz = 0.f;
+    if (route) {
+      if (a.softmax) dz = -(__expf(sv[i] - mx) / den) * dot;
+      for (int j = m; j < k; ++j)
+        if (a.idx[t * k + j] == i) {
+          const float pj = a.p[t * k + j], dpj = a.dp[t * k + j];
+          dz += a.softmax ? pj * dpj : dpj * pj * (1.0f - pj);
+        }
+      m1 += a.colsum[i] * dz;
       m2 += sv[i] * dz;
     }
-  } else if (k > m) {
-    float mx = sv[0];
-    for (int i = 1; i < N; ++i) mx = fmaxf(mx, sv[i]);
-    float den = 0.f;
-    for (int i = 0; i < N; ++i) den += __expf(sv[i] - mx);
-    float dot = 0.f;
-    for (int j = m; j < k; ++j) dot += p[t * k + j] * dp[t * k + j];
-    for (int i = 0; i < N; ++i) tk[i] = -(__expf(sv[i] - mx) / den) * dot;
-    for (int j = m; j < k; ++j) tk[idx[t * k + j]] += p[t * k + j] * dp[t * k + j];
-    for (int i = 0; i < N; ++i) {
-      m1 += colsum[i] * tk[i];
-      m2 += sv[i] * tk[i];
-    }
+    if (in) tk[i] = dz;
   }
-  m1 /= NC;
-  m2 /= NC;
+  m1 = mix_group_sum<KP>(m1) / NC;
+  m2 = mix_group_sum<KP>(m2) / NC;
   // post-map: H = 2 sigma(a z + b)
-  float da_post = 0.f, ba = 0.f;
-  for (int o = 0; o < k * Kr; ++o) {
-    const float h = Hpost[t * k * Kr + o];
-    const float du = dHpost[t * k * Kr + o] * h * (1.0f - 0.5f * h);
-    const float z = sv[2 * N + o];
-    tk[2 * N + o] = a_post * du;
-    da_post += du * z;
-    g[3 + N + k * k + o] = du;
-    ba += a_post * du * z;
-  }
-  // residual map: H = clamp(SK(exp(a z + b)))
-  constexpr int KS = KC > 0 ? KC : kMaxK;   // row stride of the matrices below
-  float dL[KS * KS];
-  if constexpr (KC > 0) {
-    float L[KC * KC], dH[KC * KC];
-#pragma unroll
-    for (int j = 0; j < KC; ++j)
-#pragma unroll
-      for (int l = 0; l < KC; ++l) {
-        L[j * KC + l] = a_res * sv[2 * N + KC * Kr + j * KC + l] + b_res[j * KC + l];
-        dH[j * KC + l] = dHres[(t * KC + j) * KC + l];
+  float da_post = 0.f, da_res = 0.f;
+  if (a.dHpost) {
+    for (int o = e; o < k * Kr; o += GL) {
+      const float h = a.Hpost[t * k * Kr + o];
+      const float du = a.dHpost[t * k * Kr + o] * h * (1.0f - 0.5f * h);
+      da_post += du * sv[2 * N + o];
+      if (in) {
+        tk[2 * N + o] = a_post * du;
+        g[3 + N + k * k + o] = du;
       }
-    sinkhorn_clamp_reverse_fast<KC>(L, iters, delta, dH, dL, &sk[threadIdx.x], kPreTokThreads);
-  } else {
-    float L[kMaxK * kMaxK], dH[kMaxK * kMaxK];
-    for (int j = 0; j < kMaxK; ++j)
-      for (int l = 0; l < kMaxK; ++l) {
-        const bool in = j < k && l < k;
-        L[j * kMaxK + l] = in ? a_res * sv[2 * N + k * Kr + j * k + l] + b_res[j * k + l] : 0.f;
-        dH[j * kMaxK + l] = in ? dHres[(t * k + j) * k + l] : 0.f;
-        dL[j * kMaxK + l] = 0.f;
-      }
-    sinkhorn_clamp_reverse(L, k, iters, delta, dH, dL);
-  }
-  float da_res = 0.f;
-  for (int j = 0; j < k; ++j)
-    for (int l = 0; l < k; ++l) {
-      const float z = sv[2 * N + k * Kr + j * k + l];
-      const float d = dL[j * KS + l];
-      tk[2 * N + k * Kr + j * k + l] = a_res * d;
-      da_res += d * z;
-      g[3 + N + j * k + l] = d;
-      ba += a_res * d * z;
     }
+    da_post = mix_group_sum<KP>(da_post);
+    // residual map: H = clamp(SK(exp(a z + b)))
+    const int j = e / KP % KP, l = e % KP;
+    const bool used = e < KP * KP && j < k && l < k;
+    const int o = used ? j * k + l : 0;
+    float d = 0.f;
+    if (a.dHres) {
+      const float z = sv[2 * N + k * Kr + o];
+      d = sinkhorn_clamp_reverse_lanes<KP>(a_res * z + a.b_res[o], used, a.iters, a.delta,
+                                           used ? a.dHres[t * k * k + o] : 0.f, j, l, norm + u, NT);
+      da_res = mix_group_sum<KP>(used ? d * z : 0.f);
+    }
+    if (used && in) {
+      tk[2 * N + k * Kr + o] = a_res * d;
+      g[3 + N + o] = d;
+    }
+  }
+  if (e != 0 || !in) return;
   g[0] = da_pre;
   g[1] = da_res;
   g[2] = da_post;
@@ -1369,7 +1252,7 @@ __global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(
   sc[4] = m1;
   sc[5] = m2;
   sc[6] = r_a;
-  sc[7] = r_a * r_a * ba / kC;
+  sc[7] = r_a * r_a * (a_post * da_post + a_res * da_res) / kC;
 }
 
 // Weight-stationary pass over rows K = i*C + c of [W_r | W_pre] (one row per
@@ -2270,32 +2153,46 @@ hipError_t launch_bwd_pre(const xhc_dims* d, const void* X, const float* colsum,
     // the row passes ran elsewhere (their partials are in this workspace)
     if (mf) k_mu_dz_sum<<<dim3((unsigned)N), dim3(256), 0, s>>>(tok, T, N, NA, pgsum + pg_floats(N, k, Kr));
   } else {
-    if (phase == kBwdPreTokensGiven) {
-      // the dH^pre partials are already in the workspace
-    } else if (!dense_rows) {
-      hipError_t e0 = launch_fill0(part, (size_t)ncb * N * T * sizeof(float), s);
-      if (e0 != hipSuccess) return e0;
-    } else {
+    if (phase != kBwdPreTokensGiven && dense_rows) {   // (else the partials are given, or there are none)
       XHC_TS_DISPATCH(d->state_dtype,
         k_bwd_dhpre<TS><<<dim3((unsigned)(T * ncb)), dim3(256), 0, s>>>(reinterpret_cast<const TS*>(X),
             reinterpret_cast<const TS*>(d_input), T, N, C, part));
     }
-    if (dhpre_act) {
-      k_bwd_dhpre_override<<<dim3((unsigned)((T * k + 255) / 256)), dim3(256), 0, s>>>(dhpre_act, idx, T, N, k, ncb,
-                                                                                      part);
-    }
     {
-      const dim3 gt((unsigned)((T + kPreTokThreads - 1) / kPreTokThreads)), bt(kPreTokThreads);
-      if (k == 4 && 2 * d->sinkhorn_iters <= kSkMaxSteps)
-        k_bwd_pre_token<4><<<gt, bt, 0, s>>>(part, ncb, T, N, d->m, k, Kr, C, saved, colsum, alpha, b_res, idx, p,
-                                            Hpre, Hpost, dHres, dHpost, dp, d->eps, d->sinkhorn_iters,
-                                            d->clamp_delta, tok, pg,
-                                            d->router == XHC_ROUTER_SOFTMAX ? 1 : 0);
-      else
-        k_bwd_pre_token<0><<<gt, bt, 0, s>>>(part, ncb, T, N, d->m, k, Kr, C, saved, colsum, alpha, b_res, idx, p,
-                                            Hpre, Hpost, dHres, dHpost, dp, d->eps, d->sinkhorn_iters,
-                                            d->clamp_delta, tok, pg,
-                                            d->router == XHC_ROUTER_SOFTMAX ? 1 : 0);
+      PreTokArgs ta{};
+      ta.part = dense_rows ? part : nullptr;
+      ta.nchunk = ncb;
+      ta.T = T;
+      ta.N = N;
+      ta.m = d->m;
+      ta.k = k;
+      ta.Kr = Kr;
+      ta.C = C;
+      ta.saved = saved;
+      ta.colsum = colsum;
+      ta.alpha = alpha;
+      ta.b_res = b_res;
+      ta.idx = idx;
+      ta.p = p;
+      ta.Hpre = Hpre;
+      ta.Hpost = Hpost;
+      ta.dHres = dHres;
+      ta.dHpost = dHpost;
+      ta.dp = dp;
+      ta.dhact = dhpre_act;
+      ta.eps = d->eps;
+      ta.iters = d->sinkhorn_iters;
+      ta.delta = d->clamp_delta;
+      ta.tok = tok;
+      ta.pg = pg;
+      ta.softmax = d->router == XHC_ROUTER_SOFTMAX ? 1 : 0;
+      const auto grid = [&](int KP) {
+        const int nt = kPreTokThreads / mix_lanes(KP);
+        return dim3((unsigned)((T + nt - 1) / nt));
+      };
+      if (k <= 2) k_bwd_pre_token<2><<<grid(2), dim3(kPreTokThreads), 0, s>>>(ta);
+      else if (k <= 4) k_bwd_pre_token<4><<<grid(4), dim3(kPreTokThreads), 0, s>>>(ta);
+      else k_bwd_pre_token<8><<<grid(8), dim3(kPreTokThreads), 0, s>>>(ta);
     }
     e = hipGetLastError();
     if (e != hipSuccess || phase == kBwdPreTokens || phase == kBwdPreTokensGiven) return e;

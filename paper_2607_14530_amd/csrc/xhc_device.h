@@ -327,49 +327,83 @@ __device__ __forceinline__ void sinkhorn_clamp(float (&M)[kMaxK * kMaxK], int k,
   }
 }
 
-// The same for a compile-time k (no padded rows or columns); identical
-// arithmetic and order.
-template <int K>
-__device__ __forceinline__ void sinkhorn_clamp_k(float (&M)[K * K], int iters, float delta) {
-#pragma unroll
-  for (int j = 0; j < K; ++j) {
-    float mx = M[j * K];
-#pragma unroll
-    for (int l = 1; l < K; ++l) mx = fmaxf(mx, M[j * K + l]);
-#pragma unroll
-    for (int l = 0; l < K; ++l) M[j * K + l] = __expf(M[j * K + l] - mx);
+// The same with one element per lane: a token's k x k matrix takes the first
+// KP KP lanes (KP = 2, 4 or 8, k <= KP) of an aligned group of mix_lanes(KP),
+// lane e = element (e / KP, e % KP).  A normalisation is then a few DPP adds
+// and one division instead of k sums and k divisions of one thread, whose
+// serial chain (20 iterations, k = 4: 8 us forward, 40 us reversed, at any
+// T) is what the coefficient passes waited for.  Elements past k hold 0 and
+// their lines' normalisers are left out.  Every lane of the group is active.
+__host__ __device__ constexpr int mix_lanes(int KP) { return KP <= 4 ? 16 : KP * KP; }
+// lane (l - r) mod 16 of the 16-lane row, r = 4 or 8
+template <int R>
+__device__ __forceinline__ float dpp_ror_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + R, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float swap16_add(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap32_add(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// sums over a row (l) and over a column (j), the same bits in every lane of it
+// (each exchange adds two values in either order)
+template <int KP>
+__device__ __forceinline__ float mix_row_sum(float v) {
+  v = dpp_add(v, 0);
+  if (KP > 2) v = dpp_add(v, 1);
+  if (KP > 4) v = dpp_add(v, 2);
+  return v;
+}
+template <int KP>
+__device__ __forceinline__ float mix_col_sum(float v) {
+  if constexpr (KP == 2) {
+    return dpp_add(v, 1);
+  } else if constexpr (KP == 4) {
+    return dpp_ror_add<4>(dpp_ror_add<8>(v));
+  } else {
+    return swap32_add(swap16_add(dpp_ror_add<8>(v)));
   }
+}
+template <int KP>
+__device__ __forceinline__ float mix_row_max(float v) {
+  auto mx = [&](int o) { v = fmaxf(v, __int_as_float(o)); };
+  mx(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));
+  if (KP > 2) mx(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));
+  if (KP > 4) mx(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false));
+  return v;
+}
+// sum over the lanes of a token's group, in every lane of it
+template <int KP>
+__device__ __forceinline__ float mix_group_sum(float v) {
+  if constexpr (mix_lanes(KP) == 64) {
+    return wave_sum(v);
+  } else {
+    v = dpp_add(v, 0);
+    v = dpp_add(v, 1);
+    v = dpp_add(v, 2);
+    return dpp_add(v, 3);
+  }
+}
+// exp(L - row maximum), 0 in unused lanes
+template <int KP>
+__device__ __forceinline__ float mix_exp(float L, bool used) {
+  const float mx = mix_row_max<KP>(used ? L : -__builtin_huge_valf());
+  return used ? __expf(L - mx) : 0.f;
+}
+template <int KP>
+__device__ __forceinline__ float sinkhorn_clamp_lanes(float L, bool used, int iters, float delta) {
+  float M = mix_exp<KP>(L, used);
   for (int it = 0; it < iters; ++it) {
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      float s = 0.f;
-#pragma unroll
-      for (int l = 0; l < K; ++l) s += M[j * K + l];
-      const float r = 1.0f / s;
-#pragma unroll
-      for (int l = 0; l < K; ++l) M[j * K + l] *= r;
-    }
-#pragma unroll
-    for (int l = 0; l < K; ++l) {
-      float s = 0.f;
-#pragma unroll
-      for (int j = 0; j < K; ++j) s += M[j * K + l];
-      const float r = 1.0f / s;
-#pragma unroll
-      for (int j = 0; j < K; ++j) M[j * K + l] *= r;
-    }
+    const float rr = 1.0f / mix_row_sum<KP>(M);
+    M = used ? M * rr : 0.f;
+    const float rc = 1.0f / mix_col_sum<KP>(M);
+    M = used ? M * rc : 0.f;
   }
-#pragma unroll
-  for (int j = 0; j < K; ++j) {
-    float s = 0.f;
-#pragma unroll
-    for (int l = 0; l < K; ++l) s += M[j * K + l];
-    if (s > 1.0f + delta) {
-      const float r = 1.0f / s;
-#pragma unroll
-      for (int l = 0; l < K; ++l) M[j * K + l] *= r;
-    }
-  }
+  const float s = mix_row_sum<KP>(M);
+  return s > 1.0f + delta ? M * (1.0f / s) : M;
 }
 
 // Gram-Schmidt of the components e_0 = out, e_1..e_r = conv branches, in the

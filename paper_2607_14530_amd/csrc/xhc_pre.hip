@@ -194,11 +194,13 @@ __global__ __launch_bounds__(128) void k_pre_coef(const float* __restrict__ sums
     for (int l = 0; l < k; ++l) Hres[(t * k + j) * k + l] = M[j * kMaxK + l];
 }
 
-// k = 4: the chunk sums of the active projection and the coefficients in one
-// launch.  A block takes 32 tokens; thread (part h, token u) sums chunk range
-// h of token u (8 ranges), the ranges are added in order through LDS, and one
-// thread per token forms the coefficients.
-constexpr int kCoefTok = 64, kCoefParts = 4;   // tokens per workgroup, member-chunk parts per token
+// k = 2 and 4: the chunk sums of the active projection and the coefficients
+// in one launch.  A workgroup takes 32 tokens (128 contiguous bytes of each
+// output's row of partials); thread (part h, token u) sums chunk range h of
+// token u (8 ranges), the ranges are added in order through LDS, and 16 lanes
+// per token form the coefficients, an element of H^res each (with one thread
+// per token the Sinkhorn iterations were a chain of 8 us at any T).
+constexpr int kCoefTok = 32, kCoefParts = 8;   // tokens per workgroup, chunk ranges per token
 template <int K>
 __global__ __launch_bounds__(kCoefTok * kCoefParts) void k_pre_coef_sum(
     const float* __restrict__ part, int64_t nchunk, int NO, int64_t T, int Kq, int with_res, int64_t kC,
@@ -207,11 +209,14 @@ __global__ __launch_bounds__(kCoefTok * kCoefParts) void k_pre_coef_sum(
     float* __restrict__ Hres, float* __restrict__ saved, int nsave, int save_z_at, int save_stats_at,
     const int* __restrict__ err) {
   constexpr int NA = K * kMaxKr + K * K;   // outputs kept (at most)
+  constexpr int GL = mix_lanes(K), NT = kCoefTok * kCoefParts;
+  static_assert(NA <= 2 * GL && K * kMaxKr <= GL && K * K <= GL, "a lane keeps two outputs at most");
   __shared__ float red[kCoefParts][NA + 1][kCoefTok];
-  const int u = threadIdx.x % kCoefTok, h = threadIdx.x / kCoefTok;
-  const int64_t t = (int64_t)blockIdx.x * kCoefTok + u;
   const int nproj = K * Kq + (with_res ? K * K : 0);
+  const int64_t tb = (int64_t)blockIdx.x * kCoefTok;
   {
+    const int u = threadIdx.x % kCoefTok, h = threadIdx.x / kCoefTok;
+    const int64_t t = tb + u;
     float acc[NA + 1];
 #pragma unroll
     for (int o = 0; o <= NA; ++o) acc[o] = 0.f;
@@ -233,50 +238,39 @@ __global__ __launch_bounds__(kCoefTok * kCoefParts) void k_pre_coef_sum(
     for (int o = 0; o <= NA; ++o) red[h][o][u] = acc[o];
   }
   __syncthreads();
-  if (h != 0 || t >= T) return;
-  float acc[NA + 1];
+  for (int i = threadIdx.x; i < (NA + 1) * kCoefTok; i += NT) {
+    float* r0 = &red[0][0][0] + i;
+    float v = r0[0];
 #pragma unroll
-  for (int o = 0; o <= NA; ++o) {
-    float v = red[0][o][u];
-#pragma unroll
-    for (int q = 1; q < kCoefParts; ++q) v += red[q][o][u];
-    acc[o] = v;
+    for (int q = 1; q < kCoefParts; ++q) v += r0[q * (NA + 1) * kCoefTok];
+    r0[0] = v;
   }
-  if (err && *err != 0) {
-    // the single-pass kernel gave up a wait: its partials are not valid
-    const float nan = __uint_as_float(0x7fc00000u);
-    for (int o = 0; o < K * Kq; ++o) Hpost[t * K * Kq + o] = nan;
-    if (with_res)
-      for (int o = 0; o < K * K; ++o) Hres[t * K * K + o] = nan;
-    return;
-  }
-  const float nu_a = acc[NA] / (float)kC;
-  const float rstd = 1.0f / sqrtf(nu_a + eps);
-  if (saved) {
-    saved[t * nsave + save_stats_at] = nu_a;
+  __syncthreads();
+  // a failed single pass leaves partials that are not valid
+  const bool bad = err && *err != 0;
+  const float nan = __uint_as_float(0x7fc00000u);
+  const float ap = alpha_post[0], ar = with_res ? alpha_res[0] : 0.f;
+  const int e = threadIdx.x % GL;
+  for (int u = threadIdx.x / GL; u < kCoefTok; u += NT / GL) {   // (the same number of turns in every lane)
+    const int64_t t = tb + u;
+    const bool in = t < T;
+    const float nu_a = red[0][NA][u] / (float)kC;
+    const float rstd = 1.0f / sqrtf(nu_a + eps);
+    if (saved && in && !bad) {
+      if (e == 0) saved[t * nsave + save_stats_at] = nu_a;
 #pragma unroll
-    for (int o = 0; o < NA; ++o)
-      if (o < nproj) saved[t * nsave + save_z_at + o] = acc[o] * rstd;
-  }
-  const float ap = alpha_post[0];
-#pragma unroll
-  for (int o = 0; o < K * kMaxKr; ++o)
-    if (o < K * Kq) Hpost[t * K * Kq + o] = 2.0f * sigmoidf(ap * (acc[o] * rstd) + b_post[o]);
-  if (!with_res) return;
-  const float ar = alpha_res[0];
-  float M[K * K];
-#pragma unroll
-  for (int o = 0; o < K * K; ++o) {
+      for (int o = e; o < NA; o += GL)
+        if (o < nproj) saved[t * nsave + save_z_at + o] = red[0][o][u] * rstd;
+    }
+    if (e < K * Kq && in)
+      Hpost[t * K * Kq + e] = bad ? nan : 2.0f * sigmoidf(ap * (red[0][e][u] * rstd) + b_post[e]);
+    if (!with_res) continue;
     // the W_res outputs follow the K Kq W_post outputs
-    float z = 0.f;
-#pragma unroll
-    for (int q = 1; q <= kMaxKr; ++q)
-      if (q == Kq) z = acc[K * q + o];
-    M[o] = ar * (z * rstd) + b_res[o];
+    const bool used = e < K * K;
+    const int er = used ? e : 0;
+    const float M = sinkhorn_clamp_lanes<K>(ar * (red[0][K * Kq + er][u] * rstd) + b_res[er], used, iters, delta);
+    if (used && in) Hres[t * K * K + e] = bad ? nan : M;
   }
-  sinkhorn_clamp_k<K>(M, iters, delta);
-#pragma unroll
-  for (int o = 0; o < K * K; ++o) Hres[t * K * K + o] = M[o];
 }
 
 static hipError_t sum_chunks(const float* part, int64_t nchunk, int NO, int64_t T, float* sums, hipStream_t s) {
@@ -311,10 +305,15 @@ hipError_t launch_pre_coef(const float* part, int64_t nchunk, int64_t nout, int6
                            int save_stats_at, hipStream_t s, const int* err) {
   if (T == 0) return hipSuccess;
   const int NO = (int)out_blocks(nout) * 16 + 2;
-  if (k == 4 && Kq <= kMaxKr) {
-    k_pre_coef_sum<4><<<dim3((unsigned)((T + kCoefTok - 1) / kCoefTok)), dim3(kCoefTok * kCoefParts), 0, s>>>(
-        part, nchunk, NO, T, Kq, with_res, (int64_t)k * C, alpha_post, alpha_res, b_post, b_res, eps, iters, delta,
-        Hpost, Hres, saved, nsave, save_z_at, save_stats_at, err);
+  if ((k == 2 || k == 4) && Kq <= kMaxKr) {
+    const dim3 g((unsigned)((T + kCoefTok - 1) / kCoefTok)), b(kCoefTok * kCoefParts);
+#define XHC_COEF(KV)                                                                                              \
+  k_pre_coef_sum<KV><<<g, b, 0, s>>>(part, nchunk, NO, T, Kq, with_res, (int64_t)k * C, alpha_post, alpha_res,      \
+                                     b_post, b_res, eps, iters, delta, Hpost, Hres, saved, nsave, save_z_at,       \
+                                     save_stats_at, err)
+    if (k == 4) XHC_COEF(4);
+    else XHC_COEF(2);
+#undef XHC_COEF
     return hipGetLastError();
   }
   hipError_t e = sum_chunks(part, nchunk, NO, T, sums, s);
