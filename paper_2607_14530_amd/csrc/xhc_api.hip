@@ -172,8 +172,8 @@ xhc_dims dims_rows32(const xhc_dims* d, int Kq) {
 }
 
 struct FlashPostBwdWs {
-  size_t post, pre, part, sums, idx_id, hres_id, hsel, da_out, dhpost, dhres, dp,
-      saved, hpost_re, hres_re, wres0, bres0, alpha2, dwr, dwpre, dbpre, dwres, dbres, dalpha2, total;
+  size_t post, pre, part, sums, idx_id, hres_id, hsel, da_out, dhpost, dhres,
+      saved, hpost_re, hres_re, wres0, total;
 };
 
 FlashPostBwdWs flash_post_bwd_ws(const xhc_dims* d, int Q, int q) {
@@ -194,19 +194,10 @@ FlashPostBwdWs flash_post_bwd_ws(const xhc_dims* d, int Q, int q) {
   w.da_out = c.take((size_t)T * kC * f);
   w.dhpost = c.take((size_t)T * k * Kq * f);
   w.dhres = c.take((size_t)T * k * k * f);
-  w.dp = c.take((size_t)T * k * f);
   w.saved = c.take((size_t)T * saved_floats(k, k, Kq) * f);
   w.hpost_re = c.take((size_t)T * k * Kq * f);
   w.hres_re = c.take((size_t)T * k * k * f);
-  w.wres0 = c.take((size_t)kC * k * k * f);
-  w.bres0 = c.take((size_t)k * k * f);
-  w.alpha2 = c.take(3 * f);
-  w.dwr = c.take((size_t)kC * k * f);
-  w.dwpre = c.take((size_t)kC * k * f);
-  w.dbpre = c.take((size_t)k * f);
-  w.dwres = c.take((size_t)kC * k * k * f);
-  w.dbres = c.take((size_t)k * k * f);
-  w.dalpha2 = c.take(3 * f);
+  w.wres0 = c.take(d->state_dtype == XHC_BF16 || q == Q ? 0 : (size_t)kC * k * k * f);
   w.total = c.total;
   return w;
 }
@@ -215,7 +206,7 @@ struct FlashPreBwdWs {
   size_t pre_slice;   // one pre-map reverse's workspace (Q of them when the row passes are fused)
   bool fused;
   size_t multi;       // the fused row pass's per-token inputs
-  size_t pre, part, sums, saved, idx_s, p_s, hpre_s, hmask, alpha_e, dwr, dwres, dwpost, dalpha, dbres, dbpost, total;
+  size_t pre, part, sums, saved, idx_s, p_s, hpre_s, hmask, total;
 };
 
 FlashPreBwdWs flash_pre_bwd_ws(const xhc_dims* d, int Q) {
@@ -231,18 +222,11 @@ FlashPreBwdWs flash_pre_bwd_ws(const xhc_dims* d, int Q) {
   w.multi = c.take(w.fused ? bwd_rows_multi_ws_bytes(&e, Q) : 0);
   w.part = c.take(part_bytes(d, false, NC, nf));
   w.sums = c.take(sums_bytes(nf, T));
-  w.saved = c.take((size_t)T * saved_floats(N, k, 1) * f);
+  w.saved = c.take((size_t)(w.fused ? Q : 1) * T * saved_floats(N, k, 1) * f);   // used where none is given
   w.idx_s = c.take((size_t)T * k * sizeof(int32_t));
   w.p_s = c.take((size_t)T * k * f);
   w.hpre_s = c.take((size_t)Q * T * N * f);
   w.hmask = c.take((size_t)Q * T * N * f);   // [Q][T, N]: the masked dense-read weights of pre-map q >= 1
-  w.alpha_e = c.take(3 * f);
-  w.dwr = c.take((size_t)NC * N * f);
-  w.dwres = c.take((size_t)kC * k * k * f);
-  w.dwpost = c.take((size_t)kC * k * f);
-  w.dalpha = c.take(3 * f);
-  w.dbres = c.take((size_t)k * k * f);
-  w.dbpost = c.take((size_t)k * f);
   w.total = c.total;
   return w;
 }
@@ -684,9 +668,39 @@ xhc_status xhc_pre_bwd(const xhc_dims* d, const void* X, const void* packed_full
   const float* colsum = reinterpret_cast<const float*>(reinterpret_cast<const char*>(packed_full) +
                                                        packed_frag_bytes(NC_of(d), 2 * d->N));
   hipError_t e = hipSuccess;
-  XHC_STEP("pre_bwd", launch_bwd_pre(d, X, colsum, W_r, W_pre, W_res, W_post, alpha, b_res, saved, idx, p, Hpre,
-                                     Hpost, d_input, dHres, dHpost, dp, dX, dW_r, dW_pre, dW_res, dW_post, dalpha,
-                                     db_pre, db_res, db_post, reinterpret_cast<char*>(workspace), s));
+  BwdPre b{};
+  b.X = X;
+  b.colsum = colsum;
+  b.W_r = W_r;
+  b.W_pre = W_pre;
+  b.W_res = W_res;
+  b.W_post = W_post;
+  b.al_pre = alpha;
+  b.al_res = alpha + 1;
+  b.al_post = alpha + 2;
+  b.b_res = b_res;
+  b.saved = saved;
+  b.idx = idx;
+  b.p = p;
+  b.Hpre = Hpre;
+  b.Hpost = Hpost;
+  b.d_input = d_input;
+  b.dHres = dHres;
+  b.dHpost = dHpost;
+  b.dp = dp;
+  b.dX = dX;
+  b.dW_r = dW_r;
+  b.dW_pre = dW_pre;
+  b.dW_res = dW_res;
+  b.dW_post = dW_post;
+  b.dal_pre = dalpha;
+  b.dal_res = dalpha + 1;
+  b.dal_post = dalpha + 2;
+  b.db_pre = db_pre;
+  b.db_res = db_res;
+  b.db_post = db_post;
+  b.ws = reinterpret_cast<char*>(workspace);
+  XHC_STEP("pre_bwd", launch_bwd_pre(d, b, s));
   return hip_status(e);
 }
 
@@ -737,11 +751,11 @@ xhc_status xhc_flash_post_bwd(const xhc_dims* d, int32_t Q, int32_t q, const voi
   int32_t* idx_id = reinterpret_cast<int32_t*>(ws + w.idx_id);
   float* hres_use = last ? const_cast<float*>(Hres) : F32(w.hres_id);
   hipError_t e = hipSuccess;
-  // zero the saved logits the recompute leaves empty, and for q < Q the weights
-  // of the residual mapping that sublayer does not have
-  if (!saved_act)
-    XHC_STEP("fbwd_zero", launch_fill0(ws + w.saved, (size_t)T * saved_floats(k, k, Kq) * sizeof(float), s));
-  if (!last) XHC_STEP("fbwd_zero", launch_fill0(ws + w.wres0, w.alpha2 - w.wres0, s));   // wres0, bres0
+  // an fp32 state's row pass takes weights of a residual mapping: zero ones for
+  // q < Q, where the sublayer has none
+  const bool bf = d->state_dtype == XHC_BF16;
+  const bool zero_res = !last && !bf;
+  if (zero_res) XHC_STEP("fbwd_zero", launch_fill0(ws + w.wres0, (size_t)kC * k * k * sizeof(float), s));
   // slot map, identity mixing, pre-map weights of the active streams, <d input_q, a_j>
   XHC_STEP("fbwd_token", launch_fbwd_token(d->state_dtype, T, d->N, (int)k, (int)C, idx, Hpre_q, d_input, Xact,
                                            idx_id, last ? nullptr : F32(w.hres_id), F32(w.hsel), dHpre_act, s));
@@ -754,9 +768,8 @@ xhc_status xhc_flash_post_bwd(const xhc_dims* d, int32_t Q, int32_t q, const voi
   float* const dA_out = fold_read ? dA : F32(w.da_out);
   const xhc_dims rs = dims_rows(d, Kq);
   XHC_STEP("fbwd_post", launch_bwd_post(&rs, dA, nullptr, Xact, F, conv_w, idx_id, p, hres_use, Hpost, dA_out,
-                                        dF, F32(w.dhres), F32(w.dhpost), F32(w.dp), dconv_w, ws + w.post, s,
-                                        /*grad_f32=*/true));
-  XHC_STEP("fbwd_dp", launch_fbwd_add(dp, F32(w.dp), T * k, s));
+                                        dF, F32(w.dhres), F32(w.dhpost), dp, dconv_w, ws + w.post, s,
+                                        /*grad_f32=*/true, /*add_dp=*/true));
   // the mapping logits of sublayer q: saved by the forward, or recomputed
   // from a^(q-1) (same kernels and operands as the forward)
   const int64_t na = act_outs(d, Kq, last);
@@ -771,23 +784,34 @@ xhc_status xhc_flash_post_bwd(const xhc_dims* d, int32_t Q, int32_t q, const voi
                                           F32(w.hpost_re), last ? F32(w.hres_re) : nullptr, F32(w.sums), F32(w.saved),
                                           nsave, 2 * (int)k, nsave - 2, s));
   }
-  XHC_STEP("fbwd_alpha", launch_fbwd_alpha(nullptr, alpha_res, alpha_post, F32(w.alpha2), s));
-  // mapping reverse through a^(q-1) (its dense-row terms are all zero here:
-  // no router or pre-map weights)
-  // (the fp32 view's own row pass reads Xact only for an fp32 state; a bf16
+  // mapping reverse through a^(q-1) (that view has no router and no pre-map;
+  // the fp32 view's own row pass reads Xact only for an fp32 state, a bf16
   // state goes through the MFMA pass on Xact as saved)
-  XHC_STEP("fbwd_pre", launch_bwd_pre(&r, Xact, nullptr, nullptr, nullptr,
-                                      last ? W_res : F32(w.wres0), W_post, F32(w.alpha2),
-                                      last ? b_res : F32(w.bres0), rec, idx_id, p, F32(w.hsel), Hpost,
-                                      nullptr, last ? F32(w.dhres) : nullptr, F32(w.dhpost), F32(w.dp), dA_out,
-                                      F32(w.dwr), F32(w.dwpre), last ? dW_res : F32(w.dwres), dW_post,
-                                      F32(w.dalpha2), F32(w.dbpre), last ? db_res : F32(w.dbres), db_post,
-                                      ws + w.pre, s, nullptr, nullptr, /*dense_rows=*/false,
-                                      d->state_dtype == XHC_BF16 ? Xact : nullptr, /*act_rows=*/true, kBwdPreAll,
-                                      fold_read && reads ? d_input : nullptr));
-  XHC_STEP("fbwd_copy", hipMemcpyAsync(dalpha_post, F32(w.dalpha2) + 2, sizeof(float), hipMemcpyDeviceToDevice, s));
-  if (last)
-    XHC_STEP("fbwd_copy", hipMemcpyAsync(dalpha_res, F32(w.dalpha2) + 1, sizeof(float), hipMemcpyDeviceToDevice, s));
+  BwdPre bp{};
+  bp.X = Xact;
+  bp.W_res = last ? W_res : (zero_res ? F32(w.wres0) : nullptr);
+  bp.W_post = W_post;
+  bp.al_res = alpha_res;
+  bp.al_post = alpha_post;
+  bp.b_res = b_res;
+  bp.saved = rec;
+  bp.idx = idx_id;
+  bp.Hpre = F32(w.hsel);
+  bp.Hpost = Hpost;
+  bp.dHres = last ? F32(w.dhres) : nullptr;
+  bp.dHpost = F32(w.dhpost);
+  bp.dX = dA_out;
+  bp.dW_res = dW_res;
+  bp.dW_post = dW_post;
+  bp.dal_res = dalpha_res;
+  bp.dal_post = dalpha_post;
+  bp.db_res = db_res;
+  bp.db_post = db_post;
+  bp.ws = ws + w.pre;
+  bp.dense_rows = false;
+  bp.X_bf16 = bf ? Xact : nullptr;
+  bp.act_din = fold_read && reads ? d_input : nullptr;
+  XHC_STEP("fbwd_pre", launch_bwd_pre(&r, bp, s));
   // da = (reverse so far) + H^pre,q_{I_j} d input_q (the active part of
   // input_q's read): added by the active-row pass for a bf16 state, here
   // otherwise
@@ -829,7 +853,6 @@ xhc_status xhc_flash_pre_bwd(const xhc_dims* d, int32_t Q, const void* X, const 
   const float* colsum = reinterpret_cast<const float*>(reinterpret_cast<const char*>(packed_full) +
                                                        packed_frag_bytes(NC, nf));
   hipError_t e = hipSuccess;
-  if (!saved) XHC_STEP("fpbwd_zero", launch_fill0(ws + w.saved, (size_t)T * nsave * sizeof(float), s));
   // the group-entry logits and statistics: saved by the forward, or
   // recomputed as the forward made them
   if (!saved)
@@ -848,45 +871,51 @@ xhc_status xhc_flash_pre_bwd(const xhc_dims* d, int32_t Q, const void* X, const 
   // state (token records first, then the fused rows, then the reductions).
   const float* hrd[4] = {nullptr, nullptr, nullptr, nullptr};
   char* wsq[4] = {nullptr, nullptr, nullptr, nullptr};
-  auto pass = [&](int q, int phase) -> hipError_t {
-    char* wq = ws + w.pre + (w.fused ? (size_t)q * w.pre_slice : 0);
-    float* hm = F32(w.hmask) + (int64_t)q * T * N;
-    const float* rec = saved ? saved + (int64_t)q * T * nsave : F32(w.saved);   // pre-map q's records
-    if (phase != kBwdPreReduce) {
-      hipError_t e1 = hipSuccess;
-      if (!saved)
-        e1 = launch_pre_route(F32(w.part), proj_chunks(d->state_dtype, false, NC, (int)C, nf, T), nf, T,
-                              (int)N, d->m, (int)k, Q, C, colsum, alpha_pre, 1, b_pre, d->eps,
-                              reinterpret_cast<int32_t*>(ws + w.idx_s), F32(w.p_s), F32(w.hpre_s),
-                              F32(w.sums), F32(w.saved), nsave, nsave - 4, d->router, s, q);
-      if (e1 == hipSuccess) e1 = launch_fbwd_alpha(alpha_pre + q, nullptr, nullptr, F32(w.alpha_e), s);
-      if (e1 == hipSuccess && q >= 1) e1 = launch_fbwd_mask(T, (int)N, (int)k, idx, Hpre + (int64_t)q * T * N, hm, s);
-      if (e1 != hipSuccess) return e1;
-    }
-    hrd[q] = q >= 1 ? hm : Hpre;
-    wsq[q] = wq;
-    return launch_bwd_pre(&en, X, colsum, W_r, W_pre + (int64_t)q * NC * N, nullptr, nullptr,
-                          F32(w.alpha_e), nullptr, rec, idx, p, Hpre + (int64_t)q * T * N,
-                          nullptr, reinterpret_cast<const char*>(d_input) + (size_t)q * T * C * es,
-                          nullptr, nullptr, q == 0 ? dp : nullptr, dX, q == 0 ? dW_r : F32(w.dwr),
-                          dW_pre + (int64_t)q * NC * N, F32(w.dwres), F32(w.dwpost), F32(w.dalpha),
-                          db_pre + (int64_t)q * N, F32(w.dbres), F32(w.dbpost), wq, s,
-                          q >= 1 ? dHpre_act + (int64_t)(q - 1) * T * k : nullptr, q >= 1 ? hm : nullptr,
-                          /*dense_rows=*/true, /*X_bf16=*/nullptr, /*act_rows=*/false, phase);
+  BwdPre bp[4];
+  for (int q = 0; q < Q; ++q) {
+    BwdPre& b = bp[q];
+    b = BwdPre{};
+    wsq[q] = ws + w.pre + (w.fused ? (size_t)q * w.pre_slice : 0);
+    b.X = X;
+    b.colsum = colsum;
+    b.W_r = W_r;
+    b.W_pre = W_pre + (int64_t)q * NC * N;
+    b.al_pre = alpha_pre + q;
+    b.saved = saved ? saved + (int64_t)q * T * nsave : F32(w.saved) + (w.fused ? (int64_t)q * T * nsave : 0);
+    b.idx = idx;
+    b.p = p;
+    b.Hpre = Hpre + (int64_t)q * T * N;
+    b.d_input = reinterpret_cast<const char*>(d_input) + (size_t)q * T * C * es;
+    b.dp = q == 0 ? dp : nullptr;
+    b.dX = dX;
+    b.dW_r = q == 0 ? dW_r : nullptr;
+    b.dW_pre = dW_pre + (int64_t)q * NC * N;
+    b.dal_pre = dalpha_pre + q;
+    b.db_pre = db_pre + (int64_t)q * N;
+    b.ws = wsq[q];
+    b.dhpre_act = q >= 1 ? dHpre_act + (int64_t)(q - 1) * T * k : nullptr;
+    b.hmask = q >= 1 ? F32(w.hmask) + (int64_t)q * T * N : nullptr;
+    b.act_rows = false;
+    b.own_rows = !w.fused;
+    hrd[q] = q >= 1 ? b.hmask : b.Hpre;
+  }
+  // the logits of pre-map q, where the forward has not saved them
+  auto recompute = [&](int q) -> hipError_t {
+    return launch_pre_route(F32(w.part), proj_chunks(d->state_dtype, false, NC, (int)C, nf, T), nf, T,
+                            (int)N, d->m, (int)k, Q, C, colsum, alpha_pre, 1, b_pre, d->eps,
+                            reinterpret_cast<int32_t*>(ws + w.idx_s), F32(w.p_s), F32(w.hpre_s), F32(w.sums),
+                            const_cast<float*>(bp[q].saved), nsave, nsave - 4, d->router, s, q);
   };
   if (w.fused) {
-    for (int q = 0; q < Q; ++q) wsq[q] = ws + w.pre + (size_t)q * w.pre_slice;
+    for (int q = 0; q < Q && !saved && e == hipSuccess; ++q) XHC_STEP("fpbwd_route", recompute(q));
     XHC_STEP("fpbwd_dhpre", launch_bwd_dhpre_multi(&en, Q, X, d_input, wsq, s));
-    for (int q = 0; q < Q && e == hipSuccess; ++q) XHC_STEP("fpbwd_tokens", pass(q, kBwdPreTokensGiven));
-    XHC_STEP("fpbwd_rows", launch_bwd_rows_multi(&en, Q, X, dX, W_r, W_pre, d_input, hrd, wsq, F32(w.multi), s));
-    for (int q = 0; q < Q && e == hipSuccess; ++q) {
-      XHC_STEP("fpbwd_reduce", pass(q, kBwdPreReduce));
-      XHC_STEP("fpbwd_copy", hipMemcpyAsync(dalpha_pre + q, F32(w.dalpha), sizeof(float), hipMemcpyDeviceToDevice, s));
-    }
+    XHC_STEP("fpbwd_tokens", launch_bwd_pre_tokens(&en, bp, Q, s));
+    XHC_STEP("fpbwd_rows", launch_bwd_rows_multi(&en, Q, X, dX, W_r, W_pre, d_input, hrd, wsq, ws + w.multi, s));
+    XHC_STEP("fpbwd_reduce", launch_bwd_pre_reduce(&en, bp, Q, s));
   } else {
     for (int q = 0; q < Q && e == hipSuccess; ++q) {
-      XHC_STEP("fpbwd_pre", pass(q, kBwdPreAll));
-      XHC_STEP("fpbwd_copy", hipMemcpyAsync(dalpha_pre + q, F32(w.dalpha), sizeof(float), hipMemcpyDeviceToDevice, s));
+      if (!saved) XHC_STEP("fpbwd_route", recompute(q));
+      XHC_STEP("fpbwd_pre", launch_bwd_pre(&en, bp[q], s));
     }
   }
   return hip_status(e);

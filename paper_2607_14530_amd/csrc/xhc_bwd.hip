@@ -395,7 +395,8 @@ __global__ __launch_bounds__(128) void k_bwd_post_token(const float* __restrict_
                                                         int64_t is, int64_t ts, int64_t T, int k, int gram_schmidt,
                                                         const float* __restrict__ p, const float* __restrict__ Hpost,
                                                         float* __restrict__ dHres, float* __restrict__ dHpost,
-                                                        float* __restrict__ dp, float* __restrict__ coef) {
+                                                        float* __restrict__ dp, int add_dp,
+                                                        float* __restrict__ coef) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= T) return;
   using PD = PostDots<KR, KM>;
@@ -456,7 +457,7 @@ __global__ __launch_bounds__(128) void k_bwd_post_token(const float* __restrict_
       dpj += h * yv;
       for (int b = 0; b < KR; ++b) P[r][b] += pj * h * D2[j][b];
     }
-    dp[t * k + j] = (float)dpj;
+    dp[t * k + j] = add_dp ? dp[t * k + j] + (float)dpj : (float)dpj;
   }
   double dG[kMaxKr][kMaxKr];
   for (int a = 0; a < kMaxKr; ++a)
@@ -1011,17 +1012,42 @@ __global__ __launch_bounds__(256) void k_colsum_rows(const float* __restrict__ i
   out[col] = s;
 }
 
-// out[col] = sum over T of in[t][col], for few columns: one block per column,
-// threads stride the tokens, tree reduction in a fixed order.
-__global__ __launch_bounds__(256) void k_sum_tokens(const float* __restrict__ in, int64_t T, int ncols,
-                                                    float* __restrict__ out) {
-  __shared__ float red[256];
-  const int col = blockIdx.x;
+// Sums over the tokens of the per-token parameter gradients (pg [col][T]): one
+// workgroup per column and pre-map reverse, eight loads a thread in flight,
+// a tree in a fixed order, written where the caller wants them (null: left
+// out).  mu r_ln dz_r goes to corr, the correction of dW_r.
+constexpr int kMultiMaxQ = 4;   // pre-map reverses taken at once
+struct TokenSums {
+  const float* pg;
+  float *dal_pre, *dal_res, *dal_post, *db_pre, *db_res, *db_post, *corr;
+};
+struct TokenSumsMulti {
+  TokenSums a[kMultiMaxQ];
+};
+constexpr int kSumThreads = 1024;
+__global__ __launch_bounds__(kSumThreads) void k_sum_tokens(TokenSumsMulti ma, int64_t T, int N, int k, int Kr) {
+  const TokenSums& a = ma.a[blockIdx.y];
+  __shared__ float red[kSumThreads];
+  int col = blockIdx.x;
+  float* out = nullptr;
+  if (col < 3) out = col == 0 ? a.dal_pre : (col == 1 ? a.dal_res : a.dal_post), col = 0;
+  else if ((col -= 3) < N) out = a.db_pre;
+  else if ((col -= N) < k * k) out = a.db_res;
+  else if ((col -= k * k) < k * Kr) out = a.db_post;
+  else col -= k * Kr, out = a.corr;
+  if (!out) return;
+  const float* in = a.pg + (int64_t)blockIdx.x * T;
   float s = 0.f;
-  for (int64_t t = threadIdx.x; t < T; t += 256) s += in[t * ncols + col];
+  for (int64_t t = threadIdx.x; t < T; t += 8 * kSumThreads) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = t + u * kSumThreads < T ? in[t + u * kSumThreads] : 0.f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
   red[threadIdx.x] = s;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
+  for (int w = kSumThreads / 2; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
@@ -1111,30 +1137,61 @@ __host__ __device__ inline int pg_floats(int N, int k, int Kr) { return 3 + N + 
 struct PreTokArgs {
   const float* part;     // <d input, x_i> partials [nchunk][N][T], or null: no pre-map term
   int64_t nchunk;
-  int64_t T;
+  int64_t T, Tp;         // tokens; the same rounded up to whole blocks of the packed dz'
   int N, m, k, Kr, C;
-  const float *saved, *colsum, *alpha, *b_res;
+  const float *saved, *colsum, *b_res;
+  const float *al_pre, *al_res, *al_post;   // null: 0
   const int32_t* idx;
   const float *p, *Hpre, *Hpost;
   const float* dHres;    // null: no residual mapping (its gradients are zero)
   const float* dHpost;   // null: no active-row outputs at all
   const float* dp;       // null: no router gradient
   const float* dhact;    // [T, k] or null: replaces <d input, x_i> of the active streams
+  float* hmask;          // [T, N] or null: receives Hpre with the active streams' weights zero
   float eps;
   int iters;
   float delta;
-  float *tok, *pg;
+  float* tok;
+  float* pg;             // [pg_floats + N][T]: gradients of the parameters, then mu r_ln dz_r
+  uint16_t* dzf;         // packed dz' of the full rows (nof outputs) or null, and its scalars
+  float* srec;
+  int nof;
+  uint16_t* dza;         // packed dz' of the active rows (32 outputs) or null, and its scalars or null
+  float* sreca;
   int softmax;
 };
+struct PreTokMulti {
+  PreTokArgs a[kMultiMaxQ];   // one pre-map reverse per blockIdx.y
+};
+
+// dz' of the MFMA row passes as bf16 pairs hi + lo (hi the round-to-nearest-
+// even bf16 of the value, lo that of the rest; the packed hardware
+// conversion), NO outputs a token (zero past the used ones and past T):
+//   rows[t][0 .. NO)   hi,  rows[t][NO .. 2 NO)  lo
+//   tr[b][o][u]        the same values of token 32 b + u, row o of 2 NO
+// tr follows the Tp token rows.
+constexpr int kDzBlock = 32;   // tokens per transposed block
+__device__ __forceinline__ void dz_store(uint16_t* __restrict__ rows, int64_t Tp, int NO, int64_t t, int o, float v) {
+  const uint32_t hb = pack2bf(v, 0.f) & 0xFFFFu;
+  const uint32_t lb = pack2bf(v - __uint_as_float(hb << 16), 0.f) & 0xFFFFu;
+  rows[t * 2 * NO + o] = (uint16_t)hb;
+  rows[t * 2 * NO + NO + o] = (uint16_t)lb;
+  uint16_t* blk = rows + Tp * 2 * NO + (t / kDzBlock) * 2 * NO * kDzBlock;
+  blk[o * kDzBlock + t % kDzBlock] = (uint16_t)hb;
+  blk[(NO + o) * kDzBlock + t % kDzBlock] = (uint16_t)lb;
+}
 
 // Per-token reverses, mix_lanes(KP) lanes a token (k <= KP): streams, outputs
-// and the elements of the mixing matrix are spread over the lanes.  Bound by
+// and the elements of the mixing matrix are spread over the lanes.  The scaled
+// logit gradients go out in the layouts the row passes read as well (full
+// rows: r_ln dz_r | r dz_pre; active rows: r_a dz_act).  Bound by
 // the chain of the Sinkhorn reverse, not by its data: with one thread per
 // token it took 40 us at any T at k = 4 and 790 us at k = 2, where every step
 // back recomputed the iterate (T = 13608).
 constexpr int kPreTokThreads = 256;
 template <int KP>
-__global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(PreTokArgs a) {
+__global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(PreTokMulti ma) {
+  const PreTokArgs& a = ma.a[blockIdx.y];
   constexpr int GL = mix_lanes(KP), NT = kPreTokThreads / GL;   // lanes a token, tokens a workgroup
   __shared__ float sdh[kMaxN][NT];
   __shared__ float2 norm[kSkSeg * KP * NT];
@@ -1142,7 +1199,9 @@ __global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(PreTokArgs a) 
   const int64_t T = a.T, tb = (int64_t)blockIdx.x * NT;
   const int u = threadIdx.x / GL, e = threadIdx.x % GL;
   const bool in = tb + u < T;
-  const int64_t t = in ? tb + u : T - 1;   // (a token past the end works on the last one and writes nothing)
+  // a token past the end works on the last one and writes only zeros of the packed dz'
+  const int64_t t = in ? tb + u : T - 1, tz = tb + u;
+  const bool inz = tz < a.Tp;
   // the inner products of the workgroup's tokens: chunk sums in the order
   // chunk 0, 1, ..., then the given ones of the active streams
   if (a.part) {
@@ -1160,12 +1219,13 @@ __global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(PreTokArgs a) 
   const int NA = k * Kr + k * k, ns = saved_floats(N, k, Kr);
   const float* sv = a.saved + t * ns;
   float* tk = a.tok + t * tok_floats(N, NA);
-  float* g = a.pg + t * pg_floats(N, k, Kr);
+  float* g = a.pg + t;   // value i at g[i T]
   const float mu = sv[ns - 4], nu = sv[ns - 3], nu_a = sv[ns - 2];
   const float NC = (float)N * (float)a.C, kC = (float)k * (float)a.C;
   const float r = 1.0f / sqrtf(nu + a.eps), r_ln = 1.0f / sqrtf(ln_variance(mu, nu) + a.eps);
   const float r_a = 1.0f / sqrtf(nu_a + a.eps);
-  const float a_pre = a.alpha[0], a_res = a.alpha[1], a_post = a.alpha[2];
+  const float a_pre = a.al_pre ? *a.al_pre : 0.f, a_res = a.al_res ? *a.al_res : 0.f;
+  const float a_post = a.al_post ? *a.al_post : 0.f;
   // pre-map: H = sigma(a z + b)
   float da_pre = 0.f;
   for (int i = e; i < N; i += GL) {
@@ -1177,8 +1237,9 @@ __global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(PreTokArgs a) 
     }
     if (in) {
       tk[N + i] = a_pre * ds;
-      g[3 + i] = ds;
+      g[(3 + i) * T] = ds;
     }
+    if (a.dzf && inz) dz_store(a.dzf, a.Tp, a.nof, tz, N + i, in ? r * (a_pre * ds) : 0.f);
   }
   da_pre = mix_group_sum<KP>(da_pre);
   const float beta_pre = r * r * (a_pre * da_pre) / NC;
@@ -1197,6 +1258,11 @@ __global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(PreTokArgs a) 
   }
   for (int i = e; i < N; i += GL) {
     float dz = 0.f;
+    if (a.hmask && in) {
+      bool act = false;
+      for (int j = 0; j < k; ++j) act = act || a.idx[t * k + j] == i;
+      a.hmask[t * N + i] = act ? 0.f : a.Hpre[t * N + i];
+    }
     if (route) {
       if (a.softmax) dz = -(__expf(sv[i] - mx) / den) * dot;
       for (int j = m; j < k; ++j)
@@ -1207,7 +1273,11 @@ __global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(PreTokArgs a) 
       m1 += a.colsum[i] * dz;
       m2 += sv[i] * dz;
     }
-    if (in) tk[i] = dz;
+    if (in) {
+      tk[i] = dz;
+      g[(3 + N + k * k + k * Kr + i) * T] = mu * r_ln * dz;
+    }
+    if (a.dzf && inz) dz_store(a.dzf, a.Tp, a.nof, tz, i, in ? r_ln * dz : 0.f);
   }
   m1 = mix_group_sum<KP>(m1) / NC;
   m2 = mix_group_sum<KP>(m2) / NC;
@@ -1220,8 +1290,9 @@ __global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(PreTokArgs a) 
       da_post += du * sv[2 * N + o];
       if (in) {
         tk[2 * N + o] = a_post * du;
-        g[3 + N + k * k + o] = du;
+        g[(3 + N + k * k + o) * T] = du;
       }
+      if (a.dza && inz) dz_store(a.dza, a.Tp, 32, tz, o, in ? r_a * (a_post * du) : 0.f);
     }
     da_post = mix_group_sum<KP>(da_post);
     // residual map: H = clamp(SK(exp(a z + b)))
@@ -1237,13 +1308,28 @@ __global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(PreTokArgs a) 
     }
     if (used && in) {
       tk[2 * N + k * Kr + o] = a_res * d;
-      g[3 + N + o] = d;
+      g[(3 + N + o) * T] = d;
+    }
+    if (a.dza && inz) {
+      if (used) dz_store(a.dza, a.Tp, 32, tz, k * Kr + o, in ? r_a * (a_res * d) : 0.f);
+      for (int z = NA + e; z < 32; z += GL) dz_store(a.dza, a.Tp, 32, tz, z, 0.f);
     }
   }
-  if (e != 0 || !in) return;
+  if (a.dzf && inz)
+    for (int z = 2 * N + e; z < a.nof; z += GL) dz_store(a.dzf, a.Tp, a.nof, tz, z, 0.f);
+  if (e != 0 || !inz) return;
+  const float beta_a = r_a * r_a * (a_post * da_post + a_res * da_res) / kC;
+  // the scalars as the ring passes read them (r_ln, mu, m1, m2, beta)
+  auto scalars = [&](float* sr, float s0, float s1, float s2, float s3, float s4) {
+    reinterpret_cast<float4*>(sr + tz * 8)[0] = in ? make_float4(s0, s1, s2, s3) : make_float4(0.f, 0.f, 0.f, 0.f);
+    reinterpret_cast<float4*>(sr + tz * 8)[1] = make_float4(in ? s4 : 0.f, 0.f, 0.f, 0.f);
+  };
+  if (a.srec) scalars(a.srec, r_ln, mu, m1, m2, beta_pre);
+  if (a.sreca) scalars(a.sreca, 0.f, 0.f, 0.f, 0.f, beta_a);
+  if (!in) return;
   g[0] = da_pre;
-  g[1] = da_res;
-  g[2] = da_post;
+  g[T] = da_res;
+  g[2 * T] = da_post;
   float* sc = tk + 2 * N + NA;
   sc[0] = r;
   sc[1] = r_ln;
@@ -1252,7 +1338,7 @@ __global__ __launch_bounds__(kPreTokThreads) void k_bwd_pre_token(PreTokArgs a) 
   sc[4] = m1;
   sc[5] = m2;
   sc[6] = r_a;
-  sc[7] = r_a * r_a * (a_post * da_post + a_res * da_res) / kC;
+  sc[7] = beta_a;
 }
 
 // Weight-stationary pass over rows K = i*C + c of [W_r | W_pre] (one row per
@@ -1452,54 +1538,14 @@ __global__ __launch_bounds__(256) void k_bwd_act_rows(const TS* __restrict__ X, 
 //   dW[K, o] += sum_t x[t, K] dz'[t, o]                 MFMA D[16 o x 16 K], contraction over 32 tokens
 // with dz' the per-token scaled logit gradients (full rows: r_ln dz_r | r
 // dz_pre; active rows: r_a dz_act), entered as a bf16 pair hi + lo (2^-16
-// relative).  The pairs are formed once per token by k_dz_pack, in the two
+// relative).  The pairs are formed once per token by k_bwd_pre_token, in the two
 // layouts the MFMA operands read (token rows for dX, 32-token transposes for
 // dW).  The full rows take the ring pass of xhc_bwd_rows.hip (whose dW_r
 // misses the token sum of mu dz'_r, which the reduction removes); the active
 // rows of a routed state, gathered through idx, take k_bwd_act_rows_mfma.
 constexpr int kMfRows = 64;    // weight rows per workgroup
-constexpr int kDzBlock = 32;   // tokens per transposed block of the packed dz' (= kMfStep)
 constexpr int kMfStep = 32;    // tokens per step
 constexpr int kMfXPitch = kMfRows + 8;   // bf16 per staged token row (pad: fewer LDS bank conflicts)
-
-// dz' of the MFMA row passes as bf16 pairs hi + lo (hi the round-to-nearest-
-// even bf16 of the value, lo that of the rest; the packed hardware
-// conversion), NO outputs a token (zero past the used ones and past T):
-//   rows[t][0 .. NO)   hi,  rows[t][NO .. 2 NO)  lo
-//   tr[b][o][u]        the same values of token 32 b + u, row o of 2 NO
-// full rows (act = 0): r_ln dz_r | r dz_pre; active rows: r_a dz_act.
-// srec (or null): [Tp][8] per-token scalars of the ring pass.
-__global__ __launch_bounds__(256) void k_dz_pack(const float* __restrict__ tok, int64_t T, int N, int NA, int act,
-                                                 int NO, uint16_t* __restrict__ rows, uint16_t* __restrict__ tr,
-                                                 float* __restrict__ srec) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t Tp = (T + kDzBlock - 1) / kDzBlock * kDzBlock;
-  if (i >= Tp * NO) return;
-  const int64_t t = i / NO;
-  const int o = (int)(i % NO);
-  float v = 0.f;
-  if (t < T) {
-    const float* tk = tok + t * tok_floats(N, NA);
-    if (act) v = o < NA ? tk[2 * N + NA + 6] * tk[2 * N + o] : 0.f;
-    else if (o < N) v = tk[2 * N + NA + 1] * tk[o];
-    else if (o < 2 * N) v = tk[2 * N + NA + 0] * tk[o];
-  }
-  const uint32_t hb = pack2bf(v, 0.f) & 0xFFFFu;
-  const uint32_t lb = pack2bf(v - __uint_as_float(hb << 16), 0.f) & 0xFFFFu;
-  rows[t * 2 * NO + o] = (uint16_t)hb;
-  rows[t * 2 * NO + NO + o] = (uint16_t)lb;
-  uint16_t* blk = tr + (t / kDzBlock) * 2 * NO * kDzBlock;
-  blk[o * kDzBlock + t % kDzBlock] = (uint16_t)hb;
-  blk[(NO + o) * kDzBlock + t % kDzBlock] = (uint16_t)lb;
-  // the token's scalars as the ring pass reads them: r_ln, mu, m1, m2, beta,
-  // then zero (full rows: beta_pre; active rows: beta_a, the others zero)
-  if (srec && o < 8) {
-    const int src[5] = {1, 2, 4, 5, 3};
-    float sv = 0.f;
-    if (t < T && o < 5 && (!act || o == 4)) sv = tok[t * tok_floats(N, NA) + 2 * N + NA + (act ? 7 : src[o])];
-    srec[t * 8 + o] = sv;
-  }
-}
 
 // 4 consecutive bf16 gradient elements from floats
 __device__ __forceinline__ void st4(uint16_t* p, const float (&d)[4]) {
@@ -1710,41 +1756,42 @@ __global__ __launch_bounds__(4 * kActRows) __attribute__((amdgpu_waves_per_eu(4)
     *reinterpret_cast<float4*>(dst + 16 * oh + 4 * g4) = make_float4(dw[oh][0], dw[oh][1], dw[oh][2], dw[oh][3]);
 }
 
-// corr[o] = sum_t mu_t r_ln,t dz_r[t, o] (the part of dW_r the MFMA full-row
-// pass leaves out), one workgroup per output, fixed order
-__global__ __launch_bounds__(256) void k_mu_dz_sum(const float* __restrict__ tok, int64_t T, int N, int NA,
-                                                   float* __restrict__ corr) {
-  __shared__ float red[256];
-  const int o = blockIdx.x, TF = tok_floats(N, NA);
-  float s = 0.f;
-  for (int64_t t = threadIdx.x; t < T; t += 256) {
-    const float* tk = tok + t * TF;
-    s += tk[2 * N + NA + 2] * tk[2 * N + NA + 1] * tk[o];
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) corr[o] = red[0];
-}
-
-// out[col] = sum over rows of in[row][col] - corr[col % ncorr] (corr may be null)
-__global__ __launch_bounds__(256) void k_colsum_rows_corr(const float* __restrict__ in, int64_t nrows, int64_t ncols,
-                                                          const float* __restrict__ corr, int ncorr,
-                                                          float* __restrict__ out) {
+// The sums over row chunks of several weight gradients in one launch (segment
+// blockIdx.y): out[col] = sum_r in[r][col] - corr[col % ncorr] (corr may be
+// null).  Split segments (w1 > 0) hold rows of 32 columns, the first w1 of
+// which belong to out and the next w2 to out2.
+struct ColSeg {
+  const float* in;
+  int64_t ncols;
+  float *out, *out2;
+  const float* corr;
+  int ncorr, w1, w2;
+};
+constexpr int kMaxColSegs = 3 * kMultiMaxQ;
+struct ColSegs {
+  ColSeg g[kMaxColSegs];
+};
+__global__ __launch_bounds__(256) void k_colsum_segs(ColSegs sg, int64_t nrows) {
+  const ColSeg& g = sg.g[blockIdx.y];
   const int64_t col = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (col >= ncols) return;
+  if (col >= g.ncols) return;
+  float* out = g.out + col;
+  if (g.w1 > 0) {
+    const int64_t row = col / 32;
+    const int o = (int)(col % 32);
+    if (o < g.w1) out = g.out + row * g.w1 + o;
+    else if (o < g.w1 + g.w2) out = g.out2 + row * g.w2 + (o - g.w1);
+    else return;
+  }
   float s = 0.f;
   for (int64_t r0 = 0; r0 < nrows; r0 += 8) {
     float v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = (r0 + u < nrows) ? in[(r0 + u) * ncols + col] : 0.f;
+    for (int u = 0; u < 8; ++u) v[u] = (r0 + u < nrows) ? g.in[(r0 + u) * g.ncols + col] : 0.f;
 #pragma unroll
     for (int u = 0; u < 8; ++u) s += v[u];
   }
-  out[col] = corr ? s - corr[col % ncorr] : s;
+  *out = g.corr ? s - g.corr[col % g.ncorr] : s;
 }
 
 // ------------------------------------------------------------ launchers
@@ -1778,7 +1825,7 @@ static int dot_run_len(const xhc_dims* d, int nthr) { return halve_to_fill(kDotR
 hipError_t launch_bwd_post(const xhc_dims* d, const void* dXn, void* X, const void* Xact, const void* F,
                            const float* conv_w, const int32_t* idx, const float* p, const float* Hres,
                            const float* Hpost, void* dX, void* dF, float* dHres, float* dHpost, float* dp,
-                           float* dconv_w, char* ws, hipStream_t s, bool grad_f32) {
+                           float* dconv_w, char* ws, hipStream_t s, bool grad_f32, bool add_dp) {
   const int64_t T = d->T, S = d->S;
   const int N = d->N, C = d->C, k = d->k, Kr = d->Kr;
   const int64_t ncb = post_chunks(C);
@@ -1808,7 +1855,7 @@ hipError_t launch_bwd_post(const xhc_dims* d, const void* dXn, void* X, const vo
           part);                                                                                                 \
       k_colsum_rows<<<dim3((unsigned)((T * nd + 255) / 256)), dim3(256), 0, s>>>(part, C / 256, T * nd, dsum);     \
       k_bwd_post_token<KRV, KMV><<<dim3((unsigned)((T + 127) / 128)), dim3(128), 0, s>>>(dsum, 1, T * nd, 1, nd,    \
-          T, k, d->gram_schmidt, p, Hpost, dHres, dHpost, dp, coef);                                              \
+          T, k, d->gram_schmidt, p, Hpost, dHres, dHpost, dp, add_dp ? 1 : 0, coef);                                              \
     } else if constexpr (KRV == 1) {                                                                             \
       /* one pass over the rows: the dot products and the element pass */                                      \
       if (dX != dXn && N > k) {                                                                                  \
@@ -1821,13 +1868,13 @@ hipError_t launch_bwd_post(const xhc_dims* d, const void* dXn, void* X, const vo
           kap[2], conv_w, idx, part, Hres, p, Hpost, reinterpret_cast<TS*>(X), reinterpret_cast<TG*>(dX),        \
           reinterpret_cast<TS*>(dF));                                                                            \
       k_bwd_post_token<KRV, KMV><<<dim3((unsigned)((T + 127) / 128)), dim3(128), 0, s>>>(part, ncb, nd * T, T,      \
-          1, T, k, d->gram_schmidt, p, Hpost, dHres, dHpost, dp, coef);                                           \
+          1, T, k, d->gram_schmidt, p, Hpost, dHres, dHpost, dp, add_dp ? 1 : 0, coef);                                           \
     } else {                                                                                                     \
       k_bwd_post_dots<TS, TG, KRV, KMV><<<grid, dim3(256), 0, s>>>(reinterpret_cast<const TG*>(dXn),            \
           reinterpret_cast<const TS*>(Xact), reinterpret_cast<const TS*>(F), T, S, N, C, k, kap[0], kap[1],       \
           kap[2], conv_w, idx, part);                                                                            \
       k_bwd_post_token<KRV, KMV><<<dim3((unsigned)((T + 127) / 128)), dim3(128), 0, s>>>(part, ncb, nd * T, T,      \
-          1, T, k, d->gram_schmidt, p, Hpost, dHres, dHpost, dp, coef);                                           \
+          1, T, k, d->gram_schmidt, p, Hpost, dHres, dHpost, dp, add_dp ? 1 : 0, coef);                                           \
     }                                                                                                            \
     if (fused) {                                                                                                 \
       if (dX != dXn && N > k) {                                                                                  \
@@ -1929,7 +1976,6 @@ size_t bwd_post_ws_bytes(const xhc_dims* d) {
 // the router's LayerNorm terms of the first pass (later passes have no router
 // gradient, so theirs are zero).  The weight partials of output block ob go
 // to wout[ob] ([chunk][N C][16]: the router, then pre-map q).
-constexpr int kMultiMaxQ = 4;
 struct MultiRows {
   const float* tok[kMultiMaxQ];   // per pass: the token records
   const float* hrd[kMultiMaxQ];   // per pass: weights of the dense read [T, N]
@@ -1937,51 +1983,37 @@ struct MultiRows {
   const float* w[kMultiMaxQ + 1];  // W_r, then W_pre of pass q ([N C][16] each)
   float* wout[kMultiMaxQ + 1];
 };
-// Per token, the inputs of the multi-map ring pass gathered from the passes' token
-// records: [r_ln dz_r (16) | r dz_pre,q (16 each) | r_ln, mu, m1, m2,
-// sum_q beta_pre,q, pad], pitch 16 (NQ + 1) + 8 floats.
+// The multi-map ring pass's inputs from the passes' token records: dz' packed
+// (outputs r_ln dz_r (16) | r dz_pre,q (16 each), padded to whole 32-blocks,
+// zero past T) and the scalars r_ln, mu, m1, m2, sum_q beta_pre,q.
 template <int NQ>
-__global__ __launch_bounds__(256) void k_multi_prep(MultiRows m, int64_t T, int N, int NA, float* __restrict__ out) {
-  constexpr int NO = 16 * (NQ + 1), PITCH = NO + 8;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= T * PITCH) return;
-  const int64_t t = i / PITCH;
-  const int o = (int)(i % PITCH);
-  const int TF = tok_floats(N, NA);
-  float v = 0.f;
-  if (o < NO) {
-    const float* tk = m.tok[o < 16 ? 0 : o / 16 - 1] + t * TF;
-    v = o < 16 ? tk[2 * N + NA + 1] * tk[o] : tk[2 * N + NA + 0] * tk[N + o % 16];   // r_ln dz_r | r dz_pre,q
-  } else if (o < NO + 4) {
-    const int map[4] = {1, 2, 4, 5};   // r_ln, mu, m1, m2 of the first pass
-    v = m.tok[0][t * TF + 2 * N + NA + map[o - NO]];
-  } else if (o == NO + 4) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) v += m.tok[q][t * TF + 2 * N + NA + 3];   // beta_pre, passes in order
-  }
-  out[i] = v;
-}
-
-// The dz' of k_multi_prep as bf16 pairs hi + lo in the layouts of
-// k_dz_pack (token rows [t][2 NOP], 32-token transposes [b][2 NOP][32]),
-// NOP = the NO outputs padded to whole 32-blocks (zero past NO and past T).
-template <int NQ>
-__global__ __launch_bounds__(256) void k_dz_pack_multi(const float* __restrict__ prep, int64_t T,
-                                                       uint16_t* __restrict__ rows, uint16_t* __restrict__ tr) {
-  constexpr int NO = 16 * (NQ + 1), NOP = (NO + 31) / 32 * 32, PITCH = NO + 8;
+__global__ __launch_bounds__(256) void k_dz_pack_multi(MultiRows m, int64_t T, int N, int NA,
+                                                       uint16_t* __restrict__ rows, float* __restrict__ srec) {
+  constexpr int NO = 16 * (NQ + 1), NOP = (NO + 31) / 32 * 32;
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t Tp = (T + kDzBlock - 1) / kDzBlock * kDzBlock;
   if (i >= Tp * NOP) return;
   const int64_t t = i / NOP;
   const int o = (int)(i % NOP);
-  const float v = (t < T && o < NO) ? prep[t * PITCH + o] : 0.f;
-  const uint32_t hb = pack2bf(v, 0.f) & 0xFFFFu;
-  const uint32_t lb = pack2bf(v - __uint_as_float(hb << 16), 0.f) & 0xFFFFu;
-  rows[t * 2 * NOP + o] = (uint16_t)hb;
-  rows[t * 2 * NOP + NOP + o] = (uint16_t)lb;
-  uint16_t* blk = tr + (t / kDzBlock) * 2 * NOP * kDzBlock;
-  blk[o * kDzBlock + t % kDzBlock] = (uint16_t)hb;
-  blk[(NOP + o) * kDzBlock + t % kDzBlock] = (uint16_t)lb;
+  const int TF = tok_floats(N, NA);
+  const int64_t at = t * TF + 2 * N + NA;   // the token's scalars
+  float v = 0.f;
+  if (t < T && o < NO) {
+    const float* tk = m.tok[o < 16 ? 0 : o / 16 - 1];
+    v = o < 16 ? tk[at + 1] * tk[t * TF + o] : tk[at] * tk[t * TF + N + o % 16];
+  }
+  dz_store(rows, Tp, NOP, t, o, v);
+  if (o < 8) {
+    float sv = 0.f;
+    if (t < T && o < 4) {
+      const int map[4] = {1, 2, 4, 5};   // r_ln, mu, m1, m2 of the first pass
+      sv = m.tok[0][at + map[o]];
+    } else if (t < T && o == 4) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) sv += m.tok[q][at + 3];   // beta_pre, passes in order
+    }
+    srec[t * 8 + o] = sv;
+  }
 }
 
 constexpr int64_t kRowChunk = 1024;   // tokens per weight-gradient partial
@@ -1996,15 +2028,14 @@ BwdPreWs bwd_pre_ws(const xhc_dims* d, char* ws) {
   w.part = reinterpret_cast<float*>(ws);
   w.tok = w.part + ncb * N * T;
   w.pg = w.tok + T * tok_floats(N, NA);
-  w.wpart_r = w.pg + T * pg_floats(N, k, Kr);
+  w.wpart_r = w.pg + T * (pg_floats(N, k, Kr) + N);
   w.wpart_p = w.wpart_r + nchunk * (int64_t)N * C * N;
   w.wpart_a = w.wpart_p + nchunk * (int64_t)N * C * N;
-  w.red_a = w.wpart_a + nchunk * (int64_t)k * C * 32;           // [kC][32]
-  w.pgsum = w.red_a + (int64_t)k * C * 32;
+  w.corr = w.wpart_a + nchunk * (int64_t)k * C * 32;
   // packed dz' (16-byte aligned): full rows 2 NO_f, active rows 2 x 32 bf16 a
   // token, in token rows and in transposed 32-token blocks
   const int64_t Tp = (T + kDzBlock - 1) / kDzBlock * kDzBlock;
-  const uintptr_t a = reinterpret_cast<uintptr_t>(w.pgsum + pg_floats(N, k, Kr) + N);
+  const uintptr_t a = reinterpret_cast<uintptr_t>(w.corr + N);
   w.dzf = reinterpret_cast<uint16_t*>((a + 15) / 16 * 16);
   w.dza = w.dzf + Tp * 2 * (2 * N <= 32 ? 32 : 64) * 2;
   w.srec = reinterpret_cast<float*>(w.dza + Tp * 2 * 32 * 2);   // 16-byte aligned: Tp % 32 == 0
@@ -2030,17 +2061,16 @@ hipError_t launch_bwd_dhpre_multi(const xhc_dims* d, int Q, const void* X, const
   return hipGetLastError();
 }
 
-// prep [T][16 (Q + 1) + 8] floats, then (16-byte aligned) the packed dz'
-static size_t multi_prep_floats(int64_t T, int Q) { return (size_t)T * (16 * (Q + 1) + 8); }
+// the packed dz', then the scalars [Tp][8]
 static int64_t multi_nop(int Q) { return (16 * (Q + 1) + 31) / 32 * 32; }
 size_t bwd_rows_multi_ws_bytes(const xhc_dims* d, int Q) {
   const size_t Tp = (size_t)((d->T + kDzBlock - 1) / kDzBlock * kDzBlock);
-  return multi_prep_floats(d->T, Q) * sizeof(float) + 16 + Tp * 2 * multi_nop(Q) * 2 * sizeof(uint16_t);
+  return Tp * 2 * multi_nop(Q) * 2 * sizeof(uint16_t) + Tp * 8 * sizeof(float);
 }
 
 hipError_t launch_bwd_rows_multi(const xhc_dims* d, int Q, const void* X, void* dX, const float* W_r,
                                  const float* W_pre, const void* d_input, const float* const* hrd, char* const* ws,
-                                 float* prep, hipStream_t s) {
+                                 char* pack_ws, hipStream_t s) {
   if (!bwd_rows_multi_supported(d, Q)) return hipErrorInvalidValue;
   const int64_t T = d->T;
   const int N = d->N, C = d->C, NA = d->k * d->Kr + d->k * d->k;
@@ -2056,23 +2086,14 @@ hipError_t launch_bwd_rows_multi(const xhc_dims* d, int Q, const void* X, void* 
     m.w[q + 1] = W_pre + (int64_t)q * NC * N;
     m.wout[q + 1] = w.wpart_p;
   }
-  const int64_t np = T * (16 * (Q + 1) + 8);
-  const dim3 gp((unsigned)((np + 255) / 256));
   const int64_t Tp = (T + kDzBlock - 1) / kDzBlock * kDzBlock, nop = multi_nop(Q);
-  const uintptr_t a = reinterpret_cast<uintptr_t>(prep + multi_prep_floats(T, Q));
-  uint16_t* dzp = reinterpret_cast<uint16_t*>((a + 15) / 16 * 16);
+  uint16_t* dzp = reinterpret_cast<uint16_t*>(pack_ws);
+  float* srec = reinterpret_cast<float*>(dzp + Tp * 2 * nop * 2);
   const dim3 gk((unsigned)((Tp * nop + 255) / 256));
-  if (Q == 4) {
-    k_multi_prep<4><<<gp, dim3(256), 0, s>>>(m, T, N, NA, prep);
-    k_dz_pack_multi<4><<<gk, dim3(256), 0, s>>>(prep, T, dzp, dzp + Tp * 2 * nop);
-  } else {
-    k_multi_prep<2><<<gp, dim3(256), 0, s>>>(m, T, N, NA, prep);
-    k_dz_pack_multi<2><<<gk, dim3(256), 0, s>>>(prep, T, dzp, dzp + Tp * 2 * nop);
-  }
-  hipError_t e = hipGetLastError();
+  if (Q == 4) k_dz_pack_multi<4><<<gk, dim3(256), 0, s>>>(m, T, N, NA, dzp, srec);
+  else k_dz_pack_multi<2><<<gk, dim3(256), 0, s>>>(m, T, N, NA, dzp, srec);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // the ring pass reads the prep rows' scalars (r_ln, mu, m1, m2, sum beta_pre)
-  // at offset 16 (Q + 1) of each row
   const int no = 16 * (Q + 1);
   RowRingDesc rd{};
   rd.X = X;
@@ -2093,8 +2114,8 @@ hipError_t launch_bwd_rows_multi(const xhc_dims* d, int Q, const void* X, void* 
   rd.nout = no;
   rd.dzp = dzp;
   rd.nop = (int)nop;
-  rd.srec = prep + no;
-  rd.srec_stride = no + 8;
+  rd.srec = srec;
+  rd.srec_stride = 8;
   rd.T = T;
   rd.tchunk = kRowChunk;
   rd.N = N;
@@ -2108,11 +2129,10 @@ size_t bwd_pre_ws_bytes(const xhc_dims* d) {
   const int NA = k * Kr + k * k;
   const int64_t nchunk = (T + kRowChunk - 1) / kRowChunk;
   size_t n = (size_t)post_chunks(C) * N * T;                    // dH^pre partials
-  n += (size_t)T * tok_floats(N, NA) + (size_t)T * pg_floats(N, k, Kr);
+  n += (size_t)T * tok_floats(N, NA) + (size_t)T * (pg_floats(N, k, Kr) + N);
   n += (size_t)nchunk * N * C * N * 2;                           // dW_r, dW_pre partials
   n += (size_t)nchunk * k * C * 32;                              // dW_act partials (<= 32 columns)
-  n += (size_t)k * C * 32 + (size_t)pg_floats(N, k, Kr);          // reduced dW_act, reduced gradients
-  n += (size_t)N;                                                // token sum of mu dz'_r
+  n += (size_t)N;                                                // token sum of mu r_ln dz_r
   const size_t Tp = (size_t)((T + kDzBlock - 1) / kDzBlock * kDzBlock);
   const size_t dz = Tp * 2 * ((2 * N <= 32 ? 32 : 64) + 32) * 2 * sizeof(uint16_t);   // packed dz'
   return n * sizeof(float) + 16 + dz + 2 * Tp * 8 * sizeof(float) + 1024;             // + scalar rows
@@ -2123,219 +2143,229 @@ bool bwd_pre_supported(const xhc_dims* d) {
          d->k * d->Kr + d->k * d->k <= 32;
 }
 
-hipError_t launch_bwd_pre(const xhc_dims* d, const void* X, const float* colsum, const float* W_r,
-                          const float* W_pre, const float* W_res, const float* W_post, const float* alpha,
-                          const float* b_res, const float* saved, const int32_t* idx, const float* p,
-                          const float* Hpre, const float* Hpost, const void* d_input, const float* dHres,
-                          const float* dHpost, const float* dp, void* dX, float* dW_r, float* dW_pre, float* dW_res,
-                          float* dW_post, float* dalpha, float* db_pre, float* db_res, float* db_post, char* ws,
-                          hipStream_t s, const float* dhpre_act, const float* Hpre_read, bool dense_rows,
-                          const void* X_bf16, bool act_rows, int phase, const void* act_din) {
-  const float* Hrd = Hpre_read ? Hpre_read : Hpre;   // weights of the dense-read term
+// whether the row passes are the MFMA ones
+static bool pre_mf(const xhc_dims* d) {
+  const int N = d->N, NA = d->k * d->Kr + d->k * d->k;
+  return d->state_dtype == XHC_BF16 && (N == 4 || N == 8 || N == 16 || N == 32) && NA <= 32 &&
+         d->C % (2 * kMfRows) == 0;
+}
+static bool pre_mfa32(const xhc_dims* d, const BwdPre& b) {
+  return b.X_bf16 && d->state_dtype == XHC_F32 && d->k * d->Kr + d->k * d->k <= 32 && d->C % (2 * kMfRows) == 0;
+}
+
+// the token reverses of n pre-map reverses (their <d input, x_i> partials are
+// in the workspaces already) in one launch
+hipError_t launch_bwd_pre_tokens(const xhc_dims* d, const BwdPre* bs, int n, hipStream_t s) {
+  if (n < 1 || n > kMultiMaxQ) return hipErrorInvalidValue;
+  const int64_t T = d->T, Tp = (T + kDzBlock - 1) / kDzBlock * kDzBlock;
+  const int N = d->N, k = d->k;
+  PreTokMulti ma{};
+  for (int q = 0; q < n; ++q) {
+    const BwdPre& b = bs[q];
+    const BwdPreWs w = bwd_pre_ws(d, b.ws);
+    PreTokArgs& ta = ma.a[q];
+    ta.part = b.dense_rows ? w.part : nullptr;
+    ta.nchunk = post_chunks(d->C);
+    ta.T = T;
+    ta.Tp = Tp;
+    ta.N = N;
+    ta.m = d->m;
+    ta.k = k;
+    ta.Kr = d->Kr;
+    ta.C = d->C;
+    ta.saved = b.saved;
+    ta.colsum = b.colsum;
+    ta.b_res = b.b_res;
+    ta.al_pre = b.al_pre;
+    ta.al_res = b.al_res;
+    ta.al_post = b.al_post;
+    ta.idx = b.idx;
+    ta.p = b.p;
+    ta.Hpre = b.Hpre;
+    ta.Hpost = b.Hpost;
+    ta.dHres = b.dHres;
+    ta.dHpost = b.dHpost;
+    ta.dp = b.dp;
+    ta.dhact = b.dhpre_act;
+    ta.hmask = b.hmask;
+    ta.eps = d->eps;
+    ta.iters = d->sinkhorn_iters;
+    ta.delta = d->clamp_delta;
+    ta.tok = w.tok;
+    ta.pg = w.pg;
+    if (b.own_rows && b.dense_rows && pre_mf(d)) {
+      ta.dzf = w.dzf;
+      ta.srec = w.srec;
+      ta.nof = 2 * N <= 32 ? 32 : 64;
+    }
+    if (b.own_rows && b.act_rows && (pre_mf(d) || pre_mfa32(d, b))) {
+      ta.dza = w.dza;
+      ta.sreca = pre_mf(d) ? nullptr : w.sreca;
+    }
+    ta.softmax = d->router == XHC_ROUTER_SOFTMAX ? 1 : 0;
+  }
+  const auto grid = [&](int KP) {
+    const int nt = kPreTokThreads / mix_lanes(KP);
+    return dim3((unsigned)((Tp + nt - 1) / nt), (unsigned)n);
+  };
+  if (k <= 2) k_bwd_pre_token<2><<<grid(2), dim3(kPreTokThreads), 0, s>>>(ma);
+  else if (k <= 4) k_bwd_pre_token<4><<<grid(4), dim3(kPreTokThreads), 0, s>>>(ma);
+  else k_bwd_pre_token<8><<<grid(8), dim3(kPreTokThreads), 0, s>>>(ma);
+  return hipGetLastError();
+}
+
+// the token and row-chunk reductions of n pre-map reverses (fixed order): two launches
+hipError_t launch_bwd_pre_reduce(const xhc_dims* d, const BwdPre* bs, int n, hipStream_t s) {
+  if (n < 1 || n > kMultiMaxQ) return hipErrorInvalidValue;
+  const int64_t T = d->T;
+  const int N = d->N, k = d->k, Kr = d->Kr, C = d->C;
+  const int64_t nchunk = (T + kRowChunk - 1) / kRowChunk, nfull = (int64_t)N * C * N, nact = (int64_t)k * C * 32;
+  TokenSumsMulti ts{};
+  ColSegs cs{};
+  int ns = 0;
+  int64_t most = 0;
+  const auto seg = [&](const ColSeg& g) {
+    cs.g[ns++] = g;
+    most = g.ncols > most ? g.ncols : most;
+  };
+  for (int q = 0; q < n; ++q) {
+    const BwdPre& b = bs[q];
+    const BwdPreWs w = bwd_pre_ws(d, b.ws);
+    // (the MFMA row passes leave the token sum of mu r_ln dz_r in dW_r)
+    float* const corr = b.dW_r && pre_mf(d) ? w.corr : nullptr;
+    ts.a[q] = TokenSums{w.pg, b.dal_pre, b.dal_res, b.dal_post, b.db_pre, b.db_res, b.db_post, corr};
+    if (b.dW_r) seg(ColSeg{w.wpart_r, nfull, b.dW_r, nullptr, corr, N, 0, 0});
+    if (b.dW_pre) seg(ColSeg{w.wpart_p, nfull, b.dW_pre, nullptr, nullptr, 1, 0, 0});
+    // active partials are [chunk][kC][32]
+    if (b.dW_post) seg(ColSeg{w.wpart_a, nact, b.dW_post, b.dW_res, nullptr, 1, k * Kr, b.dW_res ? k * k : 0});
+  }
+  k_sum_tokens<<<dim3((unsigned)(pg_floats(N, k, Kr) + N), (unsigned)n), dim3(kSumThreads), 0, s>>>(ts, T, N, k, Kr);
+  if (ns > 0)
+    k_colsum_segs<<<dim3((unsigned)((most + 255) / 256), (unsigned)ns), dim3(256), 0, s>>>(cs, nchunk);
+  return hipGetLastError();
+}
+
+hipError_t launch_bwd_pre(const xhc_dims* d, const BwdPre& b, hipStream_t s) {
   const int64_t T = d->T;
   const int N = d->N, k = d->k, Kr = d->Kr, C = d->C;
   const int NA = k * Kr + k * k;
-  const int64_t ncb = post_chunks(C);
   const int64_t nchunk = (T + kRowChunk - 1) / kRowChunk;
-  const BwdPreWs w = bwd_pre_ws(d, ws);
-  float* const part = w.part;
-  float* const tok = w.tok;
-  float* const pg = w.pg;
-  float* const wpart_r = w.wpart_r;
-  float* const wpart_p = w.wpart_p;
-  float* const wpart_a = w.wpart_a;
-  float* const red_a = w.red_a;
-  float* const pgsum = w.pgsum;
-  const bool mf = d->state_dtype == XHC_BF16 && (N == 4 || N == 8 || N == 16 || N == 32) && NA <= 32 &&
-                  C % (2 * kMfRows) == 0;
-  hipError_t e = hipSuccess;
-  if (phase == kBwdPreReduce) {
-    // the row passes ran elsewhere (their partials are in this workspace)
-    if (mf) k_mu_dz_sum<<<dim3((unsigned)N), dim3(256), 0, s>>>(tok, T, N, NA, pgsum + pg_floats(N, k, Kr));
-  } else {
-    if (phase != kBwdPreTokensGiven && dense_rows) {   // (else the partials are given, or there are none)
-      XHC_TS_DISPATCH(d->state_dtype,
-        k_bwd_dhpre<TS><<<dim3((unsigned)(T * ncb)), dim3(256), 0, s>>>(reinterpret_cast<const TS*>(X),
-            reinterpret_cast<const TS*>(d_input), T, N, C, part));
-    }
-    {
-      PreTokArgs ta{};
-      ta.part = dense_rows ? part : nullptr;
-      ta.nchunk = ncb;
-      ta.T = T;
-      ta.N = N;
-      ta.m = d->m;
-      ta.k = k;
-      ta.Kr = Kr;
-      ta.C = C;
-      ta.saved = saved;
-      ta.colsum = colsum;
-      ta.alpha = alpha;
-      ta.b_res = b_res;
-      ta.idx = idx;
-      ta.p = p;
-      ta.Hpre = Hpre;
-      ta.Hpost = Hpost;
-      ta.dHres = dHres;
-      ta.dHpost = dHpost;
-      ta.dp = dp;
-      ta.dhact = dhpre_act;
-      ta.eps = d->eps;
-      ta.iters = d->sinkhorn_iters;
-      ta.delta = d->clamp_delta;
-      ta.tok = tok;
-      ta.pg = pg;
-      ta.softmax = d->router == XHC_ROUTER_SOFTMAX ? 1 : 0;
-      const auto grid = [&](int KP) {
-        const int nt = kPreTokThreads / mix_lanes(KP);
-        return dim3((unsigned)((T + nt - 1) / nt));
-      };
-      if (k <= 2) k_bwd_pre_token<2><<<grid(2), dim3(kPreTokThreads), 0, s>>>(ta);
-      else if (k <= 4) k_bwd_pre_token<4><<<grid(4), dim3(kPreTokThreads), 0, s>>>(ta);
-      else k_bwd_pre_token<8><<<grid(8), dim3(kPreTokThreads), 0, s>>>(ta);
-    }
-    e = hipGetLastError();
-    if (e != hipSuccess || phase == kBwdPreTokens || phase == kBwdPreTokensGiven) return e;
-    if (mf) {
-      // 128 rows per workgroup (256 contiguous bytes of each state row per
-      // token); C % 256 == 0 is part of the backward's supported shapes
-      const int64_t Tp = (T + kDzBlock - 1) / kDzBlock * kDzBlock;
-      const int NOf = 2 * N <= 32 ? 32 : 64;
-      if (dense_rows)
-        k_dz_pack<<<dim3((unsigned)((Tp * NOf + 255) / 256)), dim3(256), 0, s>>>(tok, T, N, NA, 0, NOf, w.dzf,
-                                                                                 w.dzf + Tp * 2 * NOf, w.srec);
-      if (act_rows)
-        k_dz_pack<<<dim3((unsigned)((Tp * 32 + 255) / 256)), dim3(256), 0, s>>>(tok, T, N, NA, 1, 32, w.dza,
-                                                                                w.dza + Tp * 2 * 32, nullptr);
-      if (dense_rows) {
-        // 2N outputs padded to one block of 32 (N <= 16) or two (N = 32)
-        RowRingDesc rd{};
-        rd.X = X;
-        rd.dX = dX;
-        rd.nq = 1;
-        rd.din[0] = d_input;
-        rd.hp[0] = Hrd;
-        rd.hp_stride = N;
-        rd.w[0] = W_r;
-        rd.w[1] = W_pre;
-        rd.win[0] = rd.win[1] = N;
-        rd.nwin = 2;
-        rd.wout[0] = wpart_r;
-        rd.wout[1] = wpart_p;
-        rd.wout_w = N;
-        rd.nout = 2 * N;
-        rd.dzp = w.dzf;
-        rd.nop = NOf;
-        rd.srec = w.srec;
-        rd.srec_stride = 8;
-        rd.T = T;
-        rd.tchunk = kRowChunk;
-        rd.N = N;
-        rd.C = C;
-        e = launch_bwd_rows_ring(rd, (int64_t)N * C, s);
-        if (e != hipSuccess) return e;
-      }
-      // 128 rows per workgroup (C % 256 == 0); the dense read of the active
-      // rows is in the full-row pass
-      const dim3 ga((unsigned)((int64_t)k * C / kActRows), (unsigned)nchunk);
-      if (act_rows)
-        k_bwd_act_rows_mfma<<<ga, dim3(4 * kActRows), 0, s>>>(reinterpret_cast<const uint16_t*>(X),
-            reinterpret_cast<uint16_t*>(dX), W_post, W_res, idx, tok, T, N, k, C, Kr, NA, kRowChunk, w.dza, wpart_a);
-      k_mu_dz_sum<<<dim3((unsigned)N), dim3(256), 0, s>>>(tok, T, N, NA, pgsum + pg_floats(N, k, Kr));
-    }
-    // an fp32 state given with its exact bf16 copy (the k-row view of an
-    // xHC-Flash sublayer, N = k, whose slot j is row j): the active rows take
-    // the ring pass with fp32 gradient rows
-    const bool mfa32 = !mf && X_bf16 && d->state_dtype == XHC_F32 && NA <= 32 && C % (2 * kMfRows) == 0;
-    if (mfa32 && act_rows) {
-      if (N != k) return hipErrorInvalidValue;
-      const int64_t Tp = (T + kDzBlock - 1) / kDzBlock * kDzBlock;
-      k_dz_pack<<<dim3((unsigned)((Tp * 32 + 255) / 256)), dim3(256), 0, s>>>(tok, T, N, NA, 1, 32, w.dza,
-                                                                              w.dza + Tp * 2 * 32, w.sreca);
+  const BwdPreWs w = bwd_pre_ws(d, b.ws);
+  const void *const X = b.X, *const d_input = b.d_input, *const X_bf16 = b.X_bf16, *const act_din = b.act_din;
+  void* const dX = b.dX;
+  const float *const W_r = b.W_r, *const W_pre = b.W_pre, *const W_res = b.W_res, *const W_post = b.W_post;
+  const float* const Hpre = b.Hpre;
+  const float* const Hrd = b.hmask ? b.hmask : Hpre;   // weights of the dense-read term
+  const int32_t* const idx = b.idx;
+  const bool dense_rows = b.dense_rows, act_rows = b.act_rows;
+  float *const tok = w.tok, *const wpart_r = w.wpart_r, *const wpart_p = w.wpart_p, *const wpart_a = w.wpart_a;
+  const bool mf = pre_mf(d);
+  if (dense_rows) {
+    const int64_t ncb = post_chunks(C);
+    XHC_TS_DISPATCH(d->state_dtype,
+      k_bwd_dhpre<TS><<<dim3((unsigned)(T * ncb)), dim3(256), 0, s>>>(reinterpret_cast<const TS*>(X),
+          reinterpret_cast<const TS*>(d_input), T, N, C, w.part));
+  }
+  hipError_t e = launch_bwd_pre_tokens(d, &b, 1, s);
+  if (e != hipSuccess) return e;
+  if (mf) {
+    // 128 rows per workgroup (256 contiguous bytes of each state row per
+    // token); C % 256 == 0 is part of the backward's supported shapes
+    const int NOf = 2 * N <= 32 ? 32 : 64;
+    if (dense_rows) {
+      // 2N outputs padded to one block of 32 (N <= 16) or two (N = 32)
       RowRingDesc rd{};
-      rd.X = X_bf16;
+      rd.X = X;
       rd.dX = dX;
-      rd.dx_f32 = true;
-      rd.nq = act_din ? 1 : 0;
-      rd.din[0] = act_din;
-      rd.hp[0] = Hpre;   // [T, k]: the weight of each slot's read of d input
-      rd.hp_stride = k;
-      rd.w[0] = W_post;
-      rd.w[1] = W_res;
-      rd.win[0] = k * Kr;
-      rd.win[1] = k * k;
+      rd.nq = 1;
+      rd.din[0] = d_input;
+      rd.hp[0] = Hrd;
+      rd.hp_stride = N;
+      rd.w[0] = W_r;
+      rd.w[1] = W_pre;
+      rd.win[0] = rd.win[1] = N;
       rd.nwin = 2;
-      rd.wout[0] = wpart_a;
-      rd.wout_w = 32;
-      rd.nout = NA;
-      rd.dzp = w.dza;
-      rd.nop = 32;
-      rd.srec = w.sreca;
+      rd.wout[0] = wpart_r;
+      rd.wout[1] = wpart_p;
+      rd.wout_w = N;
+      rd.nout = 2 * N;
+      rd.dzp = w.dzf;
+      rd.nop = NOf;
+      rd.srec = w.srec;
       rd.srec_stride = 8;
       rd.T = T;
       rd.tchunk = kRowChunk;
       rd.N = N;
       rd.C = C;
-      e = launch_bwd_rows_ring(rd, (int64_t)k * C, s);
+      e = launch_bwd_rows_ring(rd, (int64_t)N * C, s);
       if (e != hipSuccess) return e;
     }
-    const dim3 gfull((unsigned)(((int64_t)N * C + 255) / 256), (unsigned)nchunk);
+    // 128 rows per workgroup (C % 256 == 0); the dense read of the active
+    // rows is in the full-row pass
+    const dim3 ga((unsigned)((int64_t)k * C / kActRows), (unsigned)nchunk);
+    if (act_rows)
+      k_bwd_act_rows_mfma<<<ga, dim3(4 * kActRows), 0, s>>>(reinterpret_cast<const uint16_t*>(X),
+          reinterpret_cast<uint16_t*>(dX), W_post, W_res, idx, tok, T, N, k, C, Kr, NA, kRowChunk, w.dza, wpart_a);
+  }
+  // an fp32 state given with its exact bf16 copy (the k-row view of an
+  // xHC-Flash sublayer, N = k, whose slot j is row j): the active rows take
+  // the ring pass with fp32 gradient rows
+  const bool mfa32 = pre_mfa32(d, b);
+  if (mfa32 && act_rows) {
+    if (N != k) return hipErrorInvalidValue;
+    RowRingDesc rd{};
+    rd.X = X_bf16;
+    rd.dX = dX;
+    rd.dx_f32 = true;
+    rd.nq = act_din ? 1 : 0;
+    rd.din[0] = act_din;
+    rd.hp[0] = Hpre;   // [T, k]: the weight of each slot's read of d input
+    rd.hp_stride = k;
+    rd.w[0] = W_post;
+    rd.w[1] = W_res;
+    rd.win[0] = k * Kr;
+    rd.win[1] = k * k;
+    rd.nwin = W_res ? 2 : 1;
+    rd.wout[0] = wpart_a;
+    rd.wout_w = 32;
+    rd.nout = W_res ? NA : k * Kr;
+    rd.dzp = w.dza;
+    rd.nop = 32;
+    rd.srec = w.sreca;
+    rd.srec_stride = 8;
+    rd.T = T;
+    rd.tchunk = kRowChunk;
+    rd.N = N;
+    rd.C = C;
+    e = launch_bwd_rows_ring(rd, (int64_t)k * C, s);
+    if (e != hipSuccess) return e;
+  }
+  const dim3 gfull((unsigned)(((int64_t)N * C + 255) / 256), (unsigned)nchunk);
 #define XHC_FULL_ROWS(NNV)                                                                                       \
-    XHC_TS_DISPATCH(d->state_dtype,                                                                                \
-      k_bwd_full_rows<TS, NNV><<<gfull, dim3(256), 0, s>>>(reinterpret_cast<const TS*>(X),                        \
-          reinterpret_cast<const TS*>(d_input), reinterpret_cast<TS*>(dX), W_r, W_pre, Hrd, tok, T, C, NA,         \
-          kRowChunk, wpart_r, wpart_p))
-    if (!mf) {
-      if (dense_rows) {
-        switch (N) {
-          case 4: XHC_FULL_ROWS(4); break;
-          case 8: XHC_FULL_ROWS(8); break;
-          case 16: XHC_FULL_ROWS(16); break;
-          default: XHC_FULL_ROWS(32); break;
-        }
-      }
-      if (!mfa32 && act_rows) {
-        const dim3 gact((unsigned)(((int64_t)k * C + 255) / 256), (unsigned)nchunk);
-        XHC_TS_DISPATCH(d->state_dtype,
-          k_bwd_act_rows<TS, 32><<<gact, dim3(256), 0, s>>>(reinterpret_cast<const TS*>(X), reinterpret_cast<TS*>(dX),
-              W_post, W_res, idx, tok, T, N, k, C, Kr, kRowChunk, wpart_a));
+  XHC_TS_DISPATCH(d->state_dtype,                                                                                \
+    k_bwd_full_rows<TS, NNV><<<gfull, dim3(256), 0, s>>>(reinterpret_cast<const TS*>(X),                        \
+        reinterpret_cast<const TS*>(d_input), reinterpret_cast<TS*>(dX), W_r, W_pre, Hrd, tok, T, C, NA,         \
+        kRowChunk, wpart_r, wpart_p))
+  if (!mf) {
+    if (dense_rows) {
+      switch (N) {
+        case 4: XHC_FULL_ROWS(4); break;
+        case 8: XHC_FULL_ROWS(8); break;
+        case 16: XHC_FULL_ROWS(16); break;
+        default: XHC_FULL_ROWS(32); break;
       }
     }
+    if (!mfa32 && act_rows) {
+      const dim3 gact((unsigned)(((int64_t)k * C + 255) / 256), (unsigned)nchunk);
+      XHC_TS_DISPATCH(d->state_dtype,
+        k_bwd_act_rows<TS, 32><<<gact, dim3(256), 0, s>>>(reinterpret_cast<const TS*>(X), reinterpret_cast<TS*>(dX),
+            W_post, W_res, idx, tok, T, N, k, C, Kr, kRowChunk, wpart_a));
+    }
+  }
 #undef XHC_FULL_ROWS
-  }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // token reductions (fixed order)
-  const int64_t nfull = (int64_t)N * C * N;
-  if (dense_rows) {
-    k_colsum_rows_corr<<<dim3((unsigned)((nfull + 255) / 256)), dim3(256), 0, s>>>(
-        wpart_r, nchunk, nfull, mf ? pgsum + pg_floats(N, k, Kr) : nullptr, N, dW_r);
-    k_colsum_rows<<<dim3((unsigned)((nfull + 255) / 256)), dim3(256), 0, s>>>(wpart_p, nchunk, nfull, dW_pre);
-  }
-  // active partials are [chunk][kC][32]: split columns into W_post and W_res
-  if (act_rows) {
-    const int64_t nact = (int64_t)k * C * 32;
-    k_colsum_rows<<<dim3((unsigned)((nact + 255) / 256)), dim3(256), 0, s>>>(wpart_a, nchunk, nact, red_a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = hipMemcpy2DAsync(dW_post, (size_t)k * Kr * sizeof(float), red_a, 32 * sizeof(float),
-                         (size_t)k * Kr * sizeof(float), (size_t)k * C, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return e;
-    e = hipMemcpy2DAsync(dW_res, (size_t)k * k * sizeof(float), red_a + k * Kr, 32 * sizeof(float),
-                         (size_t)k * k * sizeof(float), (size_t)k * C, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return e;
-  }
-  const int npg = pg_floats(N, k, Kr);
-  k_sum_tokens<<<dim3((unsigned)npg), dim3(256), 0, s>>>(pg, T, npg, pgsum);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  e = hipMemcpyAsync(dalpha, pgsum, 3 * sizeof(float), hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(db_pre, pgsum + 3, N * sizeof(float), hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(db_res, pgsum + 3 + N, (size_t)k * k * sizeof(float), hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(db_post, pgsum + 3 + N + k * k, (size_t)k * Kr * sizeof(float), hipMemcpyDeviceToDevice, s);
-  return e;
+  return launch_bwd_pre_reduce(d, &b, 1, s);
 }
 
 #undef XHC_TS_DISPATCH

@@ -130,32 +130,6 @@ __global__ __launch_bounds__(256) void k_fbwd_scatter_act(int64_t T, int N, int 
   }
 }
 
-// Hm[t, i] = 0 for the active streams of token t, Hpre[t, i] otherwise
-__global__ __launch_bounds__(256) void k_fbwd_mask(int64_t T, int N, int k, const int32_t* __restrict__ idx,
-                                                   const float* __restrict__ Hpre, float* __restrict__ Hm) {
-  const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= T * N) return;
-  const int64_t t = u / N;
-  const int i = (int)(u % N);
-  bool act = false;
-  for (int j = 0; j < k; ++j) act = act || idx[t * k + j] == i;
-  Hm[u] = act ? 0.0f : Hpre[u];
-}
-
-__global__ __launch_bounds__(256) void k_fbwd_add(float* __restrict__ dst, const float* __restrict__ src, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] += src[i];
-}
-
-// out = (a0, a1, a2), each from its device scalar or 0 where the pointer is null
-__global__ void k_fbwd_alpha(const float* a0, const float* a1, const float* a2, float* out) {
-  if (threadIdx.x == 0) {
-    out[0] = a0 ? *a0 : 0.0f;
-    out[1] = a1 ? *a1 : 0.0f;
-    out[2] = a2 ? *a2 : 0.0f;
-  }
-}
-
 // da[t, j, :] = da_rev[t, j, :] + Hsel[t, j] din[t, :] (din null: a copy),
 // one workgroup per active row
 template <typename TS>
@@ -223,22 +197,6 @@ hipError_t launch_fbwd_scatter(int state_dtype, int64_t T, int N, int k, int C, 
   }
   XHC_FTS(state_dtype, k_fbwd_scatter<TS><<<dim3((unsigned)(T * N)), dim3(256), 0, s>>>(
                            T, N, k, C, idx, reinterpret_cast<const TS*>(GX), da0, reinterpret_cast<TS*>(dX)));
-  return hipGetLastError();
-}
-
-hipError_t launch_fbwd_mask(int64_t T, int N, int k, const int32_t* idx, const float* Hpre, float* Hm, hipStream_t s) {
-  k_fbwd_mask<<<dim3(blocks_for(T * N, 256)), dim3(256), 0, s>>>(T, N, k, idx, Hpre, Hm);
-  return hipGetLastError();
-}
-
-hipError_t launch_fbwd_add(float* dst, const float* src, int64_t n, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  k_fbwd_add<<<dim3(blocks_for(n, 256)), dim3(256), 0, s>>>(dst, src, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_fbwd_alpha(const float* a0, const float* a1, const float* a2, float* out, hipStream_t s) {
-  k_fbwd_alpha<<<dim3(1), dim3(64), 0, s>>>(a0, a1, a2, out);
   return hipGetLastError();
 }
 

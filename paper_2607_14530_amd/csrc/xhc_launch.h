@@ -135,20 +135,15 @@ hipError_t launch_post_apply(int state_dtype, void* X, const void* F, int64_t T,
 hipError_t launch_bwd_post(const xhc_dims* d, const void* dXn, void* X, const void* Xact, const void* F,
                            const float* conv_w, const int32_t* idx, const float* p, const float* Hres,
                            const float* Hpost, void* dX, void* dF, float* dHres, float* dHpost, float* dp,
-                           float* dconv_w, char* ws, hipStream_t s, bool grad_f32);
+                           float* dconv_w, char* ws, hipStream_t s, bool grad_f32, bool add_dp = false);
 // (X null: the saved rows are not written back into X; grad_f32: dXn and dX
-// are fp32 whatever the state dtype, as the xHC-Flash active-row gradient)
+// are fp32 whatever the state dtype, as the xHC-Flash active-row gradient;
+// add_dp: dp is added to)
 size_t bwd_post_ws_bytes(const xhc_dims* d);
 bool bwd_pre_supported(const xhc_dims* d);
 size_t bwd_pre_ws_bytes(const xhc_dims* d);
-// phases of launch_bwd_pre: kBwdPreAll everything; kBwdPreTokens the
-// per-token part only (the <d input, x_i> partials and the token reverse:
-// the records the row passes read); kBwdPreTokensGiven the same with those
-// partials already in the workspace (launch_bwd_dhpre_multi); kBwdPreReduce
-// the reductions only (the row passes' partials already in the workspace)
-constexpr int kBwdPreAll = 0, kBwdPreTokens = 1, kBwdPreReduce = 2, kBwdPreTokensGiven = 3;
 struct BwdPreWs {
-  float *part, *tok, *pg, *wpart_r, *wpart_p, *wpart_a, *red_a, *pgsum;
+  float *part, *tok, *pg, *wpart_r, *wpart_p, *wpart_a, *corr;
   uint16_t *dzf, *dza;   // packed dz' of the full-row and active-row MFMA passes
   float *srec, *sreca;   // per-token scalars of the ring passes [Tp][8]: full rows, active rows
 };
@@ -182,35 +177,54 @@ struct RowRingDesc {
 bool bwd_rows_ring_supported(int64_t rows, int C, int64_t tchunk);
 hipError_t launch_bwd_rows_ring(const RowRingDesc& d, int64_t rows, hipStream_t s);
 BwdPreWs bwd_pre_ws(const xhc_dims* d, char* ws);   // layout of launch_bwd_pre's workspace
-hipError_t launch_bwd_pre(const xhc_dims* d, const void* X, const float* colsum, const float* W_r,
-                          const float* W_pre, const float* W_res, const float* W_post, const float* alpha,
-                          const float* b_res, const float* saved, const int32_t* idx, const float* p,
-                          const float* Hpre, const float* Hpost, const void* d_input, const float* dHres,
-                          const float* dHpost, const float* dp, void* dX, float* dW_r, float* dW_pre, float* dW_res,
-                          float* dW_post, float* dalpha, float* db_pre, float* db_res, float* db_post, char* ws,
-                          hipStream_t s, const float* dhpre_act = nullptr, const float* Hpre_read = nullptr,
-                          bool dense_rows = true, const void* X_bf16 = nullptr, bool act_rows = true,
-                          int phase = kBwdPreAll, const void* act_din = nullptr);
-// dhpre_act [T,k]: when given, dL/dH^pre of the active streams (slot order)
-// replaces <d input, x_i> there; Hpre_read [T,N]: when given, the weights of
-// the dense-read term dX_i += H^pre_i d input (Hpre otherwise).  dense_rows
-// false leaves out every term of the dense rows (the read H^pre_i d input and
-// the full-state projection through W_r, W_pre): for a caller whose router
-// and pre-map weights are zero; d_input is then not read, H^pre enters as
-// zero gradient, and dW_r, dW_pre are not written.  X_bf16: for an fp32
-// state whose values are exactly bf16 and whose slot j is row j (N = k: the
-// k-row view of an xHC-Flash sublayer), the same rows as bf16 (read by the
-// ring form of the active-row pass; the gradient rows stay fp32), and then
-// act_din (bf16 [T, C]), when given: that pass also adds Hpre[t, j] act_din[t]
-// to active row j (Hpre then holds [T, k] slot weights).  act_rows
-// false leaves out the active-row pass (for a caller whose W_post and W_res
-// are zero): dW_post, dW_res are not written.
+// One pre-map reverse; gradients whose pointer is null are not formed.
+struct BwdPre {
+  const void* X;
+  const float *colsum, *W_r, *W_pre, *W_res, *W_post;   // W_res null: no residual mapping
+  const float *al_pre, *al_res, *al_post;               // device scalars; null: 0
+  const float* b_res;
+  const float* saved;
+  const int32_t* idx;
+  const float *p, *Hpre, *Hpost;
+  const void* d_input;
+  const float* dHres;    // null: no residual mapping
+  const float* dHpost;   // null: no active-row outputs
+  const float* dp;       // null: no router gradient
+  void* dX;
+  float *dW_r, *dW_pre, *dW_res, *dW_post;
+  float *dal_pre, *dal_res, *dal_post;
+  float *db_pre, *db_res, *db_post;
+  char* ws;
+  // [T, k]: dL/dH^pre of the active streams (slot order), in place of <d input, x_i> there
+  const float* dhpre_act;
+  // [T, N], written here when given: Hpre with the active streams zero, the
+  // weights of the dense-read term dX_i += H^pre_i d input (Hpre otherwise)
+  float* hmask;
+  // false leaves out every term of the dense rows (the read and the full-state
+  // projection through W_r, W_pre): d_input, W_r, W_pre and colsum are then
+  // not read (no router: every slot fixed), dW_r and dW_pre not written
+  bool dense_rows = true;
+  bool act_rows = true;    // false leaves out the active-row pass: dW_post, dW_res are not written
+  bool own_rows = true;    // false: launch_bwd_rows_multi runs the row pass
+  // for an fp32 view whose values are exactly bf16 and whose slot j is row j
+  // (N = k: the k-row view of an xHC-Flash sublayer), the same rows as bf16
+  // (read by the ring form of the active-row pass; the gradient rows stay
+  // fp32), and then act_din (bf16 [T, C]), when given: that pass also adds
+  // Hpre[t, j] act_din[t] to active row j (Hpre then holds [T, k] slot weights)
+  const void* X_bf16;
+  const void* act_din;
+};
+hipError_t launch_bwd_pre(const xhc_dims* d, const BwdPre& b, hipStream_t s);
+// its parts around launch_bwd_rows_multi, for n = Q pre-map reverses at once:
+// the token reverses (after launch_bwd_dhpre_multi) and the reductions
+hipError_t launch_bwd_pre_tokens(const xhc_dims* d, const BwdPre* b, int n, hipStream_t s);
+hipError_t launch_bwd_pre_reduce(const xhc_dims* d, const BwdPre* b, int n, hipStream_t s);
 // The full-row pass of Q pre-map reverses of one bf16 state (N = 16, Q = 2 or
 // 4) in one pass: pass q's token records and weight partials live in the
-// launch_bwd_pre workspace ws[q] (after its kBwdPreTokens phase; the router's
+// launch_bwd_pre workspace ws[q] (after launch_bwd_pre_tokens; the router's
 // partials in ws[0]), hrd[q] are its dense-read weights [T, N], d_input is
 // [Q, T, C]; dX accumulates every pass's row terms.
-// prep: a scratch buffer of bwd_rows_multi_ws_bytes (per-token inputs of the
+// pack_ws: a scratch buffer of bwd_rows_multi_ws_bytes (per-token inputs of the
 // fused pass).
 bool bwd_rows_multi_supported(const xhc_dims* d, int Q);
 size_t bwd_rows_multi_ws_bytes(const xhc_dims* d, int Q);
@@ -220,7 +234,7 @@ hipError_t launch_bwd_dhpre_multi(const xhc_dims* d, int Q, const void* X, const
                                   hipStream_t s);
 hipError_t launch_bwd_rows_multi(const xhc_dims* d, int Q, const void* X, void* dX, const float* W_r,
                                  const float* W_pre, const void* d_input, const float* const* hrd, char* const* ws,
-                                 float* prep, hipStream_t s);
+                                 char* pack_ws, hipStream_t s);
 
 // ---- xHC-Flash backward helpers
 hipError_t launch_fill0(void* p, size_t bytes, hipStream_t s);
@@ -231,9 +245,6 @@ hipError_t launch_fbwd_gather(int state_dtype, int64_t T, int N, int k, int C, c
                               float* da, hipStream_t s);
 hipError_t launch_fbwd_scatter(int state_dtype, int64_t T, int N, int k, int C, const int32_t* idx, const void* GX,
                                const float* da0, void* dX, hipStream_t s);
-hipError_t launch_fbwd_mask(int64_t T, int N, int k, const int32_t* idx, const float* Hpre, float* Hm, hipStream_t s);
-hipError_t launch_fbwd_add(float* dst, const float* src, int64_t n, hipStream_t s);
-hipError_t launch_fbwd_alpha(const float* a0, const float* a1, const float* a2, float* out, hipStream_t s);
 hipError_t launch_fbwd_finish(int state_dtype, int64_t T, int k, int C, const float* da_rev, const float* Hsel,
                               const void* din, float* da, hipStream_t s);
 
