@@ -1762,7 +1762,7 @@ __global__ __launch_bounds__(4 * kActRows) __attribute__((amdgpu_waves_per_eu(4)
 // which belong to out and the next w2 to out2.
 struct ColSeg {
   const float* in;
-  int64_t ncols;
+  int64_t nrows, ncols;
   float *out, *out2;
   const float* corr;
   int ncorr, w1, w2;
@@ -1771,7 +1771,7 @@ constexpr int kMaxColSegs = 3 * kMultiMaxQ;
 struct ColSegs {
   ColSeg g[kMaxColSegs];
 };
-__global__ __launch_bounds__(256) void k_colsum_segs(ColSegs sg, int64_t nrows) {
+__global__ __launch_bounds__(256) void k_colsum_segs(ColSegs sg) {
   const ColSeg& g = sg.g[blockIdx.y];
   const int64_t col = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (col >= g.ncols) return;
@@ -1784,10 +1784,10 @@ __global__ __launch_bounds__(256) void k_colsum_segs(ColSegs sg, int64_t nrows) 
     else return;
   }
   float s = 0.f;
-  for (int64_t r0 = 0; r0 < nrows; r0 += 8) {
+  for (int64_t r0 = 0; r0 < g.nrows; r0 += 8) {
     float v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = (r0 + u < nrows) ? g.in[(r0 + u) * g.ncols + col] : 0.f;
+    for (int u = 0; u < 8; ++u) v[u] = (r0 + u < g.nrows) ? g.in[(r0 + u) * g.ncols + col] : 0.f;
 #pragma unroll
     for (int u = 0; u < 8; ++u) s += v[u];
   }
@@ -2016,22 +2016,36 @@ __global__ __launch_bounds__(256) void k_dz_pack_multi(MultiRows m, int64_t T, i
   }
 }
 
-constexpr int64_t kRowChunk = 1024;   // tokens per weight-gradient partial
+// Tokens per weight-gradient partial of a pass over `rows` weight rows (128 a
+// workgroup).  A workgroup walks its chunk in steps of 32 tokens one after the
+// other, so its time is that of its tokens; with fewer workgroups than CUs
+// (the ring pass holds one a CU) shorter chunks finish sooner, down to two
+// steps.  Forward and backward at T = 968, N = 8, C = 256: 282 us with 16 and 8
+// workgroups of 1024 tokens (50 and 53 us of them in the full and the active
+// rows), 200 us with these; T = 512, N = 8, C = 1024: 244 and 211 us.
+static int64_t row_chunk(int64_t T, int64_t rows) {
+  int64_t c = 1024;
+  while (c > 64 && rows / kActRows * ((T + c - 1) / c) < 256) c /= 2;
+  return c;
+}
+static int64_t chunk_full(const xhc_dims* d) { return row_chunk(d->T, (int64_t)d->N * d->C); }
+static int64_t chunk_act(const xhc_dims* d) { return row_chunk(d->T, (int64_t)d->k * d->C); }
+static int64_t nchunks(int64_t T, int64_t chunk) { return (T + chunk - 1) / chunk; }
 
 BwdPreWs bwd_pre_ws(const xhc_dims* d, char* ws) {
   const int64_t T = d->T;
   const int N = d->N, k = d->k, Kr = d->Kr, C = d->C;
   const int NA = k * Kr + k * k;
   const int64_t ncb = post_chunks(C);
-  const int64_t nchunk = (T + kRowChunk - 1) / kRowChunk;
+  const int64_t nf = nchunks(T, chunk_full(d)), na = nchunks(T, chunk_act(d));
   BwdPreWs w;
   w.part = reinterpret_cast<float*>(ws);
   w.tok = w.part + ncb * N * T;
   w.pg = w.tok + T * tok_floats(N, NA);
   w.wpart_r = w.pg + T * (pg_floats(N, k, Kr) + N);
-  w.wpart_p = w.wpart_r + nchunk * (int64_t)N * C * N;
-  w.wpart_a = w.wpart_p + nchunk * (int64_t)N * C * N;
-  w.corr = w.wpart_a + nchunk * (int64_t)k * C * 32;
+  w.wpart_p = w.wpart_r + nf * (int64_t)N * C * N;
+  w.wpart_a = w.wpart_p + nf * (int64_t)N * C * N;
+  w.corr = w.wpart_a + na * (int64_t)k * C * 32;
   // packed dz' (16-byte aligned): full rows 2 NO_f, active rows 2 x 32 bf16 a
   // token, in token rows and in transposed 32-token blocks
   const int64_t Tp = (T + kDzBlock - 1) / kDzBlock * kDzBlock;
@@ -2044,7 +2058,7 @@ BwdPreWs bwd_pre_ws(const xhc_dims* d, char* ws) {
 }
 
 bool bwd_rows_multi_supported(const xhc_dims* d, int Q) {
-  return d->state_dtype == XHC_BF16 && d->N == 16 && bwd_rows_ring_supported((int64_t)d->N * d->C, d->C, kRowChunk) &&
+  return d->state_dtype == XHC_BF16 && d->N == 16 && bwd_rows_ring_supported((int64_t)d->N * d->C, d->C, chunk_full(d)) &&
          (Q == 2 || Q == 4);
 }
 
@@ -2117,7 +2131,7 @@ hipError_t launch_bwd_rows_multi(const xhc_dims* d, int Q, const void* X, void* 
   rd.srec = srec;
   rd.srec_stride = 8;
   rd.T = T;
-  rd.tchunk = kRowChunk;
+  rd.tchunk = chunk_full(d);
   rd.N = N;
   rd.C = C;
   return launch_bwd_rows_ring(rd, (int64_t)N * C, s);
@@ -2127,11 +2141,11 @@ size_t bwd_pre_ws_bytes(const xhc_dims* d) {
   const int64_t T = d->T;
   const int N = d->N, k = d->k, Kr = d->Kr, C = d->C;
   const int NA = k * Kr + k * k;
-  const int64_t nchunk = (T + kRowChunk - 1) / kRowChunk;
+  const int64_t nf = nchunks(T, chunk_full(d)), na = nchunks(T, chunk_act(d));
   size_t n = (size_t)post_chunks(C) * N * T;                    // dH^pre partials
   n += (size_t)T * tok_floats(N, NA) + (size_t)T * (pg_floats(N, k, Kr) + N);
-  n += (size_t)nchunk * N * C * N * 2;                           // dW_r, dW_pre partials
-  n += (size_t)nchunk * k * C * 32;                              // dW_act partials (<= 32 columns)
+  n += (size_t)nf * N * C * N * 2;                               // dW_r, dW_pre partials
+  n += (size_t)na * k * C * 32;                                  // dW_act partials (<= 32 columns)
   n += (size_t)N;                                                // token sum of mu r_ln dz_r
   const size_t Tp = (size_t)((T + kDzBlock - 1) / kDzBlock * kDzBlock);
   const size_t dz = Tp * 2 * ((2 * N <= 32 ? 32 : 64) + 32) * 2 * sizeof(uint16_t);   // packed dz'
@@ -2219,7 +2233,8 @@ hipError_t launch_bwd_pre_reduce(const xhc_dims* d, const BwdPre* bs, int n, hip
   if (n < 1 || n > kMultiMaxQ) return hipErrorInvalidValue;
   const int64_t T = d->T;
   const int N = d->N, k = d->k, Kr = d->Kr, C = d->C;
-  const int64_t nchunk = (T + kRowChunk - 1) / kRowChunk, nfull = (int64_t)N * C * N, nact = (int64_t)k * C * 32;
+  const int64_t nf = nchunks(T, chunk_full(d)), na = nchunks(T, chunk_act(d));
+  const int64_t nfull = (int64_t)N * C * N, nact = (int64_t)k * C * 32;
   TokenSumsMulti ts{};
   ColSegs cs{};
   int ns = 0;
@@ -2234,14 +2249,14 @@ hipError_t launch_bwd_pre_reduce(const xhc_dims* d, const BwdPre* bs, int n, hip
     // (the MFMA row passes leave the token sum of mu r_ln dz_r in dW_r)
     float* const corr = b.dW_r && pre_mf(d) ? w.corr : nullptr;
     ts.a[q] = TokenSums{w.pg, b.dal_pre, b.dal_res, b.dal_post, b.db_pre, b.db_res, b.db_post, corr};
-    if (b.dW_r) seg(ColSeg{w.wpart_r, nfull, b.dW_r, nullptr, corr, N, 0, 0});
-    if (b.dW_pre) seg(ColSeg{w.wpart_p, nfull, b.dW_pre, nullptr, nullptr, 1, 0, 0});
+    if (b.dW_r) seg(ColSeg{w.wpart_r, nf, nfull, b.dW_r, nullptr, corr, N, 0, 0});
+    if (b.dW_pre) seg(ColSeg{w.wpart_p, nf, nfull, b.dW_pre, nullptr, nullptr, 1, 0, 0});
     // active partials are [chunk][kC][32]
-    if (b.dW_post) seg(ColSeg{w.wpart_a, nact, b.dW_post, b.dW_res, nullptr, 1, k * Kr, b.dW_res ? k * k : 0});
+    if (b.dW_post) seg(ColSeg{w.wpart_a, na, nact, b.dW_post, b.dW_res, nullptr, 1, k * Kr, b.dW_res ? k * k : 0});
   }
   k_sum_tokens<<<dim3((unsigned)(pg_floats(N, k, Kr) + N), (unsigned)n), dim3(kSumThreads), 0, s>>>(ts, T, N, k, Kr);
   if (ns > 0)
-    k_colsum_segs<<<dim3((unsigned)((most + 255) / 256), (unsigned)ns), dim3(256), 0, s>>>(cs, nchunk);
+    k_colsum_segs<<<dim3((unsigned)((most + 255) / 256), (unsigned)ns), dim3(256), 0, s>>>(cs);
   return hipGetLastError();
 }
 
@@ -2249,7 +2264,7 @@ hipError_t launch_bwd_pre(const xhc_dims* d, const BwdPre& b, hipStream_t s) {
   const int64_t T = d->T;
   const int N = d->N, k = d->k, Kr = d->Kr, C = d->C;
   const int NA = k * Kr + k * k;
-  const int64_t nchunk = (T + kRowChunk - 1) / kRowChunk;
+  const int64_t cf = chunk_full(d), ca = chunk_act(d);
   const BwdPreWs w = bwd_pre_ws(d, b.ws);
   const void *const X = b.X, *const d_input = b.d_input, *const X_bf16 = b.X_bf16, *const act_din = b.act_din;
   void* const dX = b.dX;
@@ -2294,7 +2309,7 @@ hipError_t launch_bwd_pre(const xhc_dims* d, const BwdPre& b, hipStream_t s) {
       rd.srec = w.srec;
       rd.srec_stride = 8;
       rd.T = T;
-      rd.tchunk = kRowChunk;
+      rd.tchunk = cf;
       rd.N = N;
       rd.C = C;
       e = launch_bwd_rows_ring(rd, (int64_t)N * C, s);
@@ -2302,10 +2317,10 @@ hipError_t launch_bwd_pre(const xhc_dims* d, const BwdPre& b, hipStream_t s) {
     }
     // 128 rows per workgroup (C % 256 == 0); the dense read of the active
     // rows is in the full-row pass
-    const dim3 ga((unsigned)((int64_t)k * C / kActRows), (unsigned)nchunk);
+    const dim3 ga((unsigned)((int64_t)k * C / kActRows), (unsigned)nchunks(T, ca));
     if (act_rows)
       k_bwd_act_rows_mfma<<<ga, dim3(4 * kActRows), 0, s>>>(reinterpret_cast<const uint16_t*>(X),
-          reinterpret_cast<uint16_t*>(dX), W_post, W_res, idx, tok, T, N, k, C, Kr, NA, kRowChunk, w.dza, wpart_a);
+          reinterpret_cast<uint16_t*>(dX), W_post, W_res, idx, tok, T, N, k, C, Kr, NA, ca, w.dza, wpart_a);
   }
   // an fp32 state given with its exact bf16 copy (the k-row view of an
   // xHC-Flash sublayer, N = k, whose slot j is row j): the active rows take
@@ -2334,18 +2349,18 @@ hipError_t launch_bwd_pre(const xhc_dims* d, const BwdPre& b, hipStream_t s) {
     rd.srec = w.sreca;
     rd.srec_stride = 8;
     rd.T = T;
-    rd.tchunk = kRowChunk;
+    rd.tchunk = ca;
     rd.N = N;
     rd.C = C;
     e = launch_bwd_rows_ring(rd, (int64_t)k * C, s);
     if (e != hipSuccess) return e;
   }
-  const dim3 gfull((unsigned)(((int64_t)N * C + 255) / 256), (unsigned)nchunk);
+  const dim3 gfull((unsigned)(((int64_t)N * C + 255) / 256), (unsigned)nchunks(T, cf));
 #define XHC_FULL_ROWS(NNV)                                                                                       \
   XHC_TS_DISPATCH(d->state_dtype,                                                                                \
     k_bwd_full_rows<TS, NNV><<<gfull, dim3(256), 0, s>>>(reinterpret_cast<const TS*>(X),                        \
         reinterpret_cast<const TS*>(d_input), reinterpret_cast<TS*>(dX), W_r, W_pre, Hrd, tok, T, C, NA,         \
-        kRowChunk, wpart_r, wpart_p))
+        cf, wpart_r, wpart_p))
   if (!mf) {
     if (dense_rows) {
       switch (N) {
@@ -2356,10 +2371,10 @@ hipError_t launch_bwd_pre(const xhc_dims* d, const BwdPre& b, hipStream_t s) {
       }
     }
     if (!mfa32 && act_rows) {
-      const dim3 gact((unsigned)(((int64_t)k * C + 255) / 256), (unsigned)nchunk);
+      const dim3 gact((unsigned)(((int64_t)k * C + 255) / 256), (unsigned)nchunks(T, ca));
       XHC_TS_DISPATCH(d->state_dtype,
         k_bwd_act_rows<TS, 32><<<gact, dim3(256), 0, s>>>(reinterpret_cast<const TS*>(X), reinterpret_cast<TS*>(dX),
-            W_post, W_res, idx, tok, T, N, k, C, Kr, kRowChunk, wpart_a));
+            W_post, W_res, idx, tok, T, N, k, C, Kr, ca, wpart_a));
     }
   }
 #undef XHC_FULL_ROWS
