@@ -108,20 +108,18 @@ size_t flash_pre_ws(const xhc_dims* d, int Q) {
   return (full > act ? full : act) + (sf > sa ? sf : sa);
 }
 
-size_t gram_bytes(const xhc_dims* d, int Kq) {
-  const int np = Kq * (Kq + 1) / 2;
-  return align_up((size_t)gram_chunks(d->C, d->S, Kq, d->kappa) * np * (size_t)d->T * sizeof(float)) +
-         align_up((size_t)d->T * d->k * Kq * sizeof(float));
+PostPlan plan_of(const xhc_dims* d, int Kq, size_t avail) {
+  return post_plan(d->T, d->S, d->C, d->k, Kq, d->kappa, avail);
 }
 
+// the projection of the next sublayer's mappings
+size_t flash_next_ws(const xhc_dims* d, int Q, int q) {
+  if (q >= Q) return 0;
+  const int64_t na = act_outs(d, flash_Kq(d, q + 1), q + 1 == Q);
+  return part_bytes(d, true, kC_of(d), na) + sums_bytes(na, d->T);
+}
 size_t flash_post_ws(const xhc_dims* d, int Q, int q) {
-  const int Kq = flash_Kq(d, q);
-  size_t need = Kq > 1 ? gram_bytes(d, Kq) : 0;
-  if (q < Q) {
-    const int64_t na = act_outs(d, flash_Kq(d, q + 1), q + 1 == Q);
-    need = std::max(need, part_bytes(d, true, kC_of(d), na) + sums_bytes(na, d->T));
-  }
-  return need;
+  return std::max(plan_of(d, flash_Kq(d, q), SIZE_MAX).bytes, flash_next_ws(d, Q, q));
 }
 
 // ---- xHC-Flash backward: the per-sublayer reverse runs the single-sublayer
@@ -231,13 +229,6 @@ FlashPreBwdWs flash_pre_bwd_ws(const xhc_dims* d, int Q) {
   return w;
 }
 
-size_t post_ws(const xhc_dims* d) {
-  if (d->Kr == 1) return 0;
-  const int np = d->Kr * (d->Kr + 1) / 2;
-  return align_up((size_t)gram_chunks(d->C, d->S, d->Kr, d->kappa) * np * (size_t)d->T * sizeof(float)) +
-         align_up((size_t)d->T * d->k * d->Kr * sizeof(float));
-}
-
 // xhc_post's work on a given scratch buffer (the caller's workspace, or the
 // library's static one for xhc_post_noalloc)
 xhc_status post_impl(const xhc_dims* d, void* X, const void* F, const float* conv_w, const int32_t* idx,
@@ -251,25 +242,21 @@ xhc_status post_impl(const xhc_dims* d, void* X, const void* F, const float* con
   if (X == F) return XHC_EINVAL;
   if (!aligned16(X) || !aligned16(F) || (conv_w && !aligned16(conv_w)) || (Xact_save && !aligned16(Xact_save)))
     return XHC_EUNSUPPORTED;
-  const size_t need = post_ws(d);
-  if (need > 0 && (!workspace || workspace_bytes < need)) return XHC_EWORKSPACE;
+  const PostPlan plan = plan_of(d, d->Kr, workspace_bytes);
+  if (plan.least > 0 && (!workspace || workspace_bytes < plan.least)) return XHC_EWORKSPACE;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   clear_stale_error();
   float* wb = nullptr;
   const float* gp = nullptr;
   hipError_t e = hipSuccess;
   if (d->Kr > 1) {
-    const int np = d->Kr * (d->Kr + 1) / 2;
     float* gpart = reinterpret_cast<float*>(workspace);
-    wb = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) +
-                                  align_up((size_t)gram_chunks(d->C, d->S, d->Kr, d->kappa) * np * (size_t)d->T *
-                                           sizeof(float)));
+    wb = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + plan.wb_at);
     gp = gpart;
-    XHC_STEP("post_gram", launch_post_gram(d->state_dtype, F, d->T, d->S, d->C, d->Kr, d->kappa, conv_w, gpart, s));
+    XHC_STEP("post_gram", launch_post_gram(plan, d->state_dtype, F, d->T, d->S, d->C, d->Kr, d->kappa, conv_w, gpart, s));
   }
-  XHC_STEP("post_apply", launch_post_apply(d->state_dtype, X, F, d->T, d->S, d->N, d->C, d->k, d->Kr, d->kappa,
-                                           conv_w, idx, p, Hres, Hpost, gp,
-                                           gram_chunks(d->C, d->S, d->Kr, d->kappa), d->gram_schmidt, wb, nullptr,
+  XHC_STEP("post_apply", launch_post_apply(plan, d->state_dtype, X, F, d->T, d->S, d->N, d->C, d->k, d->Kr,
+                                           d->kappa, conv_w, idx, p, Hres, Hpost, gp, d->gram_schmidt, wb, nullptr,
                                            nullptr, nullptr, Xact_save, s));
   return hip_status(e);
 }
@@ -376,7 +363,7 @@ size_t xhc_workspace_bytes(const xhc_dims* d, int32_t op, int32_t Q) {
   if (check_dims(d) != XHC_OK) return 0;
   switch (op) {
     case XHC_OP_PRE: return pre_ws(d);
-    case XHC_OP_POST: return post_ws(d);
+    case XHC_OP_POST: return plan_of(d, d->Kr, SIZE_MAX).bytes;
     case XHC_OP_POST_BWD: return bwd_post_ws_bytes(d);
     case XHC_OP_PRE_BWD: return bwd_pre_supported(d) ? bwd_pre_ws_bytes(d) : 0;
     case XHC_OP_FLASH_PRE: return (Q == 2 || Q == 4) ? flash_pre_ws(d, Q) : 0;
@@ -492,9 +479,10 @@ xhc_status xhc_post_noalloc(const xhc_dims* d, void* X, const void* F, const flo
                             const float* p, const float* Hres, const float* Hpost, void* Xact_save, void* stream) {
   xhc_status st = check_dims(d);
   if (st != XHC_OK) return st;
-  if (post_ws(d) > kNoAllocScratchBytes) return XHC_EWORKSPACE;
+  const size_t least = plan_of(d, d->Kr, kNoAllocScratchBytes).least;
+  if (least > kNoAllocScratchBytes) return XHC_EWORKSPACE;
   void* scr = nullptr;
-  if (post_ws(d) > 0 && d->T > 0) {
+  if (least > 0 && d->T > 0) {
     st = noalloc_scratch(&scr);
     if (st != XHC_OK) return st;
   }
@@ -576,7 +564,8 @@ xhc_status xhc_flash_post(const xhc_dims* d, int32_t Q, int32_t q, void* X, cons
   }
   if (!aligned16(X) || !aligned16(F) || (conv_w && !aligned16(conv_w)) || (Xact_save && !aligned16(Xact_save)))
     return XHC_EUNSUPPORTED;
-  const size_t need = flash_post_ws(d, Q, q);
+  const PostPlan plan = plan_of(d, Kq, workspace_bytes);
+  const size_t need = std::max(plan.least, flash_next_ws(d, Q, q));
   if (need > 0 && (!workspace || workspace_bytes < need)) return XHC_EWORKSPACE;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   clear_stale_error();
@@ -584,17 +573,13 @@ xhc_status xhc_flash_post(const xhc_dims* d, int32_t Q, int32_t q, void* X, cons
   float* wb = nullptr;
   const float* gp = nullptr;
   if (Kq > 1) {
-    const int np = Kq * (Kq + 1) / 2;
     float* gpart = reinterpret_cast<float*>(workspace);
-    wb = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) +
-                                  align_up((size_t)gram_chunks(d->C, d->S, Kq, d->kappa) * np * (size_t)d->T *
-                                           sizeof(float)));
+    wb = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + plan.wb_at);
     gp = gpart;
-    XHC_STEP("flash_post_gram", launch_post_gram(d->state_dtype, F, d->T, d->S, d->C, Kq, d->kappa, conv_w, gpart, s));
+    XHC_STEP("flash_post_gram", launch_post_gram(plan, d->state_dtype, F, d->T, d->S, d->C, Kq, d->kappa, conv_w, gpart, s));
   }
-  XHC_STEP("flash_post_apply", launch_post_apply(d->state_dtype, X, F, d->T, d->S, d->N, d->C, d->k, Kq, d->kappa,
-                                                 conv_w, idx, p, Hres, Hpost, gp,
-                                                 gram_chunks(d->C, d->S, Kq, d->kappa), d->gram_schmidt, wb,
+  XHC_STEP("flash_post_apply", launch_post_apply(plan, d->state_dtype, X, F, d->T, d->S, d->N, d->C, d->k, Kq,
+                                                 d->kappa, conv_w, idx, p, Hres, Hpost, gp, d->gram_schmidt, wb,
                                                  last ? nullptr : Hpre_next,
                                                  last ? nullptr : base_next, last ? nullptr : input_next, Xact_save,
                                                  s));

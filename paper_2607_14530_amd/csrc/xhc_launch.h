@@ -116,20 +116,28 @@ hipError_t launch_pre_fused(const xhc_dims* d, const void* X, const void* packed
 
 // ---- post
 __host__ __device__ inline int64_t post_chunks(int C) { return ((int64_t)C / 8 + 255) / 256; }
-// Gram partial chunks written by launch_post_gram (run-based kernels use 1024-channel chunks)
-int64_t gram_chunks(int C, int64_t S, int Kr, const int32_t* kappa);
-hipError_t launch_post_gram(int state_dtype, const void* F, int64_t T, int64_t S, int C, int Kr,
+// How a post with these sizes runs in a workspace of `avail` bytes: run-based
+// kernels or per-token ones, the Gram partials' chunks, and where the per-token
+// write-back weights lie behind them.  bytes: what the workspace query says;
+// least: what has to be there.
+struct PostPlan {
+  bool gram_run, apply_run;
+  int64_t nchunk;
+  size_t bytes, least, wb_at;
+};
+PostPlan post_plan(int64_t T, int64_t S, int C, int k, int Kr, const int32_t* kappa, size_t avail);
+hipError_t launch_post_gram(const PostPlan& plan, int state_dtype, const void* F, int64_t T, int64_t S, int C, int Kr,
                             const int32_t* kappa, const float* conv_w, float* gpart, hipStream_t s);
 // The write-back of the k active rows.  For K_r > 1 gpart holds the Gram
-// partials of launch_post_gram (nchunk chunks): the write-back weights are then
-// formed from them (Gram-Schmidt, p, H^post) inside the run-based kernel, or
-// into the workspace wb by a per-token pass before the generic one.  K_r = 1:
-// gpart and wb are null.
-hipError_t launch_post_apply(int state_dtype, void* X, const void* F, int64_t T, int64_t S, int N, int C,
-                             int k, int Kr, const int32_t* kappa, const float* conv_w, const int32_t* idx,
+// partials of launch_post_gram: the write-back weights are then formed from
+// them (Gram-Schmidt, p, H^post) inside the run-based kernel, or into the
+// workspace wb by a per-token pass before the generic one.  K_r = 1: gpart and
+// wb are null.
+hipError_t launch_post_apply(const PostPlan& plan, int state_dtype, void* X, const void* F, int64_t T, int64_t S, int N,
+                             int C, int k, int Kr, const int32_t* kappa, const float* conv_w, const int32_t* idx,
                              const float* p, const float* Hres, const float* Hpost, const float* gpart,
-                             int64_t nchunk, int gram_schmidt, float* wb, const float* Hpre_next,
-                             const void* base_next, void* input_next, void* Xact_save, hipStream_t s);
+                             int gram_schmidt, float* wb, const float* Hpre_next, const void* base_next,
+                             void* input_next, void* Xact_save, hipStream_t s);
 
 // ---- backward
 hipError_t launch_bwd_post(const xhc_dims* d, const void* dXn, void* X, const void* Xact, const void* F,

@@ -121,30 +121,47 @@ __global__ __launch_bounds__(128) void k_post_coef(const float* __restrict__ gpa
 
 // ------------------------------------------------------------------ run-based MLP-type kernels
 // For compile-time kernel sizes (K1, K2, K3) = (4, 8, 12): a thread owns 4
-// channels and walks a run of kRun consecutive tokens in groups of G, keeping
-// the conv taps of its channels and the last 12 values of F in registers, so F
-// is read once per kernel and the taps once per run.  Sequence starts fall on
-// group starts (S % G == 0), where the history is cleared.
+// channels and walks a run of up to kRun consecutive tokens of one sequence in
+// groups of G, keeping the conv taps of its channels and the last 12 values of
+// F in registers, so F is read once per kernel and the taps once per run.  The
+// runs cut each sequence from its start, so none crosses a sequence start; the
+// last group of a run may be short.  RAGGED: it may, or the width is no multiple
+// of a workgroup's channels and the threads past it work on zeros (instances
+// of their own, so that the others carry no trace of it).
 
 constexpr int kRun = 64;   // tokens of a run, at most
+
+// the runs of a launch: run b takes tokens t0 .. t0 + nt of sequence b / rps
+struct Runs {
+  int64_t T, S, rps;
+  int rl;
+  __device__ __forceinline__ int64_t first(int64_t b) const { return b / rps * S + b % rps * rl; }
+  __device__ __forceinline__ int count(int64_t b) const {
+    const int64_t t0 = first(b), next = (b / rps + 1) * S, end = next < T ? next : T;
+    return (int)(end - t0 < rl ? end - t0 : rl);   // (<= 0: past the last, partial sequence)
+  }
+};
 
 // Tokens per run.  A run's workgroup walks its tokens one group after the
 // other, so its time is about that of its tokens in sequence; with fewer
 // workgroups than the chip holds (two per CU at these register counts, 512)
 // shorter runs finish sooner, until the set-up (24 taps and 12 rows of
 // history a channel) is as long as the walk: 4 tokens, one group.
-static int run_len(int64_t T, int64_t chunks) {
+static Runs make_runs(int64_t T, int64_t S, int64_t chunks, int64_t* nruns) {
+  const int64_t len = S < T ? S : T, nseq = (T + len - 1) / len;
   int rl = kRun;
-  while (rl > 4 && (T + rl - 1) / rl * chunks < 512) rl /= 2;
-  return rl;
+  while (rl > 4 && nseq * ((len + rl - 1) / rl) * chunks < 512) rl /= 2;
+  const Runs r{T, len, (len + rl - 1) / rl, rl};
+  *nruns = nseq * r.rps;
+  return r;
 }
 
-// Gram partials per 1024-channel chunk.  Each lane forms its 4-channel
+// Gram partials per workgroup's channels.  Each lane forms its 4-channel
 // products for G tokens; a wave sums them over its 64 lanes through an LDS
 // transpose (lane v adds column v), and the waves' sums are added at the end.
-template <typename TS, int K1, int K2, int K3>
-__global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F, int64_t T, int64_t S, int C,
-                                                       const float* __restrict__ conv_w, int rl,
+template <typename TS, int K1, int K2, int K3, bool RAGGED>
+__global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F, Runs runs, int C,
+                                                       const float* __restrict__ conv_w,
                                                        float* __restrict__ gpart) {
   using CG = ConvGroup<K1, K2, K3>;
   constexpr int KR = CG::KR, NP = KR * (KR + 1) / 2;
@@ -155,12 +172,16 @@ __global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F,
   const int nw = blockDim.x / kWave;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int64_t cb = blockIdx.y;
-  const int c = (int)(cb * blockDim.x + threadIdx.x) * 4;
-  const int64_t t0 = (int64_t)blockIdx.x * rl;
-  const int nt = (int)((T - t0 < rl) ? T - t0 : rl);
+  const int64_t T = runs.T, t0 = runs.first(blockIdx.x);
+  const int nt = runs.count(blockIdx.x);
+  if (nt <= 0) return;
+  int c = (int)(cb * blockDim.x + threadIdx.x) * 4;
+  const bool past = RAGGED && c >= C;   // (reads the last channels, counts as zeros)
+  if (past) c = C - 4;
   CG cg;
   cg.load_taps(conv_w, C, c);
-  cg.init(F, t0, S, C, c);
+  cg.init(F, t0, runs.S, C, c);
+  if (past) cg.reset();
   float* mine = &xpose[wave][lane][0];
   // F rows are loaded PF groups ahead (a lane requests 8 bytes per token of a
   // bf16 state, so one group in flight would leave the memory system mostly
@@ -179,11 +200,12 @@ __global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F,
     for (int f = 0; f < PF; ++f) {
       const int u0 = u1 + f * G;
       if (u0 >= nt) break;
-      const int64_t t = t0 + u0;
-      if (t % S == 0) cg.reset();
       float cur[G][4];
 #pragma unroll
-      for (int g = 0; g < G; ++g) Row4<TS>::unpack(ring[f][g], cur[g]);
+      for (int g = 0; g < G; ++g) {
+        Row4<TS>::unpack(ring[f][g], cur[g]);
+        if (past) cur[g][0] = cur[g][1] = cur[g][2] = cur[g][3] = 0.f;
+      }
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const int u = u0 + PF * G + g;
@@ -241,10 +263,10 @@ __global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F,
 // (without H^res: Y_j = a_j + ...); SAVE keeps the rows read, NEXT forms the
 // next sublayer's input.  The run's indices and coefficients are staged in LDS
 // once, the write-back weights wb formed there from the Gram partials; the
-// loads of a group of G tokens are issued together.  T is a multiple of G.
-template <typename TS, int KK, int G, bool RES, bool SAVE, bool NEXT>
-__global__ __launch_bounds__(256) void k_post_apply_run(TS* __restrict__ X, const TS* __restrict__ F, int64_t T,
-                                                        int64_t S, int N, int C, int rl,
+// loads of a group of G tokens are issued together.
+template <typename TS, int KK, int G, bool RES, bool SAVE, bool NEXT, bool RAGGED>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_post_apply_run(TS* __restrict__ X, const TS* __restrict__ F, Runs runs,
+                                                        int N, int C,
                                                         const float* __restrict__ conv_w,
                                                         const int32_t* __restrict__ idx,
                                                         const float* __restrict__ Hres,
@@ -261,9 +283,12 @@ __global__ __launch_bounds__(256) void k_post_apply_run(TS* __restrict__ X, cons
   __shared__ __align__(16) float s_wb[kRun * KK * KR];
   __shared__ int32_t s_idx[kRun * KK];
   __shared__ float s_hn[NEXT ? kRun * kMaxN : 1];
-  const int c = (int)(blockIdx.y * blockDim.x + threadIdx.x) * 4;
-  const int64_t t0 = (int64_t)blockIdx.x * rl;
-  const int nt = (int)((T - t0 < rl) ? T - t0 : rl);
+  const int64_t T = runs.T, t0 = runs.first(blockIdx.x);
+  const int nt = runs.count(blockIdx.x);
+  if (nt <= 0) return;
+  int c = (int)(blockIdx.y * blockDim.x + threadIdx.x) * 4;
+  const bool past = RAGGED && c >= C;
+  if (past) c = C - 4;
   for (int i = threadIdx.x; i < nt * KK; i += blockDim.x) s_idx[i] = idx[t0 * KK + i];
   // write-back weights of the run's tokens from their Gram partials (the same
   // per-token arithmetic as k_post_coef; every channel chunk of a run forms them)
@@ -275,29 +300,36 @@ __global__ __launch_bounds__(256) void k_post_apply_run(TS* __restrict__ X, cons
     for (int i = threadIdx.x; i < nt * N; i += blockDim.x) s_hn[i] = Hpre_next[t0 * N + i];
   CG cg;
   cg.load_taps(conv_w, C, c);
-  cg.init(F, t0, S, C, c);
+  cg.init(F, t0, runs.S, C, c);
   __syncthreads();
+  if (past) return;
   for (int u0 = 0; u0 < nt; u0 += G) {
-    const int64_t t = t0 + u0;
-    if (t % S == 0) cg.reset();
+    // (changes nothing, init has cleared it, but ends the scheduler's region:
+    // without it the write-back spilled or took one wave a SIMD, 478 us
+    // against 336 at T = 16384 C = 4096)
+    if (!RAGGED && (t0 + u0) % runs.S == 0) cg.reset();
     int32_t rows[G][KK];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int l = 0; l < KK; ++l) rows[g][l] = __builtin_amdgcn_readfirstlane(s_idx[(u0 + g) * KK + l]);
     float cur[G][4];
     typename R::raw a[G][KK], nb[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      R::unpack(R::load(F + (t + g) * C + c), cur[g]);
+      const int u = !RAGGED || u0 + g < nt ? u0 + g : nt - 1;
 #pragma unroll
-      for (int l = 0; l < KK; ++l) a[g][l] = R::load(X + ((t + g) * N + rows[g][l]) * (int64_t)C + c);
-      if (NEXT) nb[g] = R::load(base_next + (t + g) * C + c);
+      for (int l = 0; l < KK; ++l) rows[g][l] = __builtin_amdgcn_readfirstlane(s_idx[u * KK + l]);
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
+      const int64_t tg = t0 + (!RAGGED || u0 + g < nt ? u0 + g : nt - 1);
+      R::unpack(R::load(F + tg * C + c), cur[g]);
+#pragma unroll
+      for (int l = 0; l < KK; ++l) a[g][l] = R::load(X + (tg * N + rows[g][l]) * (int64_t)C + c);
+      if (NEXT) nb[g] = R::load(base_next + tg * C + c);
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (RAGGED && u0 + g >= nt) break;   // (past the run: read its last token)
       const int u = u0 + g;
-      const int64_t tg = t + g;
+      const int64_t tg = t0 + u;
       float e[KR][4];
       cg.components(cur, g, e);
       if (SAVE) {
@@ -347,32 +379,66 @@ __global__ __launch_bounds__(256) void k_post_apply_run(TS* __restrict__ X, cons
   }
 }
 
-// threads per block of the run-based kernels for width C (4 channels each)
-static inline int run_threads(int C) { return C >= 1024 ? 256 : C / 4; }
-static inline bool run_ok(int C, int64_t S, int Kr, const int32_t* kappa) {
-  if (Kr != 4 || kappa[0] != 4 || kappa[1] != 8 || kappa[2] != 12) return false;
-  if (C % 4 != 0 || S % 4 != 0) return false;
-  const int nthr = run_threads(C);
-  return nthr % kWave == 0 && C % (nthr * 4) == 0;
+// Threads per workgroup of the run-based kernels for width C (4 channels
+// each): the count with the fewest threads past the width, the largest of
+// equals (2112: 3 x 192 threads, 2560: 5 x 128, 4096: 4 x 256).
+static int run_threads(int C) {
+  int best = 0, waste = 0;
+  for (int n = 256; n >= kWave; n -= kWave) {
+    const int over = (C + 4 * n - 1) / (4 * n) * 4 * n - C;
+    if (!best || over < waste) best = n, waste = over;
+  }
+  return best;
+}
+static int64_t run_chunks(int C) { return (C + 4 * run_threads(C) - 1) / (4 * run_threads(C)); }
+static bool paper_branches(int Kr, const int32_t* kappa) {
+  return Kr == 4 && kappa[0] == 4 && kappa[1] == 8 && kappa[2] == 12;
+}
+static size_t gram_floats(int64_t chunks, int Kr, int64_t T) { return (size_t)chunks * (Kr * (Kr + 1) / 2) * T; }
+static size_t bytes256(size_t floats) { return (floats * sizeof(float) + 255) / 256 * 256; }
+
+// The run kernels serve the paper's branches at k = 2, 4 and 8, any width and
+// sequence length: at T = 6164, S = 1541, N = 8, C = 2112 a Flash group's four
+// write-backs take 984 us with the per-token kernels, whose every token reads
+// 12 rows of F and 24 rows of taps, and 581 us with these.  The other k keep the
+// per-token write-back, with the run Gram where its partials fit what they need.
+// Where the caller's workspace (or the fixed scratch) holds the per-token
+// kernels' partials and not these, the per-token kernels run.
+PostPlan post_plan(int64_t T, int64_t S, int C, int k, int Kr, const int32_t* kappa, size_t avail) {
+  PostPlan p{};
+  if (Kr == 1) return p;
+  const bool even = C % 1024 == 0 || C == 256 || C == 512 || C == 768;   // whole workgroups
+  const bool exact = paper_branches(Kr, kappa) && even && S % 4 == 0;
+  const bool run = paper_branches(Kr, kappa) && C % 4 == 0 && (k == 2 || k == 4 || k == 8);
+  const size_t wb = bytes256((size_t)T * k * Kr);
+  const size_t per_run = bytes256(gram_floats(run_chunks(C), Kr, T));
+  const size_t per_token = bytes256(gram_floats(post_chunks(C), Kr, T));
+  p.least = (exact ? per_run : per_token) + wb;
+  p.bytes = run && per_run > p.least ? per_run : p.least;
+  p.apply_run = run && per_run <= avail;
+  p.gram_run = p.apply_run || exact;
+  p.nchunk = p.gram_run ? run_chunks(C) : post_chunks(C);
+  p.wb_at = p.gram_run ? per_run : per_token;
+  return p;
 }
 
-int64_t gram_chunks(int C, int64_t S, int Kr, const int32_t* kappa) {
-  if (run_ok(C, S, Kr, kappa)) return C / (run_threads(C) * 4);
-  return post_chunks(C);
-}
-
-hipError_t launch_post_gram(int state_dtype, const void* F, int64_t T, int64_t S, int C, int Kr,
+hipError_t launch_post_gram(const PostPlan& plan, int state_dtype, const void* F, int64_t T, int64_t S, int C, int Kr,
                             const int32_t* kappa, const float* conv_w, float* gpart, hipStream_t s) {
   if (T == 0) return hipSuccess;
-  if (run_ok(C, S, Kr, kappa)) {
-    const int nthr = run_threads(C), rl = run_len(T, C / (nthr * 4));
-    const dim3 grid((unsigned)((T + rl - 1) / rl), (unsigned)(C / (nthr * 4)));
-    if (state_dtype == XHC_BF16)
-      k_post_gram_run<uint16_t, 4, 8, 12><<<grid, dim3(nthr), 0, s>>>(reinterpret_cast<const uint16_t*>(F), T, S, C,
-                                                                      conv_w, rl, gpart);
-    else
-      k_post_gram_run<float, 4, 8, 12><<<grid, dim3(nthr), 0, s>>>(reinterpret_cast<const float*>(F), T, S, C,
-                                                                   conv_w, rl, gpart);
+  if (plan.gram_run) {
+    int64_t nruns = 0;
+    const Runs runs = make_runs(T, S, plan.nchunk, &nruns);
+    const int nthr = run_threads(C);
+    const dim3 grid((unsigned)nruns, (unsigned)plan.nchunk);
+#define XHC_GRAM_RUN(TS, RAG) \
+  k_post_gram_run<TS, 4, 8, 12, RAG><<<grid, dim3(nthr), 0, s>>>(reinterpret_cast<const TS*>(F), runs, C, conv_w, gpart)
+    const bool ragged = C % (4 * nthr) != 0;
+    if (state_dtype == XHC_BF16) {
+      if (ragged) XHC_GRAM_RUN(uint16_t, true); else XHC_GRAM_RUN(uint16_t, false);
+    } else {
+      if (ragged) XHC_GRAM_RUN(float, true); else XHC_GRAM_RUN(float, false);
+    }
+#undef XHC_GRAM_RUN
     return hipGetLastError();
   }
   const dim3 grid((unsigned)(T * post_chunks(C)));
@@ -477,31 +543,44 @@ __global__ __launch_bounds__(256) void k_post_apply(TS* __restrict__ X, const TS
   if (input_next) Vec8<TS>::store(input_next + t * C + c, nxt);
 }
 
-hipError_t launch_post_apply(int state_dtype, void* X, const void* F, int64_t T, int64_t S, int N, int C, int k,
-                             int Kr, const int32_t* kappa, const float* conv_w, const int32_t* idx, const float* p,
-                             const float* Hres, const float* Hpost, const float* gpart, int64_t nchunk,
+hipError_t launch_post_apply(const PostPlan& plan, int state_dtype, void* X, const void* F, int64_t T, int64_t S, int N,
+                             int C, int k, int Kr, const int32_t* kappa, const float* conv_w, const int32_t* idx,
+                             const float* p, const float* Hres, const float* Hpost, const float* gpart,
                              int gram_schmidt, float* wb, const float* Hpre_next, const void* base_next,
                              void* input_next, void* Xact_save, hipStream_t s) {
   if (T == 0) return hipSuccess;
-  if (gpart && run_ok(C, S, Kr, kappa) && T % 4 == 0 && (k == 4 || k == 8) &&
-      !(Hres && input_next) && !(Xact_save && (input_next || !Hres))) {
-    const int nthr = run_threads(C), rl = run_len(T, C / (nthr * 4));
-    const dim3 grid((unsigned)((T + rl - 1) / rl), (unsigned)(C / (nthr * 4)));
-#define XHC_APPLY_RUN(TS, KK, G, RES, SAVE, NEXT)                                                                  \
-  k_post_apply_run<TS, KK, G, RES, SAVE, NEXT><<<grid, dim3(nthr), 0, s>>>(                                      \
-      reinterpret_cast<TS*>(X), reinterpret_cast<const TS*>(F), T, S, N, C, rl, conv_w, idx, Hres, gpart, nchunk, \
-      gram_schmidt, p, Hpost, Hpre_next,                                                                         \
-      reinterpret_cast<const TS*>(base_next), reinterpret_cast<TS*>(input_next), reinterpret_cast<TS*>(Xact_save))
-#define XHC_APPLY_MODES(TS, KK, G)                                              \
-  do {                                                                          \
-    if (input_next) XHC_APPLY_RUN(TS, KK, G, false, false, true);               \
-    else if (Xact_save) XHC_APPLY_RUN(TS, KK, G, true, true, false);            \
-    else XHC_APPLY_RUN(TS, KK, G, true, false, false);                          \
+  const int64_t nchunk = plan.nchunk;
+  if (plan.apply_run && (Hres != nullptr) != (input_next != nullptr)) {
+    int64_t nruns = 0;
+    const Runs runs = make_runs(T, S, nchunk, &nruns);
+    const int nthr = run_threads(C);
+    const dim3 grid((unsigned)nruns, (unsigned)nchunk);
+#define XHC_APPLY_RUN(TS, KK, G, RES, SAVE, NEXT, RAG)                                                            \
+  k_post_apply_run<TS, KK, G, RES, SAVE, NEXT, RAG><<<grid, dim3(nthr), 0, s>>>(                                \
+      reinterpret_cast<TS*>(X), reinterpret_cast<const TS*>(F), runs, N, C, conv_w, idx, Hres, gpart, nchunk,     \
+      gram_schmidt, p, Hpost, Hpre_next, reinterpret_cast<const TS*>(base_next),                                 \
+      reinterpret_cast<TS*>(input_next), reinterpret_cast<TS*>(Xact_save))
+#define XHC_APPLY_MODES(TS, KK, G, RAG)                                                     \
+  do {                                                                                       \
+    if (input_next && Xact_save) XHC_APPLY_RUN(TS, KK, G, false, true, true, RAG);          \
+    else if (input_next) XHC_APPLY_RUN(TS, KK, G, false, false, true, RAG);                 \
+    else if (Xact_save) XHC_APPLY_RUN(TS, KK, G, true, true, false, RAG);                   \
+    else XHC_APPLY_RUN(TS, KK, G, true, false, false, RAG);                                 \
   } while (0)
+    const bool ragged = C % (4 * nthr) != 0 || runs.S % 4 != 0;   // (runs are 4 tokens and up)
+    // (k = 2 has the ragged instance alone)
     if (state_dtype == XHC_BF16) {
-      if (k == 4) XHC_APPLY_MODES(uint16_t, 4, 4); else XHC_APPLY_MODES(uint16_t, 8, 2);
+      if (k == 2) XHC_APPLY_MODES(uint16_t, 2, 4, true);
+      else if (k == 8 && ragged) XHC_APPLY_MODES(uint16_t, 8, 2, true);
+      else if (k == 8) XHC_APPLY_MODES(uint16_t, 8, 2, false);
+      else if (ragged) XHC_APPLY_MODES(uint16_t, 4, 4, true);
+      else XHC_APPLY_MODES(uint16_t, 4, 4, false);
     } else {
-      if (k == 4) XHC_APPLY_MODES(float, 4, 2); else XHC_APPLY_MODES(float, 8, 1);
+      if (k == 2) XHC_APPLY_MODES(float, 2, 4, true);
+      else if (k == 8 && ragged) XHC_APPLY_MODES(float, 8, 1, true);
+      else if (k == 8) XHC_APPLY_MODES(float, 8, 1, false);
+      else if (ragged) XHC_APPLY_MODES(float, 4, 2, true);
+      else XHC_APPLY_MODES(float, 4, 2, false);
     }
 #undef XHC_APPLY_MODES
 #undef XHC_APPLY_RUN
