@@ -64,7 +64,16 @@ inline ProjPlan proj_plan(int state_dtype, bool gather, int64_t K, int C, int64_
   while (tg > 1 && ((T + 16 * tg - 1) / (16 * tg) < 128 || NO * tg > 160)) tg /= 2;
   const int64_t wt = wide_tokens((int)out_blocks(nout));
   const int64_t tiles = wide ? (T + wt - 1) / wt : (T + 16 * tg - 1) / (16 * tg);
-  const int64_t gran = 32;                                      // chunk granularity in k-blocks
+  // chunk granularity in k-blocks: 8 steps of the wide path, and 4 or 2 while
+  // that still gives each CU one workgroup at most: a step is a round trip to
+  // memory, so a workgroup's time is that of its steps (dense T = 2164 C = 128
+  // 57 -> 43 us, Flash steps T = 380 C = 4096 71 -> 57 us; but T = 4782 N = 16 C =
+  // 448 with 266 workgroups instead of 133 69 -> 76 us).  Not past 128 chunks, whose
+  // sum then costs more than the steps saved (pre T = 9 N = 32 C = 2560 with 320
+  // chunks instead of 80: 69 -> 73 us).
+  const auto at_gran = [&](int64_t g) { return (nblk + g - 1) / g; };
+  int64_t gran = 32;
+  while (wide && gran > 8 && at_gran(gran) <= 64 && tiles * at_gran(gran / 2) <= 256) gran /= 2;
   // chunks for about 1024 workgroups, 512 for five or more output blocks and
   // 256 for the gathered active rows (longer chunks, fewer weight fills and
   // pipeline starts per byte: measured faster there)

@@ -82,12 +82,12 @@ __global__ __launch_bounds__(256) void k_sum_chunks(const float* __restrict__ pa
   if (i >= (int64_t)NO * T) return;
   const int64_t stride = (int64_t)NO * T;
   float s = 0.f;
-  for (int64_t c0 = 0; c0 < nchunk; c0 += 8) {
-    float v[8];
+  for (int64_t c0 = 0; c0 < nchunk; c0 += 16) {
+    float v[16];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = (c0 + u < nchunk) ? part[(c0 + u) * stride + i] : 0.f;
+    for (int u = 0; u < 16; ++u) v[u] = (c0 + u < nchunk) ? part[(c0 + u) * stride + i] : 0.f;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) s += v[u];
+    for (int u = 0; u < 16; ++u) s += v[u];
   }
   sums[i] = s;
 }
