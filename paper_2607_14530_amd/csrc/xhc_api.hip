@@ -76,11 +76,29 @@ size_t sums_bytes(int64_t nout, int64_t T) { return align_up((size_t)(out_blocks
 // waits that gave up (xhc_pre_failures); both paths clear it.
 constexpr size_t kPreErrBytes = 256;
 
+// Every stream active and fixed (a dense sublayer): one projection pass over
+// the state serves both mappings, which saves the second read of it (T =
+// 16384, N = 4, C = 4096: 583 -> 485 us for the whole sublayer).  The coefficient pass
+// reads the summed outputs, so it is the one for k = 2 or 4; the two packed
+// layouts agree for a bf16 state and C % 128 == 0.
+bool pre_one_projection(const xhc_dims* d) {
+  return d->k == d->N && d->m == d->k && (d->k == 2 || d->k == 4) && full_grouped(d->state_dtype, NC_of(d)) &&
+         act_grouped(d->state_dtype, d->C) && out_blocks(2 * d->N) + out_blocks(act_outs(d, d->Kr, 1)) <= 8;
+}
+// outputs of that pass, in whole blocks of 16
+int64_t both_outs(const xhc_dims* d) {
+  return 16 * (out_blocks(2 * d->N) + out_blocks(act_outs(d, d->Kr, 1)));
+}
+// partials of the larger projection (or of both in one), then the sums
+size_t pre_part_bytes(const xhc_dims* d) {
+  if (pre_one_projection(d)) return part_bytes(d, false, NC_of(d), both_outs(d));
+  return std::max(part_bytes(d, false, NC_of(d), 2 * d->N), part_bytes(d, true, kC_of(d), act_outs(d, d->Kr, 1)));
+}
 size_t pre_ws_multi(const xhc_dims* d) {
-  const size_t full = part_bytes(d, false, NC_of(d), 2 * d->N);
-  const size_t act = part_bytes(d, true, kC_of(d), act_outs(d, d->Kr, 1));
-  const size_t sf = sums_bytes(2 * d->N, d->T), sa = sums_bytes(act_outs(d, d->Kr, 1), d->T);
-  return kPreErrBytes + (full > act ? full : act) + (sf > sa ? sf : sa);
+  const size_t sums = pre_one_projection(d)
+                          ? sums_bytes(both_outs(d), d->T)
+                          : std::max(sums_bytes(2 * d->N, d->T), sums_bytes(act_outs(d, d->Kr, 1), d->T));
+  return kPreErrBytes + pre_part_bytes(d) + sums;
 }
 
 // The single-pass path may fall back to the multi-kernel path at run time
@@ -416,9 +434,7 @@ xhc_status xhc_pre(const xhc_dims* d, const void* X, const void* packed_full, co
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   clear_stale_error();
   float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + kPreErrBytes);
-  const size_t part_max = std::max(part_bytes(d, false, NC_of(d), 2 * d->N),
-                                   part_bytes(d, true, kC_of(d), act_outs(d, d->Kr, 1)));
-  float* sums = reinterpret_cast<float*>(reinterpret_cast<char*>(part) + part_max);
+  float* sums = reinterpret_cast<float*>(reinterpret_cast<char*>(part) + pre_part_bytes(d));
   const int64_t NC = NC_of(d), kC = kC_of(d);
   const int64_t nout_full = 2 * d->N, nout_act = act_outs(d, d->Kr, 1);
   const int nsave = saved_floats(d->N, d->k, d->Kr);
@@ -437,17 +453,30 @@ xhc_status xhc_pre(const xhc_dims* d, const void* X, const void* packed_full, co
     clear_stale_error();
   }
   XHC_STEP("pre_clear", launch_fill0(workspace, kPreErrBytes, s));   // no waits here: no failures
-  XHC_STEP("proj_full", launch_proj_partial(d->state_dtype, X, d->T, d->N, d->C, NC, packed_full, nout_full,
-                                            nullptr, d->k, part, s));
-  XHC_STEP("pre_route", launch_pre_route(part, proj_chunks(d->state_dtype, false, NC, d->C, nout_full, d->T), nout_full, d->T, d->N, d->m, d->k, 1, d->C, colsum,
-                                         alpha, 1, b_pre, d->eps, idx, p, Hpre, sums, saved, nsave,
-                                         nsave - 4, d->router, s));
-  XHC_STEP("proj_active", launch_proj_partial(d->state_dtype, X, d->T, d->N, d->C, kC, packed_act, nout_act, idx,
-                                              d->k, part, s));
-  XHC_STEP("pre_coef", launch_pre_coef(part, proj_chunks(d->state_dtype, true, kC, d->C, nout_act, d->T), nout_act,
-                                       d->T, d->k, d->Kr, 1, d->C, alpha + 2, alpha + 1, b_post, b_res, d->eps,
-                                       d->sinkhorn_iters, d->clamp_delta, Hpost, Hres, sums, saved, nsave, 2 * d->N,
-                                       nsave - 2, s));
+  const bool both = pre_one_projection(d);
+  const int64_t nfirst = both ? both_outs(d) : nout_full;   // outputs of the first pass
+  if (both)
+    XHC_STEP("proj_both", launch_proj_both(X, d->T, d->N, d->C, packed_full, nout_full, packed_act, nout_act, part, s));
+  else
+    XHC_STEP("proj_full", launch_proj_partial(d->state_dtype, X, d->T, d->N, d->C, NC, packed_full, nout_full,
+                                              nullptr, d->k, part, s));
+  XHC_STEP("pre_route", launch_pre_route(part, proj_chunks(d->state_dtype, false, NC, d->C, nfirst, d->T), nfirst, d->T,
+                                         d->N, d->m, d->k, 1, d->C, colsum, alpha, 1, b_pre, d->eps, idx, p, Hpre,
+                                         sums, saved, nsave, nsave - 4, d->router, s));
+  // the active outputs' partials: the sums of the first pass behind its own
+  // outputs (one chunk, the moments last in both), or a pass of their own
+  const float* apart = part;
+  int64_t achunks = 1;
+  if (both) {
+    apart = sums + 16 * out_blocks(nout_full) * d->T;
+  } else {
+    XHC_STEP("proj_active", launch_proj_partial(d->state_dtype, X, d->T, d->N, d->C, kC, packed_act, nout_act, idx,
+                                                d->k, part, s));
+    achunks = proj_chunks(d->state_dtype, true, kC, d->C, nout_act, d->T);
+  }
+  XHC_STEP("pre_coef", launch_pre_coef(apart, achunks, nout_act, d->T, d->k, d->Kr, 1, d->C, alpha + 2, alpha + 1,
+                                       b_post, b_res, d->eps, d->sinkhorn_iters, d->clamp_delta, Hpost, Hres, sums,
+                                       saved, nsave, 2 * d->N, nsave - 2, s));
   XHC_STEP("dense_read",
            launch_dense_read(d->state_dtype, X, d->T, d->N, d->C, Hpre, 1, idx, d->k, input, nullptr, s));
   return hip_status(e);

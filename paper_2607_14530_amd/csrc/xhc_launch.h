@@ -92,6 +92,13 @@ inline int64_t proj_chunks(int state_dtype, bool gather, int64_t K, int C, int64
 hipError_t launch_proj_partial(int state_dtype, const void* X, int64_t T, int N, int C, int64_t K,
                                const void* packed, int64_t nout, const int32_t* idx, int k,
                                float* part, hipStream_t s);
+// Both projections of a sublayer whose N streams are all active and fixed, in
+// one read of the state: its active rows are the state's own rows in order
+// (slot j is stream j), so [W_post | W_res] has the rows of [W_r | W_pre].
+// Partials as of out_blocks(nout_full) + out_blocks(nout_act) output blocks.
+// bf16 state, C % 128 == 0.
+hipError_t launch_proj_both(const void* X, int64_t T, int N, int C, const void* packed_full, int64_t nout_full,
+                            const void* packed_act, int64_t nout_act, float* part, hipStream_t s);
 hipError_t launch_pre_route(const float* part, int64_t nchunk, int64_t nout, int64_t T, int N, int m, int k,
                             int npre, int64_t C, const float* colsum, const float* alpha_pre, int alpha_stride,
                             const float* b_pre, float eps, int32_t* idx, float* p, float* Hpre, float* sums,

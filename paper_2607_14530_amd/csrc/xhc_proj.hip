@@ -148,10 +148,12 @@ __global__ __launch_bounds__(256) void k_proj_partial(const TS* __restrict__ X, 
 // waves.  Two LDS buffers alternate: the copy of segment g + 1 is issued when
 // segment g starts and has landed by its end, so the only wait per segment
 // is one LDS barrier.  Each wave owns its tokens, so partials go out without a
-// cross-wave reduction.  EXACT: cb divides the k-blocks.
+// cross-wave reduction.  EXACT: cb divides the k-blocks.  Output blocks nob1 ..
+// come from a second packed matrix of the same rows (nob1 = NOB: none).
 template <int NOB, bool EXACT, bool GATHER>
 __global__ __launch_bounds__(256) void k_proj_wide(const uint16_t* __restrict__ X, int64_t T, int N, int C, int64_t K,
                                                    int64_t cb, const uint4* __restrict__ wpk,
+                                                   const uint4* __restrict__ wpk2, int nob1,
                                                    const int32_t* __restrict__ idx, int k, float* __restrict__ part) {
   constexpr int TG = wide_tg(NOB), KS = kWideStep, NOr = NOB * 16 + 2;
   constexpr int SS = wide_seg_steps(NOB);   // steps whose fragments share one LDS fill
@@ -252,7 +254,9 @@ __global__ __launch_bounds__(256) void k_proj_wide(const uint16_t* __restrict__ 
     for (int fi = wave; fi < FILL; fi += 4) {
       int64_t kb = kb0 + g * SS * KS + fi / NOB;
       if (!EXACT && kb >= nblk) kb = nblk - 1;
-      lds_dma16(wpk + (kb * NOB + fi % NOB) * kWave + lane,
+      const int ob = fi % NOB;
+      const uint4* src = ob < nob1 ? wpk + (kb * nob1 + ob) * kWave : wpk2 + (kb * (NOB - nob1) + ob - nob1) * kWave;
+      lds_dma16(src + lane,
                 __builtin_amdgcn_readfirstlane(wl_base + (uint32_t)(((g & 1) * FILL + fi) * kWave * 16)));
     }
   };
@@ -369,7 +373,8 @@ static bool wide_attrs_set() {
 
 template <bool GATHER>
 static hipError_t proj_wide_launch(const uint16_t* X, int64_t T, int N, int C, int64_t K, const ProjPlan& pl,
-                                   const uint4* w, int nob, const int32_t* idx, int k, float* part, hipStream_t s) {
+                                   const uint4* w, const uint4* w2, int nob1, int nob, const int32_t* idx, int k,
+                                   float* part, hipStream_t s) {
   // (the unguarded instance for chunks that divide K needs more registers
   // than two waves per SIMD allow, so the guarded one serves both)
   const dim3 grid((unsigned)((T + wide_tokens(nob) - 1) / wide_tokens(nob)), (unsigned)pl.nchunk);
@@ -377,7 +382,8 @@ static hipError_t proj_wide_launch(const uint16_t* X, int64_t T, int N, int C, i
   if (!wide_attrs_set<GATHER>()) return hipErrorInvalidConfiguration;
 #define XHC_WIDE_CASE(NB)                                                                                      \
   case NB:                                                                                                     \
-    k_proj_wide<NB, false, GATHER><<<grid, dim3(256), lds, s>>>(X, T, N, C, K, pl.chunk_blocks, w, idx, k, part); \
+    k_proj_wide<NB, false, GATHER><<<grid, dim3(256), lds, s>>>(X, T, N, C, K, pl.chunk_blocks, w, w2, nob1, idx, \
+                                                               k, part);                               \
     break;
   switch (nob) {
     XHC_WIDE_CASE(1) XHC_WIDE_CASE(2) XHC_WIDE_CASE(3) XHC_WIDE_CASE(4)
@@ -396,7 +402,7 @@ static hipError_t proj_dispatch(const TS* X, int64_t T, int N, int C, int64_t K,
   const int nob = (int)out_blocks(nout);
   if (nob > 8) return hipErrorInvalidValue;
   if constexpr (!Vec8<TS>::kSplit) {
-    if (pl.wide) return proj_wide_launch<GATHER>(X, T, N, C, K, pl, w, nob, idx, k, part, s);
+    if (pl.wide) return proj_wide_launch<GATHER>(X, T, N, C, K, pl, w, nullptr, nob, nob, idx, k, part, s);
   }
   if (Vec8<TS>::kSplit) return proj_launch<TS, GATHER, false, 1>(X, T, N, C, K, pl, w, nob, idx, k, part, s);
   const bool exact = !GATHER && (K / 32) % pl.chunk_blocks == 0;
@@ -409,6 +415,18 @@ static hipError_t proj_dispatch(const TS* X, int64_t T, int N, int C, int64_t K,
     default: XHC_PROJ_TG(1);
   }
 #undef XHC_PROJ_TG
+}
+
+hipError_t launch_proj_both(const void* X, int64_t T, int N, int C, const void* packed_full, int64_t nout_full,
+                            const void* packed_act, int64_t nout_act, float* part, hipStream_t s) {
+  if (T == 0) return hipSuccess;
+  const int nob1 = (int)out_blocks(nout_full), nob = nob1 + (int)out_blocks(nout_act);
+  const int64_t K = (int64_t)N * C;
+  const ProjPlan pl = proj_plan(XHC_BF16, false, K, C, 16 * nob, T);
+  if (!pl.wide) return hipErrorInvalidValue;
+  return proj_wide_launch<false>(reinterpret_cast<const uint16_t*>(X), T, N, C, K, pl,
+                                 reinterpret_cast<const uint4*>(packed_full),
+                                 reinterpret_cast<const uint4*>(packed_act), nob1, nob, nullptr, N, part, s);
 }
 
 hipError_t launch_proj_partial(int state_dtype, const void* X, int64_t T, int N, int C, int64_t K,
