@@ -83,7 +83,7 @@ constexpr size_t kPreErrBytes = 256;
 // layouts agree for a bf16 state and C % 128 == 0.
 bool pre_one_projection(const xhc_dims* d) {
   return d->k == d->N && d->m == d->k && (d->k == 2 || d->k == 4) && full_grouped(d->state_dtype, NC_of(d)) &&
-         act_grouped(d->state_dtype, d->C) && out_blocks(2 * d->N) + out_blocks(act_outs(d, d->Kr, 1)) <= 8;
+         act_grouped(d->state_dtype, d->C) && out_blocks(act_outs(d, d->Kr, 1)) <= 2;
 }
 // outputs of that pass, in whole blocks of 16
 int64_t both_outs(const xhc_dims* d) {

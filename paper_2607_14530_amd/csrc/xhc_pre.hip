@@ -76,18 +76,19 @@ hipError_t launch_colsum(int64_t K, int ncols, const float* W, float* out, hipSt
 
 // sums[o][t] = sum over chunks of part[chunk][o][t] (chunk order fixed), one
 // thread per (o, t); the loads of all chunks are issued before the adds.
+template <int B>   // chunks loaded together
 __global__ __launch_bounds__(256) void k_sum_chunks(const float* __restrict__ part, int64_t nchunk, int NO,
                                                     int64_t T, float* __restrict__ sums) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= (int64_t)NO * T) return;
   const int64_t stride = (int64_t)NO * T;
   float s = 0.f;
-  for (int64_t c0 = 0; c0 < nchunk; c0 += 16) {
-    float v[16];
+  for (int64_t c0 = 0; c0 < nchunk; c0 += B) {
+    float v[B];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = (c0 + u < nchunk) ? part[(c0 + u) * stride + i] : 0.f;
+    for (int u = 0; u < B; ++u) v[u] = (c0 + u < nchunk) ? part[(c0 + u) * stride + i] : 0.f;
 #pragma unroll
-    for (int u = 0; u < 16; ++u) s += v[u];
+    for (int u = 0; u < B; ++u) s += v[u];
   }
   sums[i] = s;
 }
@@ -275,7 +276,9 @@ __global__ __launch_bounds__(kCoefTok * kCoefParts) void k_pre_coef_sum(
 
 static hipError_t sum_chunks(const float* part, int64_t nchunk, int NO, int64_t T, float* sums, hipStream_t s) {
   const int64_t n = (int64_t)NO * T;
-  k_sum_chunks<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(part, nchunk, NO, T, sums);
+  const dim3 g((unsigned)((n + 255) / 256));
+  if (nchunk <= 8) k_sum_chunks<8><<<g, dim3(256), 0, s>>>(part, nchunk, NO, T, sums);
+  else k_sum_chunks<16><<<g, dim3(256), 0, s>>>(part, nchunk, NO, T, sums);
   return hipGetLastError();
 }
 

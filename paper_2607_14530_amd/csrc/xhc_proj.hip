@@ -148,12 +148,12 @@ __global__ __launch_bounds__(256) void k_proj_partial(const TS* __restrict__ X, 
 // waves.  Two LDS buffers alternate: the copy of segment g + 1 is issued when
 // segment g starts and has landed by its end, so the only wait per segment
 // is one LDS barrier.  Each wave owns its tokens, so partials go out without a
-// cross-wave reduction.  EXACT: cb divides the k-blocks.  Output blocks nob1 ..
-// come from a second packed matrix of the same rows (nob1 = NOB: none).
-template <int NOB, bool EXACT, bool GATHER>
+// cross-wave reduction.  EXACT: cb divides the k-blocks.  Output blocks NOB1 ..
+// come from a second packed matrix of the same rows (NOB1 = NOB: none).
+template <int NOB, bool EXACT, bool GATHER, int NOB1 = NOB>
 __global__ __launch_bounds__(256) void k_proj_wide(const uint16_t* __restrict__ X, int64_t T, int N, int C, int64_t K,
                                                    int64_t cb, const uint4* __restrict__ wpk,
-                                                   const uint4* __restrict__ wpk2, int nob1,
+                                                   const uint4* __restrict__ wpk2,
                                                    const int32_t* __restrict__ idx, int k, float* __restrict__ part) {
   constexpr int TG = wide_tg(NOB), KS = kWideStep, NOr = NOB * 16 + 2;
   constexpr int SS = wide_seg_steps(NOB);   // steps whose fragments share one LDS fill
@@ -255,7 +255,8 @@ __global__ __launch_bounds__(256) void k_proj_wide(const uint16_t* __restrict__ 
       int64_t kb = kb0 + g * SS * KS + fi / NOB;
       if (!EXACT && kb >= nblk) kb = nblk - 1;
       const int ob = fi % NOB;
-      const uint4* src = ob < nob1 ? wpk + (kb * nob1 + ob) * kWave : wpk2 + (kb * (NOB - nob1) + ob - nob1) * kWave;
+      const uint4* src = NOB1 == NOB || ob < NOB1 ? wpk + (kb * NOB1 + ob) * kWave
+                                                  : wpk2 + (kb * (NOB - NOB1) + ob - NOB1) * kWave;
       lds_dma16(src + lane,
                 __builtin_amdgcn_readfirstlane(wl_base + (uint32_t)(((g & 1) * FILL + fi) * kWave * 16)));
     }
@@ -367,23 +368,38 @@ static bool wide_attrs_set() {
     if (hipFuncSetAttribute(fs[nb - 1], hipFuncAttributeMaxDynamicSharedMemorySize, (int)wide_lds_bytes(nb)) !=
         hipSuccess)
       return false;
+  if (!GATHER &&
+      (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_proj_wide<2, false, false, 1>),
+                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)wide_lds_bytes(2)) != hipSuccess ||
+       hipFuncSetAttribute(reinterpret_cast<const void*>(&k_proj_wide<3, false, false, 1>),
+                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)wide_lds_bytes(3)) != hipSuccess))
+    return false;
   dev_done = dev;
   return true;
 }
 
 template <bool GATHER>
 static hipError_t proj_wide_launch(const uint16_t* X, int64_t T, int N, int C, int64_t K, const ProjPlan& pl,
-                                   const uint4* w, const uint4* w2, int nob1, int nob, const int32_t* idx, int k,
+                                   const uint4* w, const uint4* w2, int nob, const int32_t* idx, int k,
                                    float* part, hipStream_t s) {
   // (the unguarded instance for chunks that divide K needs more registers
   // than two waves per SIMD allow, so the guarded one serves both)
   const dim3 grid((unsigned)((T + wide_tokens(nob) - 1) / wide_tokens(nob)), (unsigned)pl.nchunk);
   const size_t lds = wide_lds_bytes(nob);
   if (!wide_attrs_set<GATHER>()) return hipErrorInvalidConfiguration;
-#define XHC_WIDE_CASE(NB)                                                                                      \
-  case NB:                                                                                                     \
-    k_proj_wide<NB, false, GATHER><<<grid, dim3(256), lds, s>>>(X, T, N, C, K, pl.chunk_blocks, w, w2, nob1, idx, \
-                                                               k, part);                               \
+  if constexpr (!GATHER)
+    if (w2) {   // two matrices: one block of the first, one or two of the second
+      if (nob == 2)
+        k_proj_wide<2, false, false, 1><<<grid, dim3(256), lds, s>>>(X, T, N, C, K, pl.chunk_blocks, w, w2, idx, k, part);
+      else if (nob == 3)
+        k_proj_wide<3, false, false, 1><<<grid, dim3(256), lds, s>>>(X, T, N, C, K, pl.chunk_blocks, w, w2, idx, k, part);
+      else
+        return hipErrorInvalidValue;
+      return hipGetLastError();
+    }
+#define XHC_WIDE_CASE(NB)                                                                                             \
+  case NB:                                                                                                            \
+    k_proj_wide<NB, false, GATHER><<<grid, dim3(256), lds, s>>>(X, T, N, C, K, pl.chunk_blocks, w, w2, idx, k, part); \
     break;
   switch (nob) {
     XHC_WIDE_CASE(1) XHC_WIDE_CASE(2) XHC_WIDE_CASE(3) XHC_WIDE_CASE(4)
@@ -402,7 +418,7 @@ static hipError_t proj_dispatch(const TS* X, int64_t T, int N, int C, int64_t K,
   const int nob = (int)out_blocks(nout);
   if (nob > 8) return hipErrorInvalidValue;
   if constexpr (!Vec8<TS>::kSplit) {
-    if (pl.wide) return proj_wide_launch<GATHER>(X, T, N, C, K, pl, w, nullptr, nob, nob, idx, k, part, s);
+    if (pl.wide) return proj_wide_launch<GATHER>(X, T, N, C, K, pl, w, nullptr, nob, idx, k, part, s);
   }
   if (Vec8<TS>::kSplit) return proj_launch<TS, GATHER, false, 1>(X, T, N, C, K, pl, w, nob, idx, k, part, s);
   const bool exact = !GATHER && (K / 32) % pl.chunk_blocks == 0;
@@ -420,13 +436,13 @@ static hipError_t proj_dispatch(const TS* X, int64_t T, int N, int C, int64_t K,
 hipError_t launch_proj_both(const void* X, int64_t T, int N, int C, const void* packed_full, int64_t nout_full,
                             const void* packed_act, int64_t nout_act, float* part, hipStream_t s) {
   if (T == 0) return hipSuccess;
-  const int nob1 = (int)out_blocks(nout_full), nob = nob1 + (int)out_blocks(nout_act);
+  const int nob = (int)(out_blocks(nout_full) + out_blocks(nout_act));
   const int64_t K = (int64_t)N * C;
   const ProjPlan pl = proj_plan(XHC_BF16, false, K, C, 16 * nob, T);
-  if (!pl.wide) return hipErrorInvalidValue;
+  if (!pl.wide || out_blocks(nout_full) != 1) return hipErrorInvalidValue;
   return proj_wide_launch<false>(reinterpret_cast<const uint16_t*>(X), T, N, C, K, pl,
                                  reinterpret_cast<const uint4*>(packed_full),
-                                 reinterpret_cast<const uint4*>(packed_act), nob1, nob, nullptr, N, part, s);
+                                 reinterpret_cast<const uint4*>(packed_act), nob, nullptr, N, part, s);
 }
 
 hipError_t launch_proj_partial(int state_dtype, const void* X, int64_t T, int N, int C, int64_t K,
