@@ -1968,28 +1968,28 @@ size_t bwd_post_ws_bytes(const xhc_dims* d) {
 
 // The full-row pass of NQ pre-map reverses over one state in a single pass
 // (the entry state of an xHC-Flash group: the router with the first pre-map,
-// then one pre-map per sublayer; bf16 state, N = 16), run by the ring pass
-// of xhc_bwd_rows.hip; the contraction of the dX product runs over the 16
-// router and 16 NQ pre-map outputs, each pass's per-token record (tok) giving its
+// then one pre-map per sublayer; bf16 state, N = 8 or 16), run by the ring pass
+// of xhc_bwd_rows.hip; the contraction of the dX product runs over the N
+// router and N NQ pre-map outputs, each pass's per-token record (tok) giving its
 // own dz'.  The per-token terms add up over the passes: the dense reads
 // sum_q H^pre,q_i d input_q, the pre-map norm terms sum_q beta_pre,q x, and
 // the router's LayerNorm terms of the first pass (later passes have no router
 // gradient, so theirs are zero).  The weight partials of output block ob go
-// to wout[ob] ([chunk][N C][16]: the router, then pre-map q).
+// to wout[ob] ([chunk][N C][N]: the router, then pre-map q).
 struct MultiRows {
   const float* tok[kMultiMaxQ];   // per pass: the token records
   const float* hrd[kMultiMaxQ];   // per pass: weights of the dense read [T, N]
   const uint16_t* din[kMultiMaxQ];
-  const float* w[kMultiMaxQ + 1];  // W_r, then W_pre of pass q ([N C][16] each)
+  const float* w[kMultiMaxQ + 1];  // W_r, then W_pre of pass q ([N C][N] each)
   float* wout[kMultiMaxQ + 1];
 };
 // The multi-map ring pass's inputs from the passes' token records: dz' packed
-// (outputs r_ln dz_r (16) | r dz_pre,q (16 each), padded to whole 32-blocks,
+// (outputs r_ln dz_r (N) | r dz_pre,q (N each), padded to whole 32-blocks,
 // zero past T) and the scalars r_ln, mu, m1, m2, sum_q beta_pre,q.
-template <int NQ>
-__global__ __launch_bounds__(256) void k_dz_pack_multi(MultiRows m, int64_t T, int N, int NA,
+template <int NQ, int N>
+__global__ __launch_bounds__(256) void k_dz_pack_multi(MultiRows m, int64_t T, int NA,
                                                        uint16_t* __restrict__ rows, float* __restrict__ srec) {
-  constexpr int NO = 16 * (NQ + 1), NOP = (NO + 31) / 32 * 32;
+  constexpr int NO = N * (NQ + 1), NOP = (NO + 31) / 32 * 32;
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t Tp = (T + kDzBlock - 1) / kDzBlock * kDzBlock;
   if (i >= Tp * NOP) return;
@@ -1999,8 +1999,8 @@ __global__ __launch_bounds__(256) void k_dz_pack_multi(MultiRows m, int64_t T, i
   const int64_t at = t * TF + 2 * N + NA;   // the token's scalars
   float v = 0.f;
   if (t < T && o < NO) {
-    const float* tk = m.tok[o < 16 ? 0 : o / 16 - 1];
-    v = o < 16 ? tk[at + 1] * tk[t * TF + o] : tk[at] * tk[t * TF + N + o % 16];
+    const float* tk = m.tok[o < N ? 0 : o / N - 1];
+    v = o < N ? tk[at + 1] * tk[t * TF + o] : tk[at] * tk[t * TF + N + o % N];
   }
   dz_store(rows, Tp, NOP, t, o, v);
   if (o < 8) {
@@ -2058,7 +2058,7 @@ BwdPreWs bwd_pre_ws(const xhc_dims* d, char* ws) {
 }
 
 bool bwd_rows_multi_supported(const xhc_dims* d, int Q) {
-  return d->state_dtype == XHC_BF16 && d->N == 16 && bwd_rows_ring_supported((int64_t)d->N * d->C, d->C, chunk_full(d)) &&
+  return d->state_dtype == XHC_BF16 && (d->N == 8 || d->N == 16) && bwd_rows_ring_supported((int64_t)d->N * d->C, d->C, chunk_full(d)) &&
          (Q == 2 || Q == 4);
 }
 
@@ -2076,10 +2076,10 @@ hipError_t launch_bwd_dhpre_multi(const xhc_dims* d, int Q, const void* X, const
 }
 
 // the packed dz', then the scalars [Tp][8]
-static int64_t multi_nop(int Q) { return (16 * (Q + 1) + 31) / 32 * 32; }
+static int64_t multi_nop(int N, int Q) { return (N * (Q + 1) + 31) / 32 * 32; }
 size_t bwd_rows_multi_ws_bytes(const xhc_dims* d, int Q) {
   const size_t Tp = (size_t)((d->T + kDzBlock - 1) / kDzBlock * kDzBlock);
-  return Tp * 2 * multi_nop(Q) * 2 * sizeof(uint16_t) + Tp * 8 * sizeof(float);
+  return Tp * 2 * multi_nop(d->N, Q) * 2 * sizeof(uint16_t) + Tp * 8 * sizeof(float);
 }
 
 hipError_t launch_bwd_rows_multi(const xhc_dims* d, int Q, const void* X, void* dX, const float* W_r,
@@ -2100,15 +2100,17 @@ hipError_t launch_bwd_rows_multi(const xhc_dims* d, int Q, const void* X, void* 
     m.w[q + 1] = W_pre + (int64_t)q * NC * N;
     m.wout[q + 1] = w.wpart_p;
   }
-  const int64_t Tp = (T + kDzBlock - 1) / kDzBlock * kDzBlock, nop = multi_nop(Q);
+  const int64_t Tp = (T + kDzBlock - 1) / kDzBlock * kDzBlock, nop = multi_nop(N, Q);
   uint16_t* dzp = reinterpret_cast<uint16_t*>(pack_ws);
   float* srec = reinterpret_cast<float*>(dzp + Tp * 2 * nop * 2);
   const dim3 gk((unsigned)((Tp * nop + 255) / 256));
-  if (Q == 4) k_dz_pack_multi<4><<<gk, dim3(256), 0, s>>>(m, T, N, NA, dzp, srec);
-  else k_dz_pack_multi<2><<<gk, dim3(256), 0, s>>>(m, T, N, NA, dzp, srec);
+  if (N == 16 && Q == 4) k_dz_pack_multi<4, 16><<<gk, dim3(256), 0, s>>>(m, T, NA, dzp, srec);
+  else if (N == 16) k_dz_pack_multi<2, 16><<<gk, dim3(256), 0, s>>>(m, T, NA, dzp, srec);
+  else if (Q == 4) k_dz_pack_multi<4, 8><<<gk, dim3(256), 0, s>>>(m, T, NA, dzp, srec);
+  else k_dz_pack_multi<2, 8><<<gk, dim3(256), 0, s>>>(m, T, NA, dzp, srec);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int no = 16 * (Q + 1);
+  const int no = N * (Q + 1);
   RowRingDesc rd{};
   rd.X = X;
   rd.dX = dX;
@@ -2120,11 +2122,11 @@ hipError_t launch_bwd_rows_multi(const xhc_dims* d, int Q, const void* X, void* 
   rd.hp_stride = N;
   for (int b = 0; b <= Q; ++b) {
     rd.w[b] = m.w[b];
-    rd.win[b] = 16;
+    rd.win[b] = N;
     rd.wout[b] = m.wout[b];
   }
   rd.nwin = Q + 1;
-  rd.wout_w = 16;
+  rd.wout_w = N;
   rd.nout = no;
   rd.dzp = dzp;
   rd.nop = (int)nop;

@@ -404,11 +404,16 @@ hipError_t launch_bwd_rows_ring(const RowRingDesc& d, int64_t rows, hipStream_t 
   a.NK = rows;
   const dim3 grid((unsigned)(rows / RR), (unsigned)((d.T + d.tchunk - 1) / d.tchunk));
   // one pre-map: 2N outputs padded to 32 (64 at N = 32); the Flash group's
-  // router and Q pre-maps: 16 (Q + 1) outputs; a Flash sublayer's active
+  // router and Q pre-maps: N (Q + 1) outputs; a Flash sublayer's active
   // rows: up to 32 outputs, fp32 gradient rows
   if (!d.dx_f32) {
     if (d.nq == 1 && d.nop == 32 && d.nout <= 32) return launch_ring<1, 32, 32, 4, uint16_t>(a, grid, s);
     if (d.nq == 1 && d.nop == 64 && d.nout <= 64) return launch_ring<1, 64, 64, 3, uint16_t>(a, grid, s);
+    // (N = 8: 8 (Q + 1) outputs; in passes of one map each the state was read and
+    // its gradient updated Q times.  Forward and backward of a group at T = 3540,
+    // C = 512, Q = 4: 1082 us so, 887 us in one pass)
+    if (d.nq == 2 && d.nop == 32 && d.nout <= 32) return launch_ring<2, 32, 32, 3, uint16_t>(a, grid, s);
+    if (d.nq == 4 && d.nop == 64 && d.nout <= 48) return launch_ring<4, 64, 48, 2, uint16_t>(a, grid, s);
     if (d.nq == 2 && d.nop == 64 && d.nout == 48) return launch_ring<2, 64, 48, 3, uint16_t>(a, grid, s);
     if (d.nq == 4 && d.nop == 96 && d.nout == 80) return launch_ring<4, 96, 80, 2, uint16_t>(a, grid, s);
   } else if (d.nop == 32 && d.nout <= 32) {

@@ -243,8 +243,8 @@ hipError_t launch_bwd_pre(const xhc_dims* d, const BwdPre& b, hipStream_t s);
 // the token reverses (after launch_bwd_dhpre_multi) and the reductions
 hipError_t launch_bwd_pre_tokens(const xhc_dims* d, const BwdPre* b, int n, hipStream_t s);
 hipError_t launch_bwd_pre_reduce(const xhc_dims* d, const BwdPre* b, int n, hipStream_t s);
-// The full-row pass of Q pre-map reverses of one bf16 state (N = 16, Q = 2 or
-// 4) in one pass: pass q's token records and weight partials live in the
+// The full-row pass of Q pre-map reverses of one bf16 state (N = 8 or 16, Q = 2
+// or 4) in one pass: pass q's token records and weight partials live in the
 // launch_bwd_pre workspace ws[q] (after launch_bwd_pre_tokens; the router's
 // partials in ws[0]), hrd[q] are its dense-read weights [T, N], d_input is
 // [Q, T, C]; dX accumulates every pass's row terms.
