@@ -124,7 +124,14 @@ xhc_status xhc_pack_full(const xhc_dims* d, int32_t npre, const float* W_r, cons
 xhc_status xhc_pack_active(const xhc_dims* d, int32_t Kq, const float* W_post, const float* W_res,
                            void* packed, void* stream);
 
-/* Workspace needed by an entry point (op: one of the XHC_OP_* values).        */
+/* Workspace of an entry point (op: one of the XHC_OP_* values): the bytes with
+ * which it takes its fastest form.  Few tokens run fastest in many short
+ * pieces, each of which leaves partial sums, so this does not grow with T
+ * throughout (N = 16, C = 4096: POST_BWD at T = 777 names 1.4 times the bytes of
+ * T = 1024).  With less the backward takes longer pieces, the same results to
+ * the order of the sums, and XHC_EWORKSPACE is returned where those do not fit
+ * either; so for POST_BWD, PRE_BWD and FLASH_POST_BWD, and FLASH_PRE_BWD of a
+ * bf16 state, a workspace of the bytes named for T tokens also serves fewer. */
 enum {
   XHC_OP_PRE = 0, XHC_OP_POST = 1, XHC_OP_FLASH_PRE = 2, XHC_OP_FLASH_POST = 3,
   XHC_OP_POST_BWD = 4, XHC_OP_PRE_BWD = 5, XHC_OP_FLASH_POST_BWD = 6, XHC_OP_FLASH_PRE_BWD = 7

@@ -192,7 +192,7 @@ struct FlashPostBwdWs {
       saved, hpost_re, hres_re, wres0, total;
 };
 
-FlashPostBwdWs flash_post_bwd_ws(const xhc_dims* d, int Q, int q) {
+FlashPostBwdWs flash_post_bwd_ws(const xhc_dims* d, int Q, int q, bool fine) {
   const int Kq = flash_Kq(d, q);
   const xhc_dims r = dims_rows32(d, Kq);
   const int64_t T = d->T, k = d->k, C = d->C, kC = k * C;
@@ -200,8 +200,8 @@ FlashPostBwdWs flash_post_bwd_ws(const xhc_dims* d, int Q, int q) {
   const int64_t na = act_outs(d, Kq, q == Q);
   Carve c;
   FlashPostBwdWs w;
-  w.post = c.take(bwd_post_ws_bytes(&r));
-  w.pre = c.take(bwd_pre_ws_bytes(&r));
+  w.post = c.take(bwd_post_ws_bytes(&r, fine));
+  w.pre = c.take(bwd_pre_ws_bytes(&r, fine));
   w.part = c.take(part_bytes(d, true, kC, na));
   w.sums = c.take(sums_bytes(na, T));
   w.idx_id = c.take((size_t)T * k * sizeof(int32_t));
@@ -225,15 +225,18 @@ struct FlashPreBwdWs {
   size_t pre, part, sums, saved, idx_s, p_s, hpre_s, hmask, total;
 };
 
-FlashPreBwdWs flash_pre_bwd_ws(const xhc_dims* d, int Q) {
+// The Q row passes in one pass over the state keep Q reverses' workspaces.  At N
+// = 8 that is a step of its own, taken with the fine layout (C = 1024, Q = 4, T =
+// 16384: 182 MB against 72).
+FlashPreBwdWs flash_pre_bwd_ws(const xhc_dims* d, int Q, bool fine) {
   const xhc_dims e = dims_entry(d);
   const int64_t T = d->T, N = d->N, k = d->k, C = d->C, NC = N * C, kC = k * C;
   const size_t f = sizeof(float);
   const int64_t nf = (int64_t)(Q + 1) * N;
   Carve c;
   FlashPreBwdWs w;
-  w.fused = bwd_rows_multi_supported(&e, Q);
-  w.pre_slice = align_up(bwd_pre_ws_bytes(&e));
+  w.fused = bwd_rows_multi_supported(&e, Q) && (fine || N == 16);
+  w.pre_slice = align_up(bwd_pre_ws_bytes(&e, fine));
   w.pre = c.take((w.fused ? Q : 1) * w.pre_slice);
   w.multi = c.take(w.fused ? bwd_rows_multi_ws_bytes(&e, Q) : 0);
   w.part = c.take(part_bytes(d, false, NC, nf));
@@ -382,8 +385,8 @@ size_t xhc_workspace_bytes(const xhc_dims* d, int32_t op, int32_t Q) {
   switch (op) {
     case XHC_OP_PRE: return pre_ws(d);
     case XHC_OP_POST: return plan_of(d, d->Kr, SIZE_MAX).bytes;
-    case XHC_OP_POST_BWD: return bwd_post_ws_bytes(d);
-    case XHC_OP_PRE_BWD: return bwd_pre_supported(d) ? bwd_pre_ws_bytes(d) : 0;
+    case XHC_OP_POST_BWD: return bwd_post_ws_bytes(d, true);
+    case XHC_OP_PRE_BWD: return bwd_pre_supported(d) ? bwd_pre_ws_bytes(d, true) : 0;
     case XHC_OP_FLASH_PRE: return (Q == 2 || Q == 4) ? flash_pre_ws(d, Q) : 0;
     case XHC_OP_FLASH_POST: {
       if (Q != 2 && Q != 4) return 0;
@@ -394,11 +397,11 @@ size_t xhc_workspace_bytes(const xhc_dims* d, int32_t op, int32_t Q) {
     case XHC_OP_FLASH_POST_BWD: {
       if ((Q != 2 && Q != 4) || !flash_bwd_supported(d)) return 0;
       size_t need = 0;
-      for (int q = 1; q <= Q; ++q) need = std::max(need, flash_post_bwd_ws(d, Q, q).total);
+      for (int q = 1; q <= Q; ++q) need = std::max(need, flash_post_bwd_ws(d, Q, q, true).total);
       return need;
     }
     case XHC_OP_FLASH_PRE_BWD:
-      return ((Q == 2 || Q == 4) && flash_bwd_supported(d)) ? flash_pre_bwd_ws(d, Q).total : 0;
+      return ((Q == 2 || Q == 4) && flash_bwd_supported(d)) ? flash_pre_bwd_ws(d, Q, true).total : 0;
     default: return 0;
   }
 }
@@ -650,12 +653,13 @@ xhc_status xhc_post_bwd(const xhc_dims* d, const void* dXn, void* X, const void*
   if (!aligned16(dXn) || !aligned16(X) || !aligned16(Xact) || !aligned16(F) || !aligned16(dX) || !aligned16(dF) ||
       (conv_w && !aligned16(conv_w)) || (dconv_w && !aligned16(dconv_w)))
     return XHC_EUNSUPPORTED;
-  if (workspace_bytes < bwd_post_ws_bytes(d)) return XHC_EWORKSPACE;
+  if (workspace_bytes < bwd_post_ws_bytes(d, false)) return XHC_EWORKSPACE;
+  const bool fine = workspace_bytes >= bwd_post_ws_bytes(d, true);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   clear_stale_error();
   hipError_t e = hipSuccess;
   XHC_STEP("post_bwd", launch_bwd_post(d, dXn, X, Xact, F, conv_w, idx, p, Hres, Hpost, dX, dF, dHres, dHpost, dp,
-                                       dconv_w, reinterpret_cast<char*>(workspace), s, /*grad_f32=*/false));
+                                       dconv_w, reinterpret_cast<char*>(workspace), fine, s, /*grad_f32=*/false));
   return hip_status(e);
 }
 
@@ -676,7 +680,7 @@ xhc_status xhc_pre_bwd(const xhc_dims* d, const void* X, const void* packed_full
     return XHC_EINVAL;
   if (dX == X) return XHC_EINVAL;
   if (!aligned16(X) || !aligned16(d_input) || !aligned16(dX)) return XHC_EUNSUPPORTED;
-  if (workspace_bytes < bwd_pre_ws_bytes(d)) return XHC_EWORKSPACE;
+  if (workspace_bytes < bwd_pre_ws_bytes(d, false)) return XHC_EWORKSPACE;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   clear_stale_error();
   const float* colsum = reinterpret_cast<const float*>(reinterpret_cast<const char*>(packed_full) +
@@ -714,6 +718,7 @@ xhc_status xhc_pre_bwd(const xhc_dims* d, const void* X, const void* packed_full
   b.db_res = db_res;
   b.db_post = db_post;
   b.ws = reinterpret_cast<char*>(workspace);
+  b.fine = workspace_bytes >= bwd_pre_ws_bytes(d, true);
   XHC_STEP("pre_bwd", launch_bwd_pre(d, b, s));
   return hip_status(e);
 }
@@ -750,8 +755,9 @@ xhc_status xhc_flash_post_bwd(const xhc_dims* d, int32_t Q, int32_t q, const voi
       (dXn && !aligned16(dXn)) || (d_input && !aligned16(d_input)) || (conv_w && !aligned16(conv_w)) ||
       (dconv_w && !aligned16(dconv_w)) || !aligned16(workspace))
     return XHC_EUNSUPPORTED;
-  const FlashPostBwdWs w = flash_post_bwd_ws(d, Q, q);
-  if (workspace_bytes < w.total) return XHC_EWORKSPACE;
+  if (workspace_bytes < flash_post_bwd_ws(d, Q, q, false).total) return XHC_EWORKSPACE;
+  const bool fine = workspace_bytes >= flash_post_bwd_ws(d, Q, q, true).total;
+  const FlashPostBwdWs w = flash_post_bwd_ws(d, Q, q, fine);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   clear_stale_error();
   char* ws = reinterpret_cast<char*>(workspace);
@@ -782,7 +788,7 @@ xhc_status xhc_flash_post_bwd(const xhc_dims* d, int32_t Q, int32_t q, const voi
   float* const dA_out = fold_read ? dA : F32(w.da_out);
   const xhc_dims rs = dims_rows(d, Kq);
   XHC_STEP("fbwd_post", launch_bwd_post(&rs, dA, nullptr, Xact, F, conv_w, idx_id, p, hres_use, Hpost, dA_out,
-                                        dF, F32(w.dhres), F32(w.dhpost), dp, dconv_w, ws + w.post, s,
+                                        dF, F32(w.dhres), F32(w.dhpost), dp, dconv_w, ws + w.post, fine, s,
                                         /*grad_f32=*/true, /*add_dp=*/true));
   // the mapping logits of sublayer q: saved by the forward, or recomputed
   // from a^(q-1) (same kernels and operands as the forward)
@@ -822,6 +828,7 @@ xhc_status xhc_flash_post_bwd(const xhc_dims* d, int32_t Q, int32_t q, const voi
   bp.db_res = db_res;
   bp.db_post = db_post;
   bp.ws = ws + w.pre;
+  bp.fine = fine;
   bp.dense_rows = false;
   bp.X_bf16 = bf ? Xact : nullptr;
   bp.act_din = fold_read && reads ? d_input : nullptr;
@@ -853,8 +860,9 @@ xhc_status xhc_flash_pre_bwd(const xhc_dims* d, int32_t Q, const void* X, const 
   if (!aligned16(X) || !aligned16(packed_full) || !aligned16(d_input) || !aligned16(dXn) || !aligned16(da0) ||
       !aligned16(dX) || !aligned16(workspace))
     return XHC_EUNSUPPORTED;
-  const FlashPreBwdWs w = flash_pre_bwd_ws(d, Q);
-  if (workspace_bytes < w.total) return XHC_EWORKSPACE;
+  if (workspace_bytes < flash_pre_bwd_ws(d, Q, false).total) return XHC_EWORKSPACE;
+  const bool fine = workspace_bytes >= flash_pre_bwd_ws(d, Q, true).total;
+  const FlashPreBwdWs w = flash_pre_bwd_ws(d, Q, fine);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   clear_stale_error();
   char* ws = reinterpret_cast<char*>(workspace);
@@ -907,6 +915,7 @@ xhc_status xhc_flash_pre_bwd(const xhc_dims* d, int32_t Q, const void* X, const 
     b.dal_pre = dalpha_pre + q;
     b.db_pre = db_pre + (int64_t)q * N;
     b.ws = wsq[q];
+    b.fine = fine;
     b.dhpre_act = q >= 1 ? dHpre_act + (int64_t)(q - 1) * T * k : nullptr;
     b.hmask = q >= 1 ? F32(w.hmask) + (int64_t)q * T * N : nullptr;
     b.act_rows = false;
@@ -924,7 +933,8 @@ xhc_status xhc_flash_pre_bwd(const xhc_dims* d, int32_t Q, const void* X, const 
     for (int q = 0; q < Q && !saved && e == hipSuccess; ++q) XHC_STEP("fpbwd_route", recompute(q));
     XHC_STEP("fpbwd_dhpre", launch_bwd_dhpre_multi(&en, Q, X, d_input, wsq, s));
     XHC_STEP("fpbwd_tokens", launch_bwd_pre_tokens(&en, bp, Q, s));
-    XHC_STEP("fpbwd_rows", launch_bwd_rows_multi(&en, Q, X, dX, W_r, W_pre, d_input, hrd, wsq, ws + w.multi, s));
+    XHC_STEP("fpbwd_rows", launch_bwd_rows_multi(&en, Q, X, dX, W_r, W_pre, d_input, hrd, wsq, ws + w.multi, fine,
+                                                 s));
     XHC_STEP("fpbwd_reduce", launch_bwd_pre_reduce(&en, bp, Q, s));
   } else {
     for (int q = 0; q < Q && e == hipSuccess; ++q) {

@@ -1810,13 +1810,17 @@ static bool post_run_ok(const xhc_dims* d) {
 // workgroups resident) would then be left partly idle.  A workgroup's time is
 // that of its tokens in sequence, so shorter runs finish sooner there: forward
 // and backward of a sublayer at T = 512, N = 8, C = 1024 took 654 us with the
-// full lengths (16 and 8 workgroups), 295 us with these.  The conv reverse needs 11 tokens a run at least (a token's dF may reach one run
-// back, no further).
+// full lengths (16 and 8 workgroups), 295 us with these.  The conv reverse
+// needs 11 tokens a run at least (a token's dF may reach one run back, no
+// further); its runs leave partials in the workspace, so it takes the full
+// length where the caller's holds no more (fine false).
 static int halve_to_fill(int rl, int least, int64_t T, int64_t blocks) {
   while (rl > least && (T + rl - 1) / rl * blocks < 512) rl /= 2;
   return rl;
 }
-static int conv_run_len(const xhc_dims* d) { return halve_to_fill(kConvRun, 16, d->T, d->C / 256); }
+static int conv_run_len(const xhc_dims* d, bool fine) {
+  return fine ? halve_to_fill(kConvRun, 16, d->T, d->C / 256) : kConvRun;
+}
 static int dot_run_len(const xhc_dims* d, int nthr) { return halve_to_fill(kDotRun, 4, d->T, d->C / (4 * nthr)); }
 
 #define XHC_TS_DISPATCH(dt, ...) \
@@ -1825,7 +1829,7 @@ static int dot_run_len(const xhc_dims* d, int nthr) { return halve_to_fill(kDotR
 hipError_t launch_bwd_post(const xhc_dims* d, const void* dXn, void* X, const void* Xact, const void* F,
                            const float* conv_w, const int32_t* idx, const float* p, const float* Hres,
                            const float* Hpost, void* dX, void* dF, float* dHres, float* dHpost, float* dp,
-                           float* dconv_w, char* ws, hipStream_t s, bool grad_f32, bool add_dp) {
+                           float* dconv_w, char* ws, bool fine, hipStream_t s, bool grad_f32, bool add_dp) {
   const int64_t T = d->T, S = d->S;
   const int N = d->N, C = d->C, k = d->k, Kr = d->Kr;
   const int64_t ncb = post_chunks(C);
@@ -1835,7 +1839,7 @@ hipError_t launch_bwd_post(const xhc_dims* d, const void* dXn, void* X, const vo
   const int km = k <= 4 ? 4 : 8;
   const int nd = km * km + km * Kr + Kr * (Kr + 1) / 2;
   const bool fused = post_run_ok(d);
-  const int crl = conv_run_len(d);   // fused: tokens per run
+  const int crl = conv_run_len(d, fine);   // fused: tokens per run
   const int64_t nruns = (T + crl - 1) / crl;
   float* part = reinterpret_cast<float*>(ws);
   // dots partials: [post_chunks(C)][nd][T], or, fused, [C / 256][T][nd]
@@ -1944,7 +1948,7 @@ hipError_t launch_bwd_post(const xhc_dims* d, const void* dXn, void* X, const vo
   return hipGetLastError();
 }
 
-size_t bwd_post_ws_bytes(const xhc_dims* d) {
+size_t bwd_post_ws_bytes(const xhc_dims* d, bool fine) {
   const int64_t T = d->T;
   const int C = d->C, k = d->k, Kr = d->Kr;
   const int km = k <= 4 ? 4 : 8;
@@ -1955,7 +1959,7 @@ size_t bwd_post_ws_bytes(const xhc_dims* d) {
     int nrows = 0;
     for (int j = 0; j < Kr - 1; ++j) nrows += d->kappa[j];
     const size_t chunked = (size_t)((T + kConvChunk - 1) / kConvChunk) * nrows * C;
-    const int crl = post_run_ok(d) ? conv_run_len(d) : kConvRun;
+    const int crl = post_run_ok(d) ? conv_run_len(d, fine) : kConvRun;
     const size_t nruns = (size_t)((T + crl - 1) / crl);
     const size_t runs = conv_run_ok(d) ? nruns * kConvRows * C : 0;
     // fused: only the run boundary parts instead of de
@@ -2022,22 +2026,25 @@ __global__ __launch_bounds__(256) void k_dz_pack_multi(MultiRows m, int64_t T, i
 // (the ring pass holds one a CU) shorter chunks finish sooner, down to two
 // steps.  Forward and backward at T = 968, N = 8, C = 256: 282 us with 16 and 8
 // workgroups of 1024 tokens (50 and 53 us of them in the full and the active
-// rows), 200 us with these; T = 512, N = 8, C = 1024: 244 and 211 us.
-static int64_t row_chunk(int64_t T, int64_t rows) {
-  int64_t c = 1024;
-  while (c > 64 && rows / kActRows * ((T + c - 1) / c) < 256) c /= 2;
+// rows), 200 us with these; T = 512, N = 8, C = 1024: 244 and 211 us.  Every
+// chunk leaves a partial in the workspace: the full length where the caller's
+// holds no more (fine false).
+constexpr int64_t kMinRowChunk = 64, kRowChunk = 1024;
+static int64_t row_chunk(int64_t T, int64_t rows, bool fine) {
+  int64_t c = kRowChunk;
+  while (fine && c > kMinRowChunk && rows / kActRows * ((T + c - 1) / c) < 256) c /= 2;
   return c;
 }
-static int64_t chunk_full(const xhc_dims* d) { return row_chunk(d->T, (int64_t)d->N * d->C); }
-static int64_t chunk_act(const xhc_dims* d) { return row_chunk(d->T, (int64_t)d->k * d->C); }
+static int64_t chunk_full(const xhc_dims* d, bool fine) { return row_chunk(d->T, (int64_t)d->N * d->C, fine); }
+static int64_t chunk_act(const xhc_dims* d, bool fine) { return row_chunk(d->T, (int64_t)d->k * d->C, fine); }
 static int64_t nchunks(int64_t T, int64_t chunk) { return (T + chunk - 1) / chunk; }
 
-BwdPreWs bwd_pre_ws(const xhc_dims* d, char* ws) {
+BwdPreWs bwd_pre_ws(const xhc_dims* d, char* ws, bool fine) {
   const int64_t T = d->T;
   const int N = d->N, k = d->k, Kr = d->Kr, C = d->C;
   const int NA = k * Kr + k * k;
   const int64_t ncb = post_chunks(C);
-  const int64_t nf = nchunks(T, chunk_full(d)), na = nchunks(T, chunk_act(d));
+  const int64_t nf = nchunks(T, chunk_full(d, fine)), na = nchunks(T, chunk_act(d, fine));
   BwdPreWs w;
   w.part = reinterpret_cast<float*>(ws);
   w.tok = w.part + ncb * N * T;
@@ -2058,15 +2065,15 @@ BwdPreWs bwd_pre_ws(const xhc_dims* d, char* ws) {
 }
 
 bool bwd_rows_multi_supported(const xhc_dims* d, int Q) {
-  return d->state_dtype == XHC_BF16 && (d->N == 8 || d->N == 16) && bwd_rows_ring_supported((int64_t)d->N * d->C, d->C, chunk_full(d)) &&
-         (Q == 2 || Q == 4);
+  return d->state_dtype == XHC_BF16 && (d->N == 8 || d->N == 16) && (Q == 2 || Q == 4) &&
+         bwd_rows_ring_supported((int64_t)d->N * d->C, d->C, kMinRowChunk);   // (and so every longer chunk)
 }
 
 hipError_t launch_bwd_dhpre_multi(const xhc_dims* d, int Q, const void* X, const void* d_input, char* const* ws,
                                   hipStream_t s) {
   if (!bwd_rows_multi_supported(d, Q)) return hipErrorInvalidValue;
   MultiParts mp{};
-  for (int q = 0; q < Q; ++q) mp.part[q] = bwd_pre_ws(d, ws[q]).part;
+  for (int q = 0; q < Q; ++q) mp.part[q] = bwd_pre_ws(d, ws[q], true).part;   // (at the start in every layout)
   const dim3 g((unsigned)(d->T * post_chunks(d->C)));
   const uint16_t* x = reinterpret_cast<const uint16_t*>(X);
   const uint16_t* din = reinterpret_cast<const uint16_t*>(d_input);
@@ -2084,16 +2091,16 @@ size_t bwd_rows_multi_ws_bytes(const xhc_dims* d, int Q) {
 
 hipError_t launch_bwd_rows_multi(const xhc_dims* d, int Q, const void* X, void* dX, const float* W_r,
                                  const float* W_pre, const void* d_input, const float* const* hrd, char* const* ws,
-                                 char* pack_ws, hipStream_t s) {
+                                 char* pack_ws, bool fine, hipStream_t s) {
   if (!bwd_rows_multi_supported(d, Q)) return hipErrorInvalidValue;
   const int64_t T = d->T;
   const int N = d->N, C = d->C, NA = d->k * d->Kr + d->k * d->k;
   const int64_t NC = (int64_t)N * C;
   MultiRows m{};
   m.w[0] = W_r;
-  m.wout[0] = bwd_pre_ws(d, ws[0]).wpart_r;
+  m.wout[0] = bwd_pre_ws(d, ws[0], fine).wpart_r;
   for (int q = 0; q < Q; ++q) {
-    const BwdPreWs w = bwd_pre_ws(d, ws[q]);
+    const BwdPreWs w = bwd_pre_ws(d, ws[q], fine);
     m.tok[q] = w.tok;
     m.hrd[q] = hrd[q];
     m.din[q] = reinterpret_cast<const uint16_t*>(d_input) + (int64_t)q * T * C;
@@ -2133,17 +2140,17 @@ hipError_t launch_bwd_rows_multi(const xhc_dims* d, int Q, const void* X, void* 
   rd.srec = srec;
   rd.srec_stride = 8;
   rd.T = T;
-  rd.tchunk = chunk_full(d);
+  rd.tchunk = chunk_full(d, fine);
   rd.N = N;
   rd.C = C;
   return launch_bwd_rows_ring(rd, (int64_t)N * C, s);
 }
 
-size_t bwd_pre_ws_bytes(const xhc_dims* d) {
+size_t bwd_pre_ws_bytes(const xhc_dims* d, bool fine) {
   const int64_t T = d->T;
   const int N = d->N, k = d->k, Kr = d->Kr, C = d->C;
   const int NA = k * Kr + k * k;
-  const int64_t nf = nchunks(T, chunk_full(d)), na = nchunks(T, chunk_act(d));
+  const int64_t nf = nchunks(T, chunk_full(d, fine)), na = nchunks(T, chunk_act(d, fine));
   size_t n = (size_t)post_chunks(C) * N * T;                    // dH^pre partials
   n += (size_t)T * tok_floats(N, NA) + (size_t)T * (pg_floats(N, k, Kr) + N);
   n += (size_t)nf * N * C * N * 2;                               // dW_r, dW_pre partials
@@ -2178,7 +2185,7 @@ hipError_t launch_bwd_pre_tokens(const xhc_dims* d, const BwdPre* bs, int n, hip
   PreTokMulti ma{};
   for (int q = 0; q < n; ++q) {
     const BwdPre& b = bs[q];
-    const BwdPreWs w = bwd_pre_ws(d, b.ws);
+    const BwdPreWs w = bwd_pre_ws(d, b.ws, b.fine);
     PreTokArgs& ta = ma.a[q];
     ta.part = b.dense_rows ? w.part : nullptr;
     ta.nchunk = post_chunks(d->C);
@@ -2235,7 +2242,7 @@ hipError_t launch_bwd_pre_reduce(const xhc_dims* d, const BwdPre* bs, int n, hip
   if (n < 1 || n > kMultiMaxQ) return hipErrorInvalidValue;
   const int64_t T = d->T;
   const int N = d->N, k = d->k, Kr = d->Kr, C = d->C;
-  const int64_t nf = nchunks(T, chunk_full(d)), na = nchunks(T, chunk_act(d));
+  const int64_t nf = nchunks(T, chunk_full(d, bs[0].fine)), na = nchunks(T, chunk_act(d, bs[0].fine));
   const int64_t nfull = (int64_t)N * C * N, nact = (int64_t)k * C * 32;
   TokenSumsMulti ts{};
   ColSegs cs{};
@@ -2247,7 +2254,7 @@ hipError_t launch_bwd_pre_reduce(const xhc_dims* d, const BwdPre* bs, int n, hip
   };
   for (int q = 0; q < n; ++q) {
     const BwdPre& b = bs[q];
-    const BwdPreWs w = bwd_pre_ws(d, b.ws);
+    const BwdPreWs w = bwd_pre_ws(d, b.ws, b.fine);
     // (the MFMA row passes leave the token sum of mu r_ln dz_r in dW_r)
     float* const corr = b.dW_r && pre_mf(d) ? w.corr : nullptr;
     ts.a[q] = TokenSums{w.pg, b.dal_pre, b.dal_res, b.dal_post, b.db_pre, b.db_res, b.db_post, corr};
@@ -2266,8 +2273,8 @@ hipError_t launch_bwd_pre(const xhc_dims* d, const BwdPre& b, hipStream_t s) {
   const int64_t T = d->T;
   const int N = d->N, k = d->k, Kr = d->Kr, C = d->C;
   const int NA = k * Kr + k * k;
-  const int64_t cf = chunk_full(d), ca = chunk_act(d);
-  const BwdPreWs w = bwd_pre_ws(d, b.ws);
+  const int64_t cf = chunk_full(d, b.fine), ca = chunk_act(d, b.fine);
+  const BwdPreWs w = bwd_pre_ws(d, b.ws, b.fine);
   const void *const X = b.X, *const d_input = b.d_input, *const X_bf16 = b.X_bf16, *const act_din = b.act_din;
   void* const dX = b.dX;
   const float *const W_r = b.W_r, *const W_pre = b.W_pre, *const W_res = b.W_res, *const W_post = b.W_post;

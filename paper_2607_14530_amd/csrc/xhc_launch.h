@@ -156,16 +156,19 @@ hipError_t launch_post_apply(const PostPlan& plan, int state_dtype, void* X, con
                              void* input_next, void* Xact_save, hipStream_t s);
 
 // ---- backward
+// fine: the shorter runs and token chunks that few tokens run faster in.  They
+// leave more partials, so the caller sets it where its workspace holds the
+// bytes of *_ws_bytes(.., true); with the full lengths the need grows with T.
 hipError_t launch_bwd_post(const xhc_dims* d, const void* dXn, void* X, const void* Xact, const void* F,
                            const float* conv_w, const int32_t* idx, const float* p, const float* Hres,
                            const float* Hpost, void* dX, void* dF, float* dHres, float* dHpost, float* dp,
-                           float* dconv_w, char* ws, hipStream_t s, bool grad_f32, bool add_dp = false);
+                           float* dconv_w, char* ws, bool fine, hipStream_t s, bool grad_f32, bool add_dp = false);
 // (X null: the saved rows are not written back into X; grad_f32: dXn and dX
 // are fp32 whatever the state dtype, as the xHC-Flash active-row gradient;
 // add_dp: dp is added to)
-size_t bwd_post_ws_bytes(const xhc_dims* d);
+size_t bwd_post_ws_bytes(const xhc_dims* d, bool fine);
 bool bwd_pre_supported(const xhc_dims* d);
-size_t bwd_pre_ws_bytes(const xhc_dims* d);
+size_t bwd_pre_ws_bytes(const xhc_dims* d, bool fine);
 struct BwdPreWs {
   float *part, *tok, *pg, *wpart_r, *wpart_p, *wpart_a, *corr;
   uint16_t *dzf, *dza;   // packed dz' of the full-row and active-row MFMA passes
@@ -200,7 +203,7 @@ struct RowRingDesc {
 };
 bool bwd_rows_ring_supported(int64_t rows, int C, int64_t tchunk);
 hipError_t launch_bwd_rows_ring(const RowRingDesc& d, int64_t rows, hipStream_t s);
-BwdPreWs bwd_pre_ws(const xhc_dims* d, char* ws);   // layout of launch_bwd_pre's workspace
+BwdPreWs bwd_pre_ws(const xhc_dims* d, char* ws, bool fine);   // layout of launch_bwd_pre's workspace
 // One pre-map reverse; gradients whose pointer is null are not formed.
 struct BwdPre {
   const void* X;
@@ -219,6 +222,7 @@ struct BwdPre {
   float *dal_pre, *dal_res, *dal_post;
   float *db_pre, *db_res, *db_post;
   char* ws;
+  bool fine = true;   // (the same for all that run together)
   // [T, k]: dL/dH^pre of the active streams (slot order), in place of <d input, x_i> there
   const float* dhpre_act;
   // [T, N], written here when given: Hpre with the active streams zero, the
@@ -258,7 +262,7 @@ hipError_t launch_bwd_dhpre_multi(const xhc_dims* d, int Q, const void* X, const
                                   hipStream_t s);
 hipError_t launch_bwd_rows_multi(const xhc_dims* d, int Q, const void* X, void* dX, const float* W_r,
                                  const float* W_pre, const void* d_input, const float* const* hrd, char* const* ws,
-                                 char* pack_ws, hipStream_t s);
+                                 char* pack_ws, bool fine, hipStream_t s);
 
 // ---- xHC-Flash backward helpers
 hipError_t launch_fill0(void* p, size_t bytes, hipStream_t s);
