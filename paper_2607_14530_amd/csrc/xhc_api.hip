@@ -64,9 +64,12 @@ int64_t NC_of(const xhc_dims* d) { return (int64_t)d->N * d->C; }
 int64_t kC_of(const xhc_dims* d) { return (int64_t)d->k * d->C; }
 int64_t act_outs(const xhc_dims* d, int Kq, int with_res) { return (int64_t)d->k * Kq + (with_res ? d->k * d->k : 0); }
 
-size_t part_bytes(const xhc_dims* d, bool gather, int64_t K, int64_t nout) {
-  return align_up((size_t)proj_chunks(d->state_dtype, gather, K, d->C, nout, d->T) * (size_t)(out_blocks(nout) * 16 + 2) *
-                  (size_t)d->T * sizeof(float));
+int64_t chunks_of(const xhc_dims* d, bool gather, int64_t K, int64_t nout, bool fine) {
+  return proj_chunks(d->state_dtype, gather, K, d->C, nout, d->T, fine);
+}
+size_t part_bytes(const xhc_dims* d, bool gather, int64_t K, int64_t nout, bool fine) {
+  return align_up((size_t)chunks_of(d, gather, K, nout, fine) * (size_t)(out_blocks(nout) * 16 + 2) * (size_t)d->T *
+                  sizeof(float));
 }
 
 // partials of the larger projection, then the per-token sums of either one
@@ -89,28 +92,46 @@ bool pre_one_projection(const xhc_dims* d) {
 int64_t both_outs(const xhc_dims* d) {
   return 16 * (out_blocks(2 * d->N) + out_blocks(act_outs(d, d->Kr, 1)));
 }
-// partials of the larger projection (or of both in one), then the sums
-size_t pre_part_bytes(const xhc_dims* d) {
-  if (pre_one_projection(d)) return part_bytes(d, false, NC_of(d), both_outs(d));
-  return std::max(part_bytes(d, false, NC_of(d), 2 * d->N), part_bytes(d, true, kC_of(d), act_outs(d, d->Kr, 1)));
+// partials of the larger projection, or of both in one
+size_t pre_part_bytes(const xhc_dims* d, bool both, bool fine) {
+  if (both) return part_bytes(d, false, NC_of(d), both_outs(d), fine);
+  return std::max(part_bytes(d, false, NC_of(d), 2 * d->N, fine),
+                  part_bytes(d, true, kC_of(d), act_outs(d, d->Kr, 1), fine));
 }
-size_t pre_ws_multi(const xhc_dims* d) {
-  const size_t sums = pre_one_projection(d)
-                          ? sums_bytes(both_outs(d), d->T)
-                          : std::max(sums_bytes(2 * d->N, d->T), sums_bytes(act_outs(d, d->Kr, 1), d->T));
-  return kPreErrBytes + pre_part_bytes(d) + sums;
+// the same, then the sums
+size_t pre_ws_multi(const xhc_dims* d, bool both, bool fine) {
+  const size_t sums = both ? sums_bytes(both_outs(d), d->T)
+                           : std::max(sums_bytes(2 * d->N, d->T), sums_bytes(act_outs(d, d->Kr, 1), d->T));
+  return kPreErrBytes + pre_part_bytes(d, both, fine) + sums;
 }
 
-// The single-pass path may fall back to the multi-kernel path at run time
-// (device too small for its grid), so AUTO sizes for both.
-size_t pre_ws(const xhc_dims* d) {
-  size_t need = 0;
-  if (d->impl != XHC_IMPL_FUSED) need = pre_ws_multi(d);
-  if (d->impl == XHC_IMPL_AUTO ? fused_pre_auto(d) : (d->impl == XHC_IMPL_FUSED && fused_pre_supported(d))) {
-    const size_t f = fused_pre_ws_bytes(d);
-    need = need > f ? need : f;
+// How xhc_pre runs in a workspace of `avail` bytes: the single pass or the
+// multi-kernel path (AUTO also where the device cannot hold the single-pass
+// grid), the latter with one projection and short chunks where their partials
+// fit.  bytes: what the workspace query says; least: what has to be there (the
+// multi-kernel path's, two projections in long chunks; with the widths that
+// impl = FUSED takes the single pass's too).
+struct PrePlan {
+  bool single, both, fine;
+  size_t bytes, least;
+};
+PrePlan pre_plan(const xhc_dims* d, size_t avail) {
+  PrePlan p{};
+  const bool forced = d->impl == XHC_IMPL_FUSED;
+  if (!forced) {
+    const bool one = pre_one_projection(d);
+    p.bytes = pre_ws_multi(d, one, true);
+    p.least = pre_ws_multi(d, false, false);
+    p.fine = p.bytes <= avail;
+    p.both = one && p.fine;
   }
-  return need;
+  if (forced ? fused_pre_supported(d) : (d->impl == XHC_IMPL_AUTO && fused_pre_auto(d))) {
+    const size_t f = fused_pre_ws_bytes(d);
+    p.single = f <= avail;
+    p.bytes = std::max(p.bytes, f);
+    if (fused_pre_supported(d)) p.least = std::max(p.least, f);
+  }
+  return p;
 }
 
 // write-back components of sublayer q (1-based) of an xHC-Flash group:
@@ -119,9 +140,9 @@ size_t pre_ws(const xhc_dims* d) {
 // attention-side temporal augmentation)
 int flash_Kq(const xhc_dims* d, int q) { return (q % 2 == 1 && !d->attn_aug) ? 1 : d->Kr; }
 
-size_t flash_pre_ws(const xhc_dims* d, int Q) {
+size_t flash_pre_ws(const xhc_dims* d, int Q, bool fine) {
   const int64_t nf = (int64_t)(Q + 1) * d->N, na = act_outs(d, flash_Kq(d, 1), 0);
-  const size_t full = part_bytes(d, false, NC_of(d), nf), act = part_bytes(d, true, kC_of(d), na);
+  const size_t full = part_bytes(d, false, NC_of(d), nf, fine), act = part_bytes(d, true, kC_of(d), na, fine);
   const size_t sf = sums_bytes(nf, d->T), sa = sums_bytes(na, d->T);
   return (full > act ? full : act) + (sf > sa ? sf : sa);
 }
@@ -131,13 +152,13 @@ PostPlan plan_of(const xhc_dims* d, int Kq, size_t avail) {
 }
 
 // the projection of the next sublayer's mappings
-size_t flash_next_ws(const xhc_dims* d, int Q, int q) {
+size_t flash_next_ws(const xhc_dims* d, int Q, int q, bool fine) {
   if (q >= Q) return 0;
   const int64_t na = act_outs(d, flash_Kq(d, q + 1), q + 1 == Q);
-  return part_bytes(d, true, kC_of(d), na) + sums_bytes(na, d->T);
+  return part_bytes(d, true, kC_of(d), na, fine) + sums_bytes(na, d->T);
 }
 size_t flash_post_ws(const xhc_dims* d, int Q, int q) {
-  return std::max(plan_of(d, flash_Kq(d, q), SIZE_MAX).bytes, flash_next_ws(d, Q, q));
+  return std::max(plan_of(d, flash_Kq(d, q), SIZE_MAX).bytes, flash_next_ws(d, Q, q, true));
 }
 
 // ---- xHC-Flash backward: the per-sublayer reverse runs the single-sublayer
@@ -202,7 +223,7 @@ FlashPostBwdWs flash_post_bwd_ws(const xhc_dims* d, int Q, int q, bool fine) {
   FlashPostBwdWs w;
   w.post = c.take(bwd_post_ws_bytes(&r, fine));
   w.pre = c.take(bwd_pre_ws_bytes(&r, fine));
-  w.part = c.take(part_bytes(d, true, kC, na));
+  w.part = c.take(part_bytes(d, true, kC, na, fine));
   w.sums = c.take(sums_bytes(na, T));
   w.idx_id = c.take((size_t)T * k * sizeof(int32_t));
   w.hres_id = c.take((size_t)T * k * k * f);
@@ -239,7 +260,7 @@ FlashPreBwdWs flash_pre_bwd_ws(const xhc_dims* d, int Q, bool fine) {
   w.pre_slice = align_up(bwd_pre_ws_bytes(&e, fine));
   w.pre = c.take((w.fused ? Q : 1) * w.pre_slice);
   w.multi = c.take(w.fused ? bwd_rows_multi_ws_bytes(&e, Q) : 0);
-  w.part = c.take(part_bytes(d, false, NC, nf));
+  w.part = c.take(part_bytes(d, false, NC, nf, fine));
   w.sums = c.take(sums_bytes(nf, T));
   w.saved = c.take((size_t)(w.fused ? Q : 1) * T * saved_floats(N, k, 1) * f);   // used where none is given
   w.idx_s = c.take((size_t)T * k * sizeof(int32_t));
@@ -383,11 +404,11 @@ xhc_status xhc_pack_active(const xhc_dims* d, int32_t Kq, const float* W_post, c
 size_t xhc_workspace_bytes(const xhc_dims* d, int32_t op, int32_t Q) {
   if (check_dims(d) != XHC_OK) return 0;
   switch (op) {
-    case XHC_OP_PRE: return pre_ws(d);
+    case XHC_OP_PRE: return pre_plan(d, SIZE_MAX).bytes;
     case XHC_OP_POST: return plan_of(d, d->Kr, SIZE_MAX).bytes;
     case XHC_OP_POST_BWD: return bwd_post_ws_bytes(d, true);
     case XHC_OP_PRE_BWD: return bwd_pre_supported(d) ? bwd_pre_ws_bytes(d, true) : 0;
-    case XHC_OP_FLASH_PRE: return (Q == 2 || Q == 4) ? flash_pre_ws(d, Q) : 0;
+    case XHC_OP_FLASH_PRE: return (Q == 2 || Q == 4) ? flash_pre_ws(d, Q, true) : 0;
     case XHC_OP_FLASH_POST: {
       if (Q != 2 && Q != 4) return 0;
       size_t need = 0;
@@ -425,10 +446,11 @@ xhc_status xhc_pre(const xhc_dims* d, const void* X, const void* packed_full, co
       !aligned16(workspace))
     return XHC_EUNSUPPORTED;
   if (d->impl == XHC_IMPL_FUSED && !fused_pre_supported(d)) return XHC_EUNSUPPORTED;
-  if (workspace_bytes < pre_ws(d)) return XHC_EWORKSPACE;
+  const PrePlan plan = pre_plan(d, workspace_bytes);
+  if (workspace_bytes < plan.least) return XHC_EWORKSPACE;
   // AUTO takes the single-pass kernel where it applies (it reads X once) and
   // the multi-kernel path elsewhere
-  if (d->impl == XHC_IMPL_AUTO && !fused_pre_auto(d)) {
+  if (d->impl == XHC_IMPL_AUTO && !plan.single) {
     xhc_dims m = *d;
     m.impl = XHC_IMPL_MULTI;
     return xhc_pre(&m, X, packed_full, packed_act, alpha, b_pre, b_res, b_post, input, idx, p, Hpre, Hres, Hpost,
@@ -437,7 +459,8 @@ xhc_status xhc_pre(const xhc_dims* d, const void* X, const void* packed_full, co
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   clear_stale_error();
   float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + kPreErrBytes);
-  float* sums = reinterpret_cast<float*>(reinterpret_cast<char*>(part) + pre_part_bytes(d));
+  const bool both = plan.both, fine = plan.fine;
+  float* sums = reinterpret_cast<float*>(reinterpret_cast<char*>(part) + pre_part_bytes(d, both, fine));
   const int64_t NC = NC_of(d), kC = kC_of(d);
   const int64_t nout_full = 2 * d->N, nout_act = act_outs(d, d->Kr, 1);
   const int nsave = saved_floats(d->N, d->k, d->Kr);
@@ -456,16 +479,16 @@ xhc_status xhc_pre(const xhc_dims* d, const void* X, const void* packed_full, co
     clear_stale_error();
   }
   XHC_STEP("pre_clear", launch_fill0(workspace, kPreErrBytes, s));   // no waits here: no failures
-  const bool both = pre_one_projection(d);
   const int64_t nfirst = both ? both_outs(d) : nout_full;   // outputs of the first pass
   if (both)
-    XHC_STEP("proj_both", launch_proj_both(X, d->T, d->N, d->C, packed_full, nout_full, packed_act, nout_act, part, s));
+    XHC_STEP("proj_both", launch_proj_both(X, d->T, d->N, d->C, packed_full, nout_full, packed_act, nout_act, fine,
+                                           part, s));
   else
     XHC_STEP("proj_full", launch_proj_partial(d->state_dtype, X, d->T, d->N, d->C, NC, packed_full, nout_full,
-                                              nullptr, d->k, part, s));
-  XHC_STEP("pre_route", launch_pre_route(part, proj_chunks(d->state_dtype, false, NC, d->C, nfirst, d->T), nfirst, d->T,
-                                         d->N, d->m, d->k, 1, d->C, colsum, alpha, 1, b_pre, d->eps, idx, p, Hpre,
-                                         sums, saved, nsave, nsave - 4, d->router, s));
+                                              nullptr, d->k, fine, part, s));
+  XHC_STEP("pre_route", launch_pre_route(part, chunks_of(d, false, NC, nfirst, fine), nfirst, d->T, d->N, d->m,
+                                         d->k, 1, d->C, colsum, alpha, 1, b_pre, d->eps, idx, p, Hpre, sums, saved,
+                                         nsave, nsave - 4, d->router, s));
   // the active outputs' partials: the sums of the first pass behind its own
   // outputs (one chunk, the moments last in both), or a pass of their own
   const float* apart = part;
@@ -474,8 +497,8 @@ xhc_status xhc_pre(const xhc_dims* d, const void* X, const void* packed_full, co
     apart = sums + 16 * out_blocks(nout_full) * d->T;
   } else {
     XHC_STEP("proj_active", launch_proj_partial(d->state_dtype, X, d->T, d->N, d->C, kC, packed_act, nout_act, idx,
-                                                d->k, part, s));
-    achunks = proj_chunks(d->state_dtype, true, kC, d->C, nout_act, d->T);
+                                                d->k, fine, part, s));
+    achunks = chunks_of(d, true, kC, nout_act, fine);
   }
   XHC_STEP("pre_coef", launch_pre_coef(apart, achunks, nout_act, d->T, d->k, d->Kr, 1, d->C, alpha + 2, alpha + 1,
                                        b_post, b_res, d->eps, d->sinkhorn_iters, d->clamp_delta, Hpost, Hres, sums,
@@ -538,7 +561,8 @@ xhc_status xhc_flash_pre(const xhc_dims* d, int32_t Q, const void* X, const void
     return XHC_EINVAL;
   if (!aligned16(X) || !aligned16(input1) || !aligned16(base) || !aligned16(packed_full) || !aligned16(packed_act1))
     return XHC_EUNSUPPORTED;
-  if (workspace_bytes < flash_pre_ws(d, Q)) return XHC_EWORKSPACE;
+  if (workspace_bytes < flash_pre_ws(d, Q, false)) return XHC_EWORKSPACE;
+  const bool fine = workspace_bytes >= flash_pre_ws(d, Q, true);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   clear_stale_error();
   const int64_t NC = NC_of(d), kC = kC_of(d);
@@ -546,26 +570,28 @@ xhc_status xhc_flash_pre(const xhc_dims* d, int32_t Q, const void* X, const void
   const int64_t nf = (int64_t)(Q + 1) * d->N, na = act_outs(d, K1, 0);
   float* part = reinterpret_cast<float*>(workspace);
   float* sums = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) +
-                                         std::max(part_bytes(d, false, NC, nf), part_bytes(d, true, kC, na)));
+                                         std::max(part_bytes(d, false, NC, nf, fine),
+                                                  part_bytes(d, true, kC, na, fine)));
   const float* colsum = reinterpret_cast<const float*>(reinterpret_cast<const char*>(packed_full) +
                                                        packed_frag_bytes(NC, nf));
   hipError_t e = hipSuccess;
   XHC_STEP("flash_proj_full",
-           launch_proj_partial(d->state_dtype, X, d->T, d->N, d->C, NC, packed_full, nf, nullptr, d->k, part, s));
+           launch_proj_partial(d->state_dtype, X, d->T, d->N, d->C, NC, packed_full, nf, nullptr, d->k, fine, part,
+                               s));
   // the records the backward reads (one per pre-map; fields it does not use stay zero)
   const int nsave = saved_floats(d->N, d->k, 1);
   if (saved) XHC_STEP("flash_save_zero", launch_fill0(saved, (size_t)Q * d->T * nsave * sizeof(float), s));
-  XHC_STEP("flash_route", launch_pre_route(part, proj_chunks(d->state_dtype, false, NC, d->C, nf, d->T), nf, d->T, d->N, d->m, d->k, Q, d->C, colsum,
-                                           alpha_pre, 1, b_pre, d->eps, idx, p, Hpre, sums, saved,
+  XHC_STEP("flash_route", launch_pre_route(part, chunks_of(d, false, NC, nf, fine), nf, d->T, d->N, d->m, d->k, Q, d->C,
+                                           colsum, alpha_pre, 1, b_pre, d->eps, idx, p, Hpre, sums, saved,
                                            saved ? nsave : 0, saved ? nsave - 4 : 0, d->router, s, -1));
   XHC_STEP("flash_proj_active",
-           launch_proj_partial(d->state_dtype, X, d->T, d->N, d->C, kC, packed_act1, na, idx, d->k, part, s));
+           launch_proj_partial(d->state_dtype, X, d->T, d->N, d->C, kC, packed_act1, na, idx, d->k, fine, part, s));
   // sublayer 1's mapping record for the backward (the layout its reverse uses)
   const int nsave1 = saved_floats(d->k, d->k, K1);
   if (saved_act1)
     XHC_STEP("flash_save_zero", launch_fill0(saved_act1, (size_t)d->T * nsave1 * sizeof(float), s));
-  XHC_STEP("flash_coef1", launch_pre_coef(part, proj_chunks(d->state_dtype, true, kC, d->C, na, d->T), na, d->T,
-                                          d->k, K1, 0, d->C, alpha_post1, nullptr, b_post1, nullptr, d->eps,
+  XHC_STEP("flash_coef1", launch_pre_coef(part, chunks_of(d, true, kC, na, fine), na, d->T, d->k, K1, 0, d->C,
+                                          alpha_post1, nullptr, b_post1, nullptr, d->eps,
                                           d->sinkhorn_iters, d->clamp_delta, Hpost1, nullptr, sums, saved_act1,
                                           saved_act1 ? nsave1 : 0, 2 * d->k, nsave1 - 2, s));
   XHC_STEP("flash_dense_read",
@@ -597,8 +623,9 @@ xhc_status xhc_flash_post(const xhc_dims* d, int32_t Q, int32_t q, void* X, cons
   if (!aligned16(X) || !aligned16(F) || (conv_w && !aligned16(conv_w)) || (Xact_save && !aligned16(Xact_save)))
     return XHC_EUNSUPPORTED;
   const PostPlan plan = plan_of(d, Kq, workspace_bytes);
-  const size_t need = std::max(plan.least, flash_next_ws(d, Q, q));
+  const size_t need = std::max(plan.least, flash_next_ws(d, Q, q, false));
   if (need > 0 && (!workspace || workspace_bytes < need)) return XHC_EWORKSPACE;
+  const bool fine = workspace_bytes >= flash_next_ws(d, Q, q, true);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   clear_stale_error();
   hipError_t e = hipSuccess;
@@ -621,14 +648,15 @@ xhc_status xhc_flash_post(const xhc_dims* d, int32_t Q, int32_t q, void* X, cons
     const int with_res = (q + 1 == Q);
     const int64_t kC = kC_of(d), na = act_outs(d, Kn, with_res);
     float* part = reinterpret_cast<float*>(workspace);
-    float* sums = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + part_bytes(d, true, kC, na));
+    float* sums = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + part_bytes(d, true, kC, na, fine));
     XHC_STEP("flash_proj_next",
-             launch_proj_partial(d->state_dtype, X, d->T, d->N, d->C, kC, packed_act_next, na, idx, d->k, part, s));
+             launch_proj_partial(d->state_dtype, X, d->T, d->N, d->C, kC, packed_act_next, na, idx, d->k, fine, part,
+                                 s));
     const int nsn = saved_floats(d->k, d->k, Kn);   // the next sublayer's mapping record
     if (saved_next)
       XHC_STEP("flash_save_zero", launch_fill0(saved_next, (size_t)d->T * nsn * sizeof(float), s));
     XHC_STEP("flash_coef_next",
-             launch_pre_coef(part, proj_chunks(d->state_dtype, true, kC, d->C, na, d->T), na, d->T, d->k, Kn, with_res, d->C, alpha_next,
+             launch_pre_coef(part, chunks_of(d, true, kC, na, fine), na, d->T, d->k, Kn, with_res, d->C, alpha_next,
                              with_res ? alpha_next + 1 : nullptr, b_post_next, b_res_next, d->eps, d->sinkhorn_iters,
                              d->clamp_delta, Hpost_next, Hres_next, sums, saved_next, saved_next ? nsn : 0,
                              2 * d->k, nsn - 2, s));
@@ -797,9 +825,9 @@ xhc_status xhc_flash_post_bwd(const xhc_dims* d, int32_t Q, int32_t q, const voi
   const float* rec = saved_act ? saved_act : F32(w.saved);
   if (!saved_act) {
     XHC_STEP("fbwd_proj", launch_proj_partial(d->state_dtype, Xact, T, (int)k, (int)C, kC, packed_act, na, idx_id,
-                                              (int)k, F32(w.part), s));
-    XHC_STEP("fbwd_coef", launch_pre_coef(F32(w.part), proj_chunks(d->state_dtype, true, kC, (int)C, na, T), na, T,
-                                          (int)k, Kq, last, C, alpha_post, last ? alpha_res : nullptr, b_post,
+                                              (int)k, fine, F32(w.part), s));
+    XHC_STEP("fbwd_coef", launch_pre_coef(F32(w.part), chunks_of(d, true, kC, na, fine), na, T, (int)k, Kq, last, C,
+                                          alpha_post, last ? alpha_res : nullptr, b_post,
                                           last ? b_res : nullptr, d->eps, d->sinkhorn_iters, d->clamp_delta,
                                           F32(w.hpost_re), last ? F32(w.hres_re) : nullptr, F32(w.sums), F32(w.saved),
                                           nsave, 2 * (int)k, nsave - 2, s));
@@ -879,7 +907,7 @@ xhc_status xhc_flash_pre_bwd(const xhc_dims* d, int32_t Q, const void* X, const 
   // recomputed as the forward made them
   if (!saved)
     XHC_STEP("fpbwd_proj", launch_proj_partial(d->state_dtype, X, T, (int)N, (int)C, NC, packed_full, nf, nullptr,
-                                               (int)k, F32(w.part), s));
+                                               (int)k, fine, F32(w.part), s));
   // dL/dX starts as the gradient of the state after the group: the untouched
   // streams pass it through, the active ones carry the reverse of the group
   XHC_STEP("fpbwd_scatter", launch_fbwd_scatter(d->state_dtype, T, (int)N, (int)k, (int)C, idx,
@@ -924,8 +952,8 @@ xhc_status xhc_flash_pre_bwd(const xhc_dims* d, int32_t Q, const void* X, const 
   }
   // the logits of pre-map q, where the forward has not saved them
   auto recompute = [&](int q) -> hipError_t {
-    return launch_pre_route(F32(w.part), proj_chunks(d->state_dtype, false, NC, (int)C, nf, T), nf, T,
-                            (int)N, d->m, (int)k, Q, C, colsum, alpha_pre, 1, b_pre, d->eps,
+    return launch_pre_route(F32(w.part), chunks_of(d, false, NC, nf, fine), nf, T, (int)N, d->m, (int)k, Q, C,
+                            colsum, alpha_pre, 1, b_pre, d->eps,
                             reinterpret_cast<int32_t*>(ws + w.idx_s), F32(w.p_s), F32(w.hpre_s), F32(w.sums),
                             const_cast<float*>(bp[q].saved), nsave, nsave - 4, d->router, s, q);
   };

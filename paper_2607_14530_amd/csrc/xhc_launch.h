@@ -57,7 +57,9 @@ constexpr int kWideStep = 4;   // k-blocks per step of the wide path
 // one step from five blocks on (40 KiB at five, more workgroups per CU;
 // measured faster for the router-plus-pre projection of the Flash group)
 __host__ __device__ constexpr int wide_seg_steps(int nob) { return nob <= 4 ? 4 : 1; }
-inline ProjPlan proj_plan(int state_dtype, bool gather, int64_t K, int C, int64_t nout, int64_t T) {
+// fine: short chunks where few tokens run faster in them.  They leave more
+// partials, so the caller sets it where its workspace holds those.
+inline ProjPlan proj_plan(int state_dtype, bool gather, int64_t K, int C, int64_t nout, int64_t T, bool fine) {
   const int64_t nblk = K / 32, NO = out_blocks(nout) * 16 + 2;
   const bool wide = (gather ? act_grouped(state_dtype, C) : full_grouped(state_dtype, K)) && out_blocks(nout) <= 8;
   int tg = 4;
@@ -73,7 +75,7 @@ inline ProjPlan proj_plan(int state_dtype, bool gather, int64_t K, int C, int64_
   // chunks instead of 80: 69 -> 73 us).
   const auto at_gran = [&](int64_t g) { return (nblk + g - 1) / g; };
   int64_t gran = 32;
-  while (wide && gran > 8 && at_gran(gran) <= 64 && tiles * at_gran(gran / 2) <= 256) gran /= 2;
+  while (fine && wide && gran > 8 && at_gran(gran) <= 64 && tiles * at_gran(gran / 2) <= 256) gran /= 2;
   // chunks for about 1024 workgroups, 512 for five or more output blocks and
   // 256 for the gathered active rows (longer chunks, fewer weight fills and
   // pipeline starts per byte: measured faster there)
@@ -85,20 +87,20 @@ inline ProjPlan proj_plan(int state_dtype, bool gather, int64_t K, int C, int64_
   cb = (cb + gran - 1) / gran * gran;
   return ProjPlan{wide, tg, cb, (nblk + cb - 1) / cb};
 }
-inline int64_t proj_chunks(int state_dtype, bool gather, int64_t K, int C, int64_t nout, int64_t T) {
-  return proj_plan(state_dtype, gather, K, C, nout, T).nchunk;
+inline int64_t proj_chunks(int state_dtype, bool gather, int64_t K, int C, int64_t nout, int64_t T, bool fine) {
+  return proj_plan(state_dtype, gather, K, C, nout, T, fine).nchunk;
 }
 
 hipError_t launch_proj_partial(int state_dtype, const void* X, int64_t T, int N, int C, int64_t K,
                                const void* packed, int64_t nout, const int32_t* idx, int k,
-                               float* part, hipStream_t s);
+                               bool fine, float* part, hipStream_t s);
 // Both projections of a sublayer whose N streams are all active and fixed, in
 // one read of the state: its active rows are the state's own rows in order
 // (slot j is stream j), so [W_post | W_res] has the rows of [W_r | W_pre].
 // Partials as of out_blocks(nout_full) + out_blocks(nout_act) output blocks.
 // bf16 state, C % 128 == 0.
 hipError_t launch_proj_both(const void* X, int64_t T, int N, int C, const void* packed_full, int64_t nout_full,
-                            const void* packed_act, int64_t nout_act, float* part, hipStream_t s);
+                            const void* packed_act, int64_t nout_act, bool fine, float* part, hipStream_t s);
 hipError_t launch_pre_route(const float* part, int64_t nchunk, int64_t nout, int64_t T, int N, int m, int k,
                             int npre, int64_t C, const float* colsum, const float* alpha_pre, int alpha_stride,
                             const float* b_pre, float eps, int32_t* idx, float* p, float* Hpre, float* sums,

@@ -412,8 +412,8 @@ static hipError_t proj_wide_launch(const uint16_t* X, int64_t T, int N, int C, i
 
 template <typename TS, bool GATHER>
 static hipError_t proj_dispatch(const TS* X, int64_t T, int N, int C, int64_t K, const void* packed, int64_t nout,
-                                const int32_t* idx, int k, float* part, hipStream_t s) {
-  const ProjPlan pl = proj_plan(Vec8<TS>::kSplit ? XHC_F32 : XHC_BF16, GATHER, K, C, nout, T);
+                                const int32_t* idx, int k, bool fine, float* part, hipStream_t s) {
+  const ProjPlan pl = proj_plan(Vec8<TS>::kSplit ? XHC_F32 : XHC_BF16, GATHER, K, C, nout, T, fine);
   const uint4* w = reinterpret_cast<const uint4*>(packed);
   const int nob = (int)out_blocks(nout);
   if (nob > 8) return hipErrorInvalidValue;
@@ -434,11 +434,11 @@ static hipError_t proj_dispatch(const TS* X, int64_t T, int N, int C, int64_t K,
 }
 
 hipError_t launch_proj_both(const void* X, int64_t T, int N, int C, const void* packed_full, int64_t nout_full,
-                            const void* packed_act, int64_t nout_act, float* part, hipStream_t s) {
+                            const void* packed_act, int64_t nout_act, bool fine, float* part, hipStream_t s) {
   if (T == 0) return hipSuccess;
   const int nob = (int)(out_blocks(nout_full) + out_blocks(nout_act));
   const int64_t K = (int64_t)N * C;
-  const ProjPlan pl = proj_plan(XHC_BF16, false, K, C, 16 * nob, T);
+  const ProjPlan pl = proj_plan(XHC_BF16, false, K, C, 16 * nob, T, fine);
   if (!pl.wide || out_blocks(nout_full) != 1) return hipErrorInvalidValue;
   return proj_wide_launch<false>(reinterpret_cast<const uint16_t*>(X), T, N, C, K, pl,
                                  reinterpret_cast<const uint4*>(packed_full),
@@ -446,17 +446,17 @@ hipError_t launch_proj_both(const void* X, int64_t T, int N, int C, const void* 
 }
 
 hipError_t launch_proj_partial(int state_dtype, const void* X, int64_t T, int N, int C, int64_t K,
-                               const void* packed, int64_t nout, const int32_t* idx, int k, float* part,
-                               hipStream_t s) {
+                               const void* packed, int64_t nout, const int32_t* idx, int k, bool fine,
+                               float* part, hipStream_t s) {
   if (T == 0) return hipSuccess;
   if (state_dtype == XHC_BF16) {
     const uint16_t* x = reinterpret_cast<const uint16_t*>(X);
-    return idx ? proj_dispatch<uint16_t, true>(x, T, N, C, K, packed, nout, idx, k, part, s)
-               : proj_dispatch<uint16_t, false>(x, T, N, C, K, packed, nout, idx, k, part, s);
+    return idx ? proj_dispatch<uint16_t, true>(x, T, N, C, K, packed, nout, idx, k, fine, part, s)
+               : proj_dispatch<uint16_t, false>(x, T, N, C, K, packed, nout, idx, k, fine, part, s);
   }
   const float* x = reinterpret_cast<const float*>(X);
-  return idx ? proj_dispatch<float, true>(x, T, N, C, K, packed, nout, idx, k, part, s)
-             : proj_dispatch<float, false>(x, T, N, C, K, packed, nout, idx, k, part, s);
+  return idx ? proj_dispatch<float, true>(x, T, N, C, K, packed, nout, idx, k, fine, part, s)
+             : proj_dispatch<float, false>(x, T, N, C, K, packed, nout, idx, k, fine, part, s);
 }
 
 }  // namespace xhc

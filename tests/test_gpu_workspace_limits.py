@@ -1,13 +1,15 @@
-"""The backward in the least workspace that its entry points take, smaller than
-what the query names: the full lengths of runs and token chunks (and, at N = 8,
-the group's entry reverse map by map).  The results are those of the preferred
-lengths to the order of the sums, and nothing is written past the end."""
+"""The entry points in the least workspace that they take, smaller than what
+the query names: the full lengths of runs and chunks, at N = 8 the group's entry
+reverse map by map, a dense sublayer's mappings from two projections, the
+multi-kernel pre instead of the single pass.  The results are those of the
+preferred forms to the order of the sums, and nothing is written past the end."""
 
 import pytest
 import torch
 
 from paper_2607_14530_amd import synth
 from paper_2607_14530_amd import xhc as X
+from tests.parity_util import check_sublayer
 
 pytestmark = pytest.mark.gpu
 
@@ -86,3 +88,40 @@ def test_group_backward(T, S, N, C, Q, recompute):
         l.check()
     # map by map the gradient rows are rounded to bf16 Q + 1 times (2^-9 of an element each)
     assert_same(got, ref, w.name, bf16=(Q + 1) ** 0.5 * 2.0 ** -9)
+
+
+# short chunks of the projection; both mappings of a dense sublayer from one pass; the single pass
+@pytest.mark.parametrize("T,N,k,m,C", [(512, 32, 4, 2, 1024), (1000, 4, 4, 4, 1024), (300, 16, 4, 2, 2112)])
+def test_sublayer_forward(T, N, k, m, C):
+    w = synth.Workload(T=T, S=T, N=N, k=k, m=m, C=C, Kr=4, name=f"wslim-pre-T{T}-N{N}-C{C}")
+    print(f"[ws] {w.name}", flush=True)
+    inp = synth.sublayer_inputs(w, 35, device="cuda")
+    sub = X.Sublayer(X.dims_for(w), inp, "cuda")
+    least = Least(sub, "ws_pre", lambda: sub.pre(inp["X"]))
+    after = inp["X"].clone()
+    sub.pre(after)
+    sub.post(after, inp["F"])
+    torch.cuda.synchronize()
+    least.check()
+    tok = torch.arange(0, T, max(1, T // 64), device="cuda")
+    check_sublayer(sub, inp, w, inp["X"][tok], after[tok], tokens=tok)
+
+
+@pytest.mark.parametrize("T,N,C,Q", [(512, 16, 2048, 4), (600, 8, 1024, 2)])
+def test_group_forward(T, N, C, Q):
+    w = synth.Workload(T=T, S=T, N=N, k=4, m=2, C=C, Kr=4, name=f"wslim-group-T{T}-N{N}-Q{Q}")
+    print(f"[ws] {w.name}", flush=True)
+    d = synth.flash_inputs(w, Q, 37, device="cuda")
+    grp = X.FlashGroup(X.dims_for(w), Q, d, "cuda")
+    names = ("idx", "p", "Hpre", "Hres", "base")
+    out = lambda st: dict({n: getattr(grp, n).clone() for n in names}, X=st, inputs=[v.clone() for v in grp.inputs],
+                          Hpost=[v.clone() for v in grp.Hpost])
+    ref = out(grp.run(d["X"].clone(), d["F_list"]))
+    least = [Least(grp, "ws_pre", lambda: grp.pre(d["X"]))]
+    least.append(Least(grp, "ws_post", lambda: grp.run(d["X"].clone(), d["F_list"])))
+    got = out(grp.run(d["X"].clone(), d["F_list"]))
+    torch.cuda.synchronize()
+    for l in least:
+        l.check()
+    assert torch.equal(got.pop("idx"), ref.pop("idx")), "routing differs (near-tie seed?)"
+    assert_same(got, ref, w.name)
