@@ -88,14 +88,25 @@ typedef struct xhc_dims {
  * the stream's score.                                                      */
 typedef enum { XHC_ROUTER_SIGMOID = 0, XHC_ROUTER_SOFTMAX = 1 } xhc_router;
 
-/* Kernel selection for xhc_pre.  AUTO takes the single-pass cooperative
- * kernel where it applies (bf16 state, N = 16, k = 4, C <= 4096) and the
- * multi-kernel path elsewhere, or when the device cannot hold the single-pass
- * grid.  MULTI forces the multi-kernel path.  FUSED forces the single-pass
- * kernel at C = 128 G with G dividing 32 and returns XHC_EUNSUPPORTED
- * elsewhere.  All give the same results within rounding.  If a wait of the
- * single-pass kernel ever gives up (bounded spin), H^post and H^res come out
- * as NaN rather than as silently wrong values.                              */
+/* Kernel selection for xhc_pre.  AUTO takes the single-pass kernel where it
+ * applies (bf16 state, N = 16, k = 4, C <= 4096) and the multi-kernel path
+ * elsewhere, or when the device cannot hold the single-pass grid.  MULTI forces
+ * the multi-kernel path.  FUSED forces the single-pass kernel at C = 128 G with
+ * G dividing 32 and returns XHC_EUNSUPPORTED elsewhere.  All give the same
+ * results within rounding.
+ *
+ * The single pass splits a tile of 16 tokens over a team of ceil(C / 128)
+ * workgroups (at most 32) that wait for one another; every wait is bounded.
+ * Its launch is a plain one where the launches this process can have in
+ * flight leave room on the chip whatever they hold, and cooperative elsewhere
+ * (streams of another priority or with a CU mask, HSA_CU_MASK or
+ * ROC_GLOBAL_CU_MASK set, GPU_MAX_HW_QUEUES above 7); under capture the stream
+ * captured decides.  Not counted are the launches of other processes: where
+ * several share the GPU and nine or more single-pass launches can be in flight
+ * at once, their unfinished teams could hold every CU until waits give up.
+ * Programs that share a GPU so take MULTI, which waits for nothing.
+ * If a wait ever gives up, H^post and H^res come out as NaN rather than as
+ * silently wrong values.                                                    */
 typedef enum { XHC_IMPL_AUTO = 0, XHC_IMPL_MULTI = 1, XHC_IMPL_FUSED = 2 } xhc_impl;
 
 /* Name of a status code, and the name of the HIP error behind the last

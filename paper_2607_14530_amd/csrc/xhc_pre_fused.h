@@ -39,9 +39,9 @@
 // either.  Teams form in the
 // order in which workgroups start (a ticket), so a launch has at most one team
 // that waits for members not yet started; the others run to their end and
-// free their CUs, and the last team then starts (see plain_launch for when
-// the launch is cooperative instead).  Every wait is bounded, so every wave
-// exits.
+// free their CUs, and the last team then starts (see xhc_plain_launch.h for
+// when the launch is cooperative instead, and for what it cannot count).
+// Every wait is bounded, so every wave exits.
 //
 // SHORT: C is no multiple of 128 or the team is larger than the width needs
 // (an instance of its own: the exact one then has no trace of the zero

@@ -1,7 +1,6 @@
 // Launch of the single-pass pre (xhc_pre_fused.h), and its instances for widths
 // that fill their team.
-#include <stdlib.h>
-
+#include "xhc_plain_launch.h"
 #include "xhc_pre_fused.h"
 
 namespace xhc {
@@ -62,25 +61,10 @@ DeviceInfo device_info(int C) {
   return slot;
 }
 
-// Whether the launch may be a plain one.  A team waits for its members, so
-// launches in flight together must not fill the chip with unfinished teams
-// only: each has at most one (G - 1 workgroups), and HIP runs at most one
-// kernel per hardware queue at a time, 4 queues unless GPU_MAX_HW_QUEUES says
-// otherwise (streams of another priority have queues of their own).  With room
-// for 8 such teams beside one more workgroup the launch is plain; else it is
-// cooperative, which costs about 20 us more (T = 16, C = 4096: 54 against 36 us a
-// call, of which the kernels are 35).
-bool plain_launch(int G, int slots, hipStream_t s) {
-  constexpr int kQueues = 8;
-  static const int queues = [] {
-    const char* v = getenv("GPU_MAX_HW_QUEUES");
-    return v && *v ? atoi(v) : 4;
-  }();
-  if (queues < 1 || queues > kQueues || kQueues * (G - 1) >= slots) return false;
-  int prio = 0;
-  if (s && hipStreamGetPriority(s, &prio) != hipSuccess) return false;
-  return prio == 0;
-}
+struct StreamApi {
+  static hipError_t priority(hipStream_t s, int* prio) { return hipStreamGetPriority(s, prio); }
+  static hipError_t cu_mask(hipStream_t s, int words, uint32_t* mask) { return hipExtStreamGetCUMask(s, words, mask); }
+};
 
 }  // namespace
 
@@ -144,7 +128,8 @@ hipError_t launch_pre_fused(const xhc_dims* d, const void* X, const void* packed
   a.saved = saved;
   a.nsave = saved_floats(FN, FK, d->Kr);
   a.err = reinterpret_cast<int*>(w);
-  const bool plain = plain_launch(G, di.cus * di.per_cu, s);
+  static const ProcessQueues queues = process_queues();
+  const bool plain = plain_launch<StreamApi>(G, di.cus, di.per_cu, queues, s);
   a.ticket = plain ? reinterpret_cast<int*>(w + 128) : nullptr;
   a.rec1 = reinterpret_cast<uint64_t*>(w + 256);
   a.rec2 = reinterpret_cast<uint64_t*>(w + 256 + align256(rec1_words(d) * 8));
