@@ -47,8 +47,10 @@ bool stream_has_whole_chip(hipStream_t s, int cus) {
   constexpr int kWords = 32;
   uint32_t mask[kWords] = {};
   int prio = 0;
-  if (cus > 32 * kWords || Api::priority(s, &prio) != hipSuccess || Api::cu_mask(s, kWords, mask) != hipSuccess)
+  if (cus > 32 * kWords || Api::priority(s, &prio) != hipSuccess || Api::cu_mask(s, kWords, mask) != hipSuccess) {
+    Api::clear_error();   // (the launch's own check would report it)
     return false;
+  }
   int n = 0;
   for (uint32_t w : mask) n += __builtin_popcount(w);
   return prio == 0 && n >= cus;

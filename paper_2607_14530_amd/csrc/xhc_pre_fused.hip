@@ -64,6 +64,7 @@ DeviceInfo device_info(int C) {
 struct StreamApi {
   static hipError_t priority(hipStream_t s, int* prio) { return hipStreamGetPriority(s, prio); }
   static hipError_t cu_mask(hipStream_t s, int words, uint32_t* mask) { return hipExtStreamGetCUMask(s, words, mask); }
+  static void clear_error() { (void)hipGetLastError(); }
 };
 
 }  // namespace

@@ -25,6 +25,7 @@ struct FakeApi {
     for (int i = 0; i < g_bits && i < 32 * words; ++i) mask[i / 32] |= 1u << (i % 32);
     return hipSuccess;
   }
+  static void clear_error() { g_errors = 0; }
 };
 
 int main() {

@@ -2,7 +2,7 @@
 CPU (tests/host/plain_launch.cpp): the launches that may be in flight together
 leave a workgroup's room on the chip beside their unfinished teams, and a
 stream that has not the whole chip, or cannot be asked, is launched
-cooperatively."""
+cooperatively with no error left behind."""
 
 import os
 import shutil
@@ -57,8 +57,9 @@ def test_a_masked_process_is_not(rule):
     assert not rule(ROC_GLOBAL_CU_MASK="0xffff")[0]
 
 
-def test_a_stream_that_cannot_be_asked_is_not(rule):
-    assert not rule(prio_status=1)[0] and not rule(mask_status=1)[0]
+def test_a_stream_that_cannot_be_asked_leaves_no_error(rule):
+    assert rule(prio_status=1) == (False, 1, 0)
+    assert rule(mask_status=1) == (False, 2, 0)
 
 
 def test_unfinished_teams_leave_room(rule):
