@@ -159,18 +159,9 @@ __global__ __launch_bounds__(128) void k_pre_coef(const float* __restrict__ sums
                                                   const float* __restrict__ b_res, float eps, int iters,
                                                   float delta, float* __restrict__ Hpost,
                                                   float* __restrict__ Hres, float* __restrict__ saved, int nsave,
-                                                  int save_z_at, int save_stats_at,
-                                                  const int* __restrict__ err) {
+                                                  int save_z_at, int save_stats_at) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= T) return;
-  if (err && *err != 0) {
-    // the single-pass kernel gave up a wait: its partials are not valid
-    const float nan = __uint_as_float(0x7fc00000u);
-    for (int o = 0; o < k * Kq; ++o) Hpost[t * k * Kq + o] = nan;
-    if (with_res)
-      for (int o = 0; o < k * k; ++o) Hres[t * k * k + o] = nan;
-    return;
-  }
   const float nu_a = sums[(int64_t)(NO - 1) * T + t] / (float)kC;
   const float rstd = 1.0f / sqrtf(nu_a + eps);
   if (saved) {
@@ -208,7 +199,7 @@ __global__ __launch_bounds__(kCoefTok * kCoefParts) void k_pre_coef_sum(
     const float* __restrict__ alpha_post, const float* __restrict__ alpha_res, const float* __restrict__ b_post,
     const float* __restrict__ b_res, float eps, int iters, float delta, float* __restrict__ Hpost,
     float* __restrict__ Hres, float* __restrict__ saved, int nsave, int save_z_at, int save_stats_at,
-    const int* __restrict__ err) {
+    PreFailed f) {
   constexpr int NA = K * kMaxKr + K * K;   // outputs kept (at most)
   constexpr int GL = mix_lanes(K), NT = kCoefTok * kCoefParts;
   static_assert(NA <= 2 * GL && K * kMaxKr <= GL && K * K <= GL, "a lane keeps two outputs at most");
@@ -247,9 +238,18 @@ __global__ __launch_bounds__(kCoefTok * kCoefParts) void k_pre_coef_sum(
     r0[0] = v;
   }
   __syncthreads();
-  // a failed single pass leaves partials that are not valid
-  const bool bad = err && *err != 0;
+  // a failed single pass leaves partials that are not valid, and its own
+  // outputs were formed from records that had not come
+  const bool bad = f.err && *f.err != 0;
   const float nan = __uint_as_float(0x7fc00000u);
+  if (bad) {
+    const int64_t te = tb + kCoefTok < T ? tb + kCoefTok : T;
+    for (int64_t i = tb * f.C + threadIdx.x; i < te * f.C; i += NT) f.input[i] = 0x7fc0;
+    for (int64_t i = tb * f.N + threadIdx.x; i < te * f.N; i += NT) f.Hpre[i] = nan;
+    for (int64_t i = tb * K + threadIdx.x; i < te * K; i += NT) f.p[i] = nan;
+    if (saved)
+      for (int64_t i = tb * nsave + threadIdx.x; i < te * nsave; i += NT) saved[i] = nan;
+  }
   const float ap = alpha_post[0], ar = with_res ? alpha_res[0] : 0.f;
   const int e = threadIdx.x % GL;
   for (int u = threadIdx.x / GL; u < kCoefTok; u += NT / GL) {   // (the same number of turns in every lane)
@@ -305,7 +305,7 @@ hipError_t launch_pre_coef(const float* part, int64_t nchunk, int64_t nout, int6
                            int with_res, int64_t C, const float* alpha_post, const float* alpha_res,
                            const float* b_post, const float* b_res, float eps, int iters, float delta,
                            float* Hpost, float* Hres, float* sums, float* saved, int nsave, int save_z_at,
-                           int save_stats_at, hipStream_t s, const int* err) {
+                           int save_stats_at, hipStream_t s, const PreFailed* failed) {
   if (T == 0) return hipSuccess;
   const int NO = (int)out_blocks(nout) * 16 + 2;
   if ((k == 2 || k == 4) && Kq <= kMaxKr) {
@@ -313,17 +313,18 @@ hipError_t launch_pre_coef(const float* part, int64_t nchunk, int64_t nout, int6
 #define XHC_COEF(KV)                                                                                              \
   k_pre_coef_sum<KV><<<g, b, 0, s>>>(part, nchunk, NO, T, Kq, with_res, (int64_t)k * C, alpha_post, alpha_res,      \
                                      b_post, b_res, eps, iters, delta, Hpost, Hres, saved, nsave, save_z_at,       \
-                                     save_stats_at, err)
+                                     save_stats_at, failed ? *failed : PreFailed{})
     if (k == 4) XHC_COEF(4);
     else XHC_COEF(2);
 #undef XHC_COEF
     return hipGetLastError();
   }
+  if (failed) return hipErrorInvalidValue;   // (the single pass has k = 4)
   hipError_t e = sum_chunks(part, nchunk, NO, T, sums, s);
   if (e != hipSuccess) return e;
   k_pre_coef<<<dim3((unsigned)((T + 127) / 128)), dim3(128), 0, s>>>(
       sums, NO, T, k, Kq, with_res, (int64_t)k * C, alpha_post, alpha_res, b_post, b_res, eps, iters, delta,
-      Hpost, Hres, saved, nsave, save_z_at, save_stats_at, err);
+      Hpost, Hres, saved, nsave, save_z_at, save_stats_at);
   return hipGetLastError();
 }
 
