@@ -447,7 +447,7 @@ __global__ __launch_bounds__(FNT, 1) void k_pre_fused(FusedArgs a) {
         pv = sc;
       }
       if (a.saved && tg < T) {
-        float* sv = a.saved + tg * a.nsave;
+        float* sv = a.saved + (int64_t)tg * a.nsave;   // (past 2^31 floats from 31.6M tokens on)
         if (lane < FN) sv[lane] = z;
         else if (lane == FN) sv[a.nsave - 4] = mu;
         else if (lane == FN + 1) sv[a.nsave - 3] = nu;
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(FNT, 1) void k_pre_fused(FusedArgs a) {
       const float nu = lane_value(mo, 0) * inv_nc;
       const float r_rms = __builtin_amdgcn_rsqf(nu + a.eps);
       if (lane < FN) {
-        if (a.saved && tg < T) a.saved[tg * a.nsave + FN + lane] = v * r_rms;
+        if (a.saved && tg < T) a.saved[(int64_t)tg * a.nsave + FN + lane] = v * r_rms;
         const float hpre = sigmoidf(alpha_pre * (v * r_rms) + bpre_l);
         st_rec(r2 + lane, hpre, tag);
         if (tg < T) a.Hpre[tg * FN + lane] = hpre;
