@@ -121,24 +121,39 @@ __global__ __launch_bounds__(128) void k_post_coef(const float* __restrict__ gpa
 
 // ------------------------------------------------------------------ run-based MLP-type kernels
 // For compile-time kernel sizes (K1, K2, K3) = (4, 8, 12): a thread owns 4
-// channels and walks a run of up to kRun consecutive tokens of one sequence in
-// groups of G, keeping the conv taps of its channels and the last 12 values of
-// F in registers, so F is read once per kernel and the taps once per run.  The
-// runs cut each sequence from its start, so none crosses a sequence start; the
-// last group of a run may be short.  RAGGED: it may, or the width is no multiple
-// of a workgroup's channels and the threads past it work on zeros (instances
-// of their own, so that the others carry no trace of it).
+// channels and walks a run of up to kRun consecutive tokens in groups of G,
+// keeping the conv taps of its channels and the last 12 values of F in
+// registers, so F is read once per kernel and the taps once per run.  Where a
+// sequence starts the history is cleared: FIT: starts fall on group starts, the
+// runs cut all tokens alike and the width in whole workgroups.  SPLIT: the same
+// for the starts (or no run crosses one), but the last group may be short and the
+// threads past the width work on zeros.  CROSS: starts fall anywhere.
 
 constexpr int kRun = 64;   // tokens of a run, at most
+enum RunMode { FIT, SPLIT, CROSS };
 
-// the runs of a launch: run b takes tokens t0 .. t0 + nt of sequence b / rps
+// Sequences this short, and no multiple of a group, are crossed; longer ones are
+// cut each from its start.  A cut costs its run the set-up again, a crossing
+// the clearing of the history (60 registers) in an instance that carries it at
+// every token.  T = 8192, k = 4, cut / crossed: C = 4096 S = 2 490 / 220 us, S = 7
+// 267 / 216, S = 33 196 / 210, S = 1541 188 / 218; C = 2112 S = 2 295 / 155, S = 7
+// 147 / 150, S = 31 134 / 149.
+constexpr int kCrossed = 8;
+
+// the runs of a launch: units of consecutive tokens, cut into runs of rl
 struct Runs {
-  int64_t T, S, rps;
+  int64_t T, S;
+  int64_t unit, rpu;   // tokens and runs of a unit
   int rl;
-  __device__ __forceinline__ int64_t first(int64_t b) const { return b / rps * S + b % rps * rl; }
+  __device__ __forceinline__ int64_t first(int64_t b) const { return b / rpu * unit + b % rpu * rl; }
   __device__ __forceinline__ int count(int64_t b) const {
-    const int64_t t0 = first(b), next = (b / rps + 1) * S, end = next < T ? next : T;
-    return (int)(end - t0 < rl ? end - t0 : rl);   // (<= 0: past the last, partial sequence)
+    const int64_t t0 = first(b), next = (b / rpu + 1) * unit;
+    return (int)(next - t0 < rl ? next - t0 : rl);
+  }
+  // tokens from t to the next sequence start after it (at most 2^30: no run is longer)
+  __device__ __forceinline__ int left(int64_t t) const {
+    const int64_t n = S - t % S;
+    return n < (1 << 30) ? (int)n : 1 << 30;
   }
 };
 
@@ -146,20 +161,52 @@ struct Runs {
 // other, so its time is about that of its tokens in sequence; with fewer
 // workgroups than the chip holds (two per CU at these register counts, 512)
 // shorter runs finish sooner, until the set-up (24 taps and 12 rows of
-// history a channel) is as long as the walk: 4 tokens, one group.
+// history a channel) is as long as the walk: 4 tokens, one group.  Sequences of
+// whole groups are no matter to the cut (each cut from its start, T = 8192 k = 4
+// C = 4096: S = 8 222 us against 166, S = 100 221 against 166).
 static Runs make_runs(int64_t T, int64_t S, int64_t chunks, int64_t* nruns) {
-  const int64_t len = S < T ? S : T, nseq = (T + len - 1) / len;
+  const int64_t unit = S % 4 == 0 || S < kCrossed ? T : S;   // (T is a multiple of S)
   int rl = kRun;
-  while (rl > 4 && nseq * ((len + rl - 1) / rl) * chunks < 512) rl /= 2;
-  const Runs r{T, len, (len + rl - 1) / rl, rl};
-  *nruns = nseq * r.rps;
+  while (rl > 4 && T / unit * ((unit + rl - 1) / rl) * chunks < 512) rl /= 2;
+  const Runs r{T, S, unit, (unit + rl - 1) / rl, rl};
+  *nruns = T / unit * r.rpu;
   return r;
+}
+static RunMode run_mode(int64_t S, int C, int nthr) {
+  if (S % 4 != 0) return S < kCrossed ? CROSS : SPLIT;
+  return C % (4 * nthr) != 0 ? SPLIT : FIT;
+}
+
+// Clears what precedes token g of a group where a sequence starts there: the
+// history, and the group's earlier tokens, which have been used; the shift at
+// the group's end then puts the zeros where the history has them.  left counts
+// the tokens to the next start, from 0 where token g is one.
+template <typename CG, int G>
+__device__ __forceinline__ void start_at(CG& cg, float (&cur)[G][4], int g, int seq, int& left) {
+  if (left == 0) {
+    cg.reset();
+#pragma unroll
+    for (int h = 0; h < G; ++h)
+      if (h < g) cur[h][0] = cur[h][1] = cur[h][2] = cur[h][3] = 0.f;
+    left = seq;
+  }
+  --left;
+}
+
+// The same where starts fall on group starts.
+template <typename CG>
+__device__ __forceinline__ void start_at_group(CG& cg, int G, int seq, int& left) {
+  if (left == 0) {
+    cg.reset();
+    left = seq;
+  }
+  left -= G;
 }
 
 // Gram partials per workgroup's channels.  Each lane forms its 4-channel
 // products for G tokens; a wave sums them over its 64 lanes through an LDS
 // transpose (lane v adds column v), and the waves' sums are added at the end.
-template <typename TS, int K1, int K2, int K3, bool RAGGED>
+template <typename TS, int K1, int K2, int K3, RunMode MODE>
 __global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F, Runs runs, int C,
                                                        const float* __restrict__ conv_w,
                                                        float* __restrict__ gpart) {
@@ -174,14 +221,15 @@ __global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F,
   const int64_t cb = blockIdx.y;
   const int64_t T = runs.T, t0 = runs.first(blockIdx.x);
   const int nt = runs.count(blockIdx.x);
-  if (nt <= 0) return;
   int c = (int)(cb * blockDim.x + threadIdx.x) * 4;
-  const bool past = RAGGED && c >= C;   // (reads the last channels, counts as zeros)
+  const bool past = MODE != FIT && c >= C;   // (reads the last channels, counts as zeros)
   if (past) c = C - 4;
   CG cg;
   cg.load_taps(conv_w, C, c);
   cg.init(F, t0, runs.S, C, c);
   if (past) cg.reset();
+  const int seq = runs.left(0);
+  int left = runs.left(t0);
   float* mine = &xpose[wave][lane][0];
   // F rows are loaded PF groups ahead (a lane requests 8 bytes per token of a
   // bf16 state, so one group in flight would leave the memory system mostly
@@ -200,6 +248,7 @@ __global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F,
     for (int f = 0; f < PF; ++f) {
       const int u0 = u1 + f * G;
       if (u0 >= nt) break;
+      if (MODE != CROSS) start_at_group(cg, G, seq, left);
       float cur[G][4];
 #pragma unroll
       for (int g = 0; g < G; ++g) {
@@ -214,6 +263,7 @@ __global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F,
       float part[NV];
 #pragma unroll
       for (int g = 0; g < G; ++g) {
+        if (MODE == CROSS) start_at(cg, cur, g, seq, left);
         float e[KR][4];
         cg.components(cur, g, e);
         int pi = 0;
@@ -264,7 +314,7 @@ __global__ __launch_bounds__(256) void k_post_gram_run(const TS* __restrict__ F,
 // next sublayer's input.  The run's indices and coefficients are staged in LDS
 // once, the write-back weights wb formed there from the Gram partials; the
 // loads of a group of G tokens are issued together.
-template <typename TS, int KK, int G, bool RES, bool SAVE, bool NEXT, bool RAGGED>
+template <typename TS, int KK, int G, bool RES, bool SAVE, bool NEXT, RunMode MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_post_apply_run(TS* __restrict__ X, const TS* __restrict__ F, Runs runs,
                                                         int N, int C,
                                                         const float* __restrict__ conv_w,
@@ -285,9 +335,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   __shared__ float s_hn[NEXT ? kRun * kMaxN : 1];
   const int64_t T = runs.T, t0 = runs.first(blockIdx.x);
   const int nt = runs.count(blockIdx.x);
-  if (nt <= 0) return;
   int c = (int)(blockIdx.y * blockDim.x + threadIdx.x) * 4;
-  const bool past = RAGGED && c >= C;
+  const bool past = MODE != FIT && c >= C;
   if (past) c = C - 4;
   for (int i = threadIdx.x; i < nt * KK; i += blockDim.x) s_idx[i] = idx[t0 * KK + i];
   // write-back weights of the run's tokens from their Gram partials (the same
@@ -303,23 +352,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   cg.init(F, t0, runs.S, C, c);
   __syncthreads();
   if (past) return;
+  const int seq = runs.left(0);
+  int left = runs.left(t0);
   for (int u0 = 0; u0 < nt; u0 += G) {
-    // (changes nothing, init has cleared it, but ends the scheduler's region:
-    // without it the write-back spilled or took one wave a SIMD, 478 us
-    // against 336 at T = 16384 C = 4096)
-    if (!RAGGED && (t0 + u0) % runs.S == 0) cg.reset();
+    // (the branch also ends the scheduler's region: without one here the
+    // write-back spilled or took one wave a SIMD, 478 us against 336 at T =
+    // 16384 C = 4096)
+    if (MODE == FIT && (t0 + u0) % runs.S == 0) cg.reset();
+    if (MODE == SPLIT) start_at_group(cg, G, seq, left);
     int32_t rows[G][KK];
     float cur[G][4];
     typename R::raw a[G][KK], nb[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const int u = !RAGGED || u0 + g < nt ? u0 + g : nt - 1;
+      const int u = MODE == FIT || u0 + g < nt ? u0 + g : nt - 1;
 #pragma unroll
       for (int l = 0; l < KK; ++l) rows[g][l] = __builtin_amdgcn_readfirstlane(s_idx[u * KK + l]);
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const int64_t tg = t0 + (!RAGGED || u0 + g < nt ? u0 + g : nt - 1);
+      const int64_t tg = t0 + (MODE == FIT || u0 + g < nt ? u0 + g : nt - 1);
       R::unpack(R::load(F + tg * C + c), cur[g]);
 #pragma unroll
       for (int l = 0; l < KK; ++l) a[g][l] = R::load(X + (tg * N + rows[g][l]) * (int64_t)C + c);
@@ -327,9 +379,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      if (RAGGED && u0 + g >= nt) break;   // (past the run: read its last token)
+      if (MODE != FIT && u0 + g >= nt) break;   // (past the run: read its last token)
       const int u = u0 + g;
       const int64_t tg = t0 + u;
+      if (MODE == CROSS) start_at(cg, cur, g, seq, left);
       float e[KR][4];
       cg.components(cur, g, e);
       if (SAVE) {
@@ -399,9 +452,14 @@ static size_t bytes256(size_t floats) { return (floats * sizeof(float) + 255) / 
 
 // The run kernels serve the paper's branches at k = 2, 4 and 8, any width and
 // sequence length: at T = 6164, S = 1541, N = 8, C = 2112 a Flash group's four
-// write-backs take 984 us with the per-token kernels, whose every token reads
-// 12 rows of F and 24 rows of taps, and 581 us with these.  The other k keep the
-// per-token write-back, with the run Gram where its partials fit what they need.
+// write-backs take 984 us with the per-token kernels, whose every token reads up
+// to 12 rows of F and 24 rows of taps, and 581 us with these; k = 8, C = 1024, T =
+// 8192, S = 1024 one write-back 140 and 67 us.  The other k keep the per-token
+// write-back, with the run Gram where its partials fit what they need.
+// So do many tokens in sequences of one to three, of which a token reads that
+// many rows and taps only, where the width fills the per-token workgroups of
+// 2048 channels (per token / run, T = 8192, k = 4: C = 4096 S = 1 203 / 223 us, S
+// = 2 220 / 219, C = 6144 S = 3 304 / 359; T = 2048, C = 4096, S = 1 68 / 61).
 // Where the caller's workspace (or the fixed scratch) holds the per-token
 // kernels' partials and not these, the per-token kernels run.
 PostPlan post_plan(int64_t T, int64_t S, int C, int k, int Kr, const int32_t* kappa, size_t avail) {
@@ -409,7 +467,8 @@ PostPlan post_plan(int64_t T, int64_t S, int C, int k, int Kr, const int32_t* ka
   if (Kr == 1) return p;
   const bool even = C % 1024 == 0 || C == 256 || C == 512 || C == 768;   // whole workgroups
   const bool exact = paper_branches(Kr, kappa) && even && S % 4 == 0;
-  const bool run = paper_branches(Kr, kappa) && C % 4 == 0 && (k == 2 || k == 4 || k == 8);
+  const bool few = S <= 3 && S <= C / 2048 && C % 2048 == 0 && k <= 4 && T * C >= (int64_t)1 << 24;
+  const bool run = paper_branches(Kr, kappa) && C % 4 == 0 && (k == 2 || k == 4 || k == 8) && !few;
   const size_t wb = bytes256((size_t)T * k * Kr);
   const size_t per_run = bytes256(gram_floats(run_chunks(C), Kr, T));
   const size_t per_token = bytes256(gram_floats(post_chunks(C), Kr, T));
@@ -430,14 +489,16 @@ hipError_t launch_post_gram(const PostPlan& plan, int state_dtype, const void* F
     const Runs runs = make_runs(T, S, plan.nchunk, &nruns);
     const int nthr = run_threads(C);
     const dim3 grid((unsigned)nruns, (unsigned)plan.nchunk);
-#define XHC_GRAM_RUN(TS, RAG) \
-  k_post_gram_run<TS, 4, 8, 12, RAG><<<grid, dim3(nthr), 0, s>>>(reinterpret_cast<const TS*>(F), runs, C, conv_w, gpart)
-    const bool ragged = C % (4 * nthr) != 0;
-    if (state_dtype == XHC_BF16) {
-      if (ragged) XHC_GRAM_RUN(uint16_t, true); else XHC_GRAM_RUN(uint16_t, false);
-    } else {
-      if (ragged) XHC_GRAM_RUN(float, true); else XHC_GRAM_RUN(float, false);
-    }
+#define XHC_GRAM_RUN(TS, MODE) \
+  k_post_gram_run<TS, 4, 8, 12, MODE><<<grid, dim3(nthr), 0, s>>>(reinterpret_cast<const TS*>(F), runs, C, conv_w, gpart)
+#define XHC_GRAM_MODES(TS)                            \
+  switch (run_mode(S, C, nthr)) {                     \
+    case FIT: XHC_GRAM_RUN(TS, FIT); break;           \
+    case SPLIT: XHC_GRAM_RUN(TS, SPLIT); break;       \
+    case CROSS: XHC_GRAM_RUN(TS, CROSS); break;       \
+  }
+    if (state_dtype == XHC_BF16) XHC_GRAM_MODES(uint16_t) else XHC_GRAM_MODES(float)
+#undef XHC_GRAM_MODES
 #undef XHC_GRAM_RUN
     return hipGetLastError();
   }
@@ -555,34 +616,42 @@ hipError_t launch_post_apply(const PostPlan& plan, int state_dtype, void* X, con
     const Runs runs = make_runs(T, S, nchunk, &nruns);
     const int nthr = run_threads(C);
     const dim3 grid((unsigned)nruns, (unsigned)nchunk);
-#define XHC_APPLY_RUN(TS, KK, G, RES, SAVE, NEXT, RAG)                                                            \
-  k_post_apply_run<TS, KK, G, RES, SAVE, NEXT, RAG><<<grid, dim3(nthr), 0, s>>>(                                \
+#define XHC_APPLY_RUN(TS, KK, G, RES, SAVE, NEXT, MODE)                                                           \
+  k_post_apply_run<TS, KK, G, RES, SAVE, NEXT, MODE><<<grid, dim3(nthr), 0, s>>>(                               \
       reinterpret_cast<TS*>(X), reinterpret_cast<const TS*>(F), runs, N, C, conv_w, idx, Hres, gpart, nchunk,     \
       gram_schmidt, p, Hpost, Hpre_next, reinterpret_cast<const TS*>(base_next),                                 \
       reinterpret_cast<TS*>(input_next), reinterpret_cast<TS*>(Xact_save))
-#define XHC_APPLY_MODES(TS, KK, G, RAG)                                                     \
+#define XHC_APPLY_FORMS(TS, KK, G, MODE)                                                    \
   do {                                                                                       \
-    if (input_next && Xact_save) XHC_APPLY_RUN(TS, KK, G, false, true, true, RAG);          \
-    else if (input_next) XHC_APPLY_RUN(TS, KK, G, false, false, true, RAG);                 \
-    else if (Xact_save) XHC_APPLY_RUN(TS, KK, G, true, true, false, RAG);                   \
-    else XHC_APPLY_RUN(TS, KK, G, true, false, false, RAG);                                 \
+    if (input_next && Xact_save) XHC_APPLY_RUN(TS, KK, G, false, true, true, MODE);         \
+    else if (input_next) XHC_APPLY_RUN(TS, KK, G, false, false, true, MODE);                \
+    else if (Xact_save) XHC_APPLY_RUN(TS, KK, G, true, true, false, MODE);                  \
+    else XHC_APPLY_RUN(TS, KK, G, true, false, false, MODE);                                \
   } while (0)
-    const bool ragged = C % (4 * nthr) != 0 || runs.S % 4 != 0;   // (runs are 4 tokens and up)
-    // (k = 2 has the ragged instance alone)
+#define XHC_APPLY_MODES(TS, KK, G)                    \
+  switch (mode) {                                     \
+    case FIT: XHC_APPLY_FORMS(TS, KK, G, FIT); break; \
+    case SPLIT: XHC_APPLY_FORMS(TS, KK, G, SPLIT); break; \
+    case CROSS: XHC_APPLY_FORMS(TS, KK, G, CROSS); break; \
+  }
+#define XHC_APPLY_MODES2(TS)                                                     \
+  {                                                                              \
+    if (mode == CROSS) XHC_APPLY_FORMS(TS, 2, 4, CROSS);                         \
+    else XHC_APPLY_FORMS(TS, 2, 4, SPLIT);   /* (a fitting one runs in it) */    \
+  }
+    const RunMode mode = run_mode(S, C, nthr);
     if (state_dtype == XHC_BF16) {
-      if (k == 2) XHC_APPLY_MODES(uint16_t, 2, 4, true);
-      else if (k == 8 && ragged) XHC_APPLY_MODES(uint16_t, 8, 2, true);
-      else if (k == 8) XHC_APPLY_MODES(uint16_t, 8, 2, false);
-      else if (ragged) XHC_APPLY_MODES(uint16_t, 4, 4, true);
-      else XHC_APPLY_MODES(uint16_t, 4, 4, false);
+      if (k == 2) XHC_APPLY_MODES2(uint16_t)
+      else if (k == 8) XHC_APPLY_MODES(uint16_t, 8, 2)
+      else XHC_APPLY_MODES(uint16_t, 4, 4)
     } else {
-      if (k == 2) XHC_APPLY_MODES(float, 2, 4, true);
-      else if (k == 8 && ragged) XHC_APPLY_MODES(float, 8, 1, true);
-      else if (k == 8) XHC_APPLY_MODES(float, 8, 1, false);
-      else if (ragged) XHC_APPLY_MODES(float, 4, 2, true);
-      else XHC_APPLY_MODES(float, 4, 2, false);
+      if (k == 2) XHC_APPLY_MODES2(float)
+      else if (k == 8) XHC_APPLY_MODES(float, 8, 1)
+      else XHC_APPLY_MODES(float, 4, 2)
     }
+#undef XHC_APPLY_MODES2
 #undef XHC_APPLY_MODES
+#undef XHC_APPLY_FORMS
 #undef XHC_APPLY_RUN
     return hipGetLastError();
   }

@@ -17,7 +17,7 @@ F64 = torch.float64
 
 # (T, S, C): tokens per run of the conv reverse / the dot products / the forward
 CASES = [(20, 4, 256),        # 16 / 4 / 4
-         (1030, 515, 1024),   # 16 / 4 / generic (odd sequence length)
+         (1030, 515, 1024),   # 16 / 4 / 4, each sequence cut from its start
          (4100, 820, 1024),   # 32 / 8 / 8
          (2080, 2080, 4096)]  # 64 / 16 / 16
 
