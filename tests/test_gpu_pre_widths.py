@@ -10,6 +10,7 @@ import torch
 from paper_2607_14530_amd import synth
 from paper_2607_14530_amd import xhc as X
 from tests.parity_util import check_sublayer
+from tests.test_gpu_pre_streams import plain_workgroups
 
 pytestmark = pytest.mark.gpu
 
@@ -27,6 +28,7 @@ def test_single_pass_widths(C, T, Kr):
     before = inp["X"].clone()
     sub.pre(inp["X"], saved=saved)
     assert sub.pre_failures() == 0
+    assert plain_workgroups(sub) > 0, "AUTO fell back to the multi-kernel path"
     assert torch.equal(inp["X"], before)
     sub.post(inp["X"], inp["F"])
     torch.cuda.synchronize()
@@ -36,6 +38,7 @@ def test_single_pass_widths(C, T, Kr):
     ref = torch.empty_like(saved)
     multi.pre(before, saved=ref)
     torch.cuda.synchronize()
+    assert plain_workgroups(multi) == 0
     same = same.to("cuda")
     n = saved.shape[1] - 1      # the last float is padding
     assert float((saved[same, :n] - ref[same, :n]).abs().max()) < 2e-4
@@ -60,6 +63,6 @@ def test_single_pass_on_several_streams(C):
             sub.pre(inp["X"], stream=st)
     torch.cuda.synchronize()
     for sub, ref in zip(subs, refs):
-        assert sub.pre_failures() == 0
+        assert sub.pre_failures() == 0 and plain_workgroups(sub) > 0
         for n in names:
             assert torch.equal(getattr(sub, n), ref[n]), n
