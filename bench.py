@@ -396,7 +396,7 @@ def main():
         "segments_ms_p10_p50_p90": {n: [pctl(seg[j], 10), pctl(seg[j], 50), pctl(seg[j], 90)]
                                     for j, n in enumerate(("attn_pre", "attn_post", "mlp_pre", "mlp_post"))},
         "wall_s": wall,
-        "roofline": {"kernel": "xhc_pre entry point (single-pass cooperative kernel k_pre_fused: projection, "
+        "roofline": {"kernel": "xhc_pre entry point (single-pass kernel k_pre_fused: projection, "
                                "routing, dense read, gathered projection; then the per-token coefficient pass), "
                                "mean of the two sublayer kinds",
                      "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",

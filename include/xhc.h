@@ -209,11 +209,12 @@ xhc_status xhc_post(const xhc_dims* d, void* X, const void* F, const float* conv
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc).  Same arguments, results and errors as xhc_post, without the
  * workspace: the MLP-type write-back's scratch (Gram partials and write-back
- * weights, xhc_workspace_bytes(d, XHC_OP_POST, 0) bytes) lives in a static
- * device array of XHC_NOALLOC_SCRATCH_BYTES that every GPU the library runs
- * on holds until the process ends.  The call allocates nothing.  Shapes whose
- * scratch exceeds that size return XHC_EWORKSPACE before any work is
- * enqueued (at C = 4096, K_r = 4: T up to about 72K tokens).  All calls on
+ * weights) lives in a static device array of XHC_NOALLOC_SCRATCH_BYTES that
+ * every GPU the library runs on holds until the process ends.  The call
+ * allocates nothing.  It takes the form that the array holds (the per-token
+ * kernels where xhc_workspace_bytes(d, XHC_OP_POST, 0) is more for the partials
+ * of the run-based ones), and returns XHC_EWORKSPACE before any work is
+ * enqueued where it holds none (at C = 4096, K_r = 4: T up to about 72K tokens).  All calls on
  * one GPU share its array: calls that overlap on one GPU (different streams
  * without ordering between them) race and must not be made.            */
 #define XHC_NOALLOC_SCRATCH_BYTES ((size_t)16 << 20)

@@ -1545,7 +1545,6 @@ __global__ __launch_bounds__(256) void k_bwd_act_rows(const TS* __restrict__ X, 
 // rows of a routed state, gathered through idx, take k_bwd_act_rows_mfma.
 constexpr int kMfRows = 64;    // weight rows per workgroup
 constexpr int kMfStep = 32;    // tokens per step
-constexpr int kMfXPitch = kMfRows + 8;   // bf16 per staged token row (pad: fewer LDS bank conflicts)
 
 // 4 consecutive bf16 gradient elements from floats
 __device__ __forceinline__ void st4(uint16_t* p, const float (&d)[4]) {
