@@ -104,10 +104,11 @@ typedef enum { XHC_ROUTER_SIGMOID = 0, XHC_ROUTER_SOFTMAX = 1 } xhc_router;
  * captured decides.  Not counted are the launches of other processes: where
  * several share the GPU and nine or more single-pass launches can be in flight
  * at once, their unfinished teams could hold every CU until waits give up.
- * Programs that share a GPU so take MULTI, which waits for nothing.
- * If a wait ever gives up, every float output of the call (input, p, H^pre,
- * H^post, H^res, saved) comes out as NaN rather than as a wrong value, and
- * xhc_pre_failures says so.                                                 */
+ * If a wait gives up, the pass behind the kernel forms all outputs of the call
+ * again without the partial sums that had not come: the results are as right
+ * as any, late by the wait's bound (65536 polls of a record) and some
+ * milliseconds (C = 4096: 2.7 at T = 16, 10 at T = 16384), and xhc_pre_failures
+ * says so.  A program that sees that takes MULTI, which waits for nothing.  */
 typedef enum { XHC_IMPL_AUTO = 0, XHC_IMPL_MULTI = 1, XHC_IMPL_FUSED = 2 } xhc_impl;
 
 /* Name of a status code, and the name of the HIP error behind the last
@@ -176,9 +177,9 @@ xhc_status xhc_pre(const xhc_dims* d, const void* X, const void* packed_full, co
  * finished, then sets *failures to the number of bounded waits that gave up
  * in the last xhc_pre call that used `workspace` (that call's own workspace
  * pointer).  The single-pass kernel's members exchange partial sums through
- * device memory and every wait on another member is bounded; a wait that
- * gives up leaves NaN in the call's float outputs, and this count says that it
- * happened.  The multi-kernel path has no such waits and reports 0.
+ * device memory and every wait on another member is bounded; after a wait that
+ * gives up the outputs are formed again (see xhc_impl), and this count says
+ * that it happened.  The multi-kernel path has no such waits and reports 0.
  * Errors: XHC_EINVAL (NULL pointer), XHC_EUNSUPPORTED (workspace not 16-byte
  * aligned), XHC_EHIP (the copy or the synchronisation failed).            */
 xhc_status xhc_pre_failures(const void* workspace, int32_t* failures, void* stream);

@@ -107,20 +107,24 @@ hipError_t launch_pre_route(const float* part, int64_t nchunk, int64_t nout, int
                             float* saved, int nsave, int save_stats_at, int router, hipStream_t s,
                             int save_pre = 0);   // which pre-map's z goes to saved[N .. 2N); -1: all, one record each
 // The single pass whose partials a coefficient pass sums: its count of waits that
-// gave up, and the outputs it wrote itself (bf16 input).  Where the count is not
-// zero every float output comes out as NaN (idx stays a valid choice: the
-// reducers rank whatever they have).  k = 4.
-struct PreFailed {
+// gave up, and what it takes to form a token's outputs again where that is not
+// zero (bf16 state, N = 16, k = 4).
+struct PreRedo {
   const int* err;
+  const uint16_t* X;
+  const uint4 *wfull, *wact;   // the packed weights; wact grouped or plain
+  int act_grouped;
+  const float *colsum, *alpha_pre, *b_pre;
   uint16_t* input;
+  int32_t* idx;
   float *p, *Hpre;
-  int N, C;
+  int C, m, softmax;
 };
 hipError_t launch_pre_coef(const float* part, int64_t nchunk, int64_t nout, int64_t T, int k, int Kq,
                            int with_res, int64_t C, const float* alpha_post, const float* alpha_res,
                            const float* b_post, const float* b_res, float eps, int iters, float delta,
                            float* Hpost, float* Hres, float* sums, float* saved, int nsave, int save_z_at,
-                           int save_stats_at, hipStream_t s, const PreFailed* failed = nullptr);
+                           int save_stats_at, hipStream_t s, const PreRedo* redo = nullptr);
 // out0 gets map 0 (full dense read); maps 1..nmap-1 leave out the active
 // streams and go to outr + (q - 1) * T * C.
 hipError_t launch_dense_read(int state_dtype, const void* X, int64_t T, int N, int C, const float* Hpre,

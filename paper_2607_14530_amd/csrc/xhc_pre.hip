@@ -193,13 +193,114 @@ __global__ __launch_bounds__(128) void k_pre_coef(const float* __restrict__ sums
 // per token form the coefficients, an element of H^res each (with one thread
 // per token the Sinkhorn iterations were a chain of 8 us at any T).
 constexpr int kCoefTok = 32, kCoefParts = 8;   // tokens per workgroup, chunk ranges per token
-template <int K>
+
+// Everything xhc_pre has for token t, formed by a workgroup without the partials of
+// the single pass: the full-state projection (a thread takes 8 consecutive rows
+// K at a time, all 32 outputs), routing and H^pre, the dense read, then the
+// active projection, whose sums go to act[o pitch] (o < 32) and act[32 pitch]
+// (the square sum).  Reached only after a wait that gave up, so that a launch
+// whose teams could not all run still ends in the right results; not fast (C =
+// 4096: T = 16 2.7 ms, T = 16384 10 ms, against 36 and 605 us of the call), and at
+// no cost where the count is zero, in registers and time.
+constexpr int kRedoThreads = kCoefTok * kCoefParts;
+struct RedoLds {
+  float wave[kRedoThreads / kWave][34], tot[34], hpre[16];
+  int32_t id[4];
+};
+__device__ __forceinline__ void redo_token(const PreRedo& r, int64_t t, float eps, float* saved, int nsave,
+                                           RedoLds& s, float* act, int pitch) {
+  constexpr int N = 16, k = 4, NO = 32;
+  const int C = r.C, tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  const uint16_t* x = r.X + t * N * C;
+#pragma nounroll
+  for (int ph = 0; ph < 2; ++ph) {   // the state's rows, then the routed ones
+    const uint4* w = ph == 0 ? r.wfull : r.wact;
+    const bool grouped = ph == 0 || r.act_grouped;
+    float acc[NO + 2];
+#pragma unroll
+    for (int o = 0; o < NO + 2; ++o) acc[o] = 0.f;
+    for (int K = tid * 8; K < (ph == 0 ? N : k) * C; K += kRedoThreads * 8) {
+      const int j = K / C, c = K - j * C;
+      float f[8];
+      unpack8(*reinterpret_cast<const uint4*>(x + (int64_t)(ph == 0 ? j : s.id[j]) * C + c), f);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        acc[NO] += f[e];
+        acc[NO + 1] += f[e] * f[e];
+      }
+      const int64_t kb = grouped ? (K >> 7) * 4 + ((K & 31) >> 3) : K >> 5;
+      const int g = (grouped ? (K & 127) >> 5 : (K & 31) >> 3) * 16;
+#pragma unroll
+      for (int o = 0; o < NO; ++o) {
+        float wv[8];
+        unpack8(w[(kb * 2 + o / 16) * kWave + g + o % 16], wv);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[o] = fmaf(f[e], wv[e], acc[o]);
+      }
+    }
+#pragma unroll
+    for (int o = 0; o < NO + 2; ++o) {
+      const float v = wave_sum(acc[o]);
+      if (lane == 0) s.wave[wave][o] = v;
+    }
+    __syncthreads();
+    if (tid < NO + 2) {
+      float v = 0.f;
+#pragma unroll
+      for (int q = 0; q < kRedoThreads / kWave; ++q) v += s.wave[q][tid];
+      if (ph == 0) s.tot[tid] = v;
+      else if (tid != NO) act[(tid < NO ? tid : NO) * pitch] = v;
+    }
+    __syncthreads();
+    if (ph == 1) return;
+    if (tid == 0) {
+      const float NC = (float)N * (float)C, mu = s.tot[NO] / NC, nu = s.tot[NO + 1] / NC;
+      const float r_ln = 1.0f / sqrtf(ln_variance(mu, nu) + eps), r_rms = 1.0f / sqrtf(nu + eps);
+      float z[N], pp[kMaxK];
+      int32_t id[kMaxK];
+#pragma unroll
+      for (int i = 0; i < N; ++i) z[i] = (s.tot[i] - mu * r.colsum[i]) * r_ln;
+      route_token<N>(z, N, r.m, k, id, pp, r.softmax != 0);
+      for (int j = 0; j < k; ++j) {
+        s.id[j] = r.idx[t * k + j] = id[j];
+        r.p[t * k + j] = pp[j];
+      }
+      float* sv = saved ? saved + t * nsave : nullptr;
+      for (int i = 0; i < N; ++i) {
+        const float zp = s.tot[N + i] * r_rms;
+        s.hpre[i] = r.Hpre[t * N + i] = sigmoidf(r.alpha_pre[0] * zp + r.b_pre[i]);
+        if (sv) sv[N + i] = zp;
+      }
+      if (sv) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) sv[i] = z[i];
+        sv[nsave - 4] = mu;
+        sv[nsave - 3] = nu;
+      }
+    }
+    __syncthreads();
+    for (int c = tid * 8; c < C; c += kRedoThreads * 8) {
+      float in[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < N; ++i) {
+        float f[8];
+        unpack8(*reinterpret_cast<const uint4*>(x + (int64_t)i * C + c), f);
+        const float h = s.hpre[i];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) in[e] = fmaf(h, f[e], in[e]);
+      }
+      *reinterpret_cast<uint4*>(r.input + t * C + c) = pack8(in);
+    }
+  }
+}
+
+// SINGLE: behind a single pass, which may have failed.
+template <int K, bool SINGLE>
 __global__ __launch_bounds__(kCoefTok * kCoefParts) void k_pre_coef_sum(
     const float* __restrict__ part, int64_t nchunk, int NO, int64_t T, int Kq, int with_res, int64_t kC,
     const float* __restrict__ alpha_post, const float* __restrict__ alpha_res, const float* __restrict__ b_post,
     const float* __restrict__ b_res, float eps, int iters, float delta, float* __restrict__ Hpost,
     float* __restrict__ Hres, float* __restrict__ saved, int nsave, int save_z_at, int save_stats_at,
-    PreFailed f) {
+    PreRedo redo) {
   constexpr int NA = K * kMaxKr + K * K;   // outputs kept (at most)
   constexpr int GL = mix_lanes(K), NT = kCoefTok * kCoefParts;
   static_assert(NA <= 2 * GL && K * kMaxKr <= GL && K * K <= GL, "a lane keeps two outputs at most");
@@ -238,17 +339,15 @@ __global__ __launch_bounds__(kCoefTok * kCoefParts) void k_pre_coef_sum(
     r0[0] = v;
   }
   __syncthreads();
-  // a failed single pass leaves partials that are not valid, and its own
-  // outputs were formed from records that had not come
-  const bool bad = f.err && *f.err != 0;
-  const float nan = __uint_as_float(0x7fc00000u);
-  if (bad) {
-    const int64_t te = tb + kCoefTok < T ? tb + kCoefTok : T;
-    for (int64_t i = tb * f.C + threadIdx.x; i < te * f.C; i += NT) f.input[i] = 0x7fc0;
-    for (int64_t i = tb * f.N + threadIdx.x; i < te * f.N; i += NT) f.Hpre[i] = nan;
-    for (int64_t i = tb * K + threadIdx.x; i < te * K; i += NT) f.p[i] = nan;
-    if (saved)
-      for (int64_t i = tb * nsave + threadIdx.x; i < te * nsave; i += NT) saved[i] = nan;
+  if constexpr (SINGLE) {
+    // after failed waits the partials are not valid, and the single pass's own
+    // outputs were formed from records that had not come
+    __shared__ RedoLds rs;
+    if (*redo.err != 0) {
+      for (int u = 0; u < kCoefTok && tb + u < T; ++u)
+        redo_token(redo, tb + u, eps, saved, nsave, rs, &red[0][0][u], kCoefTok);
+      __syncthreads();
+    }
   }
   const float ap = alpha_post[0], ar = with_res ? alpha_res[0] : 0.f;
   const int e = threadIdx.x % GL;
@@ -257,20 +356,20 @@ __global__ __launch_bounds__(kCoefTok * kCoefParts) void k_pre_coef_sum(
     const bool in = t < T;
     const float nu_a = red[0][NA][u] / (float)kC;
     const float rstd = 1.0f / sqrtf(nu_a + eps);
-    if (saved && in && !bad) {
+    if (saved && in) {
       if (e == 0) saved[t * nsave + save_stats_at] = nu_a;
 #pragma unroll
       for (int o = e; o < NA; o += GL)
         if (o < nproj) saved[t * nsave + save_z_at + o] = red[0][o][u] * rstd;
     }
     if (e < K * Kq && in)
-      Hpost[t * K * Kq + e] = bad ? nan : 2.0f * sigmoidf(ap * (red[0][e][u] * rstd) + b_post[e]);
+      Hpost[t * K * Kq + e] = 2.0f * sigmoidf(ap * (red[0][e][u] * rstd) + b_post[e]);
     if (!with_res) continue;
     // the W_res outputs follow the K Kq W_post outputs
     const bool used = e < K * K;
     const int er = used ? e : 0;
     const float M = sinkhorn_clamp_lanes<K>(ar * (red[0][K * Kq + er][u] * rstd) + b_res[er], used, iters, delta);
-    if (used && in) Hres[t * K * K + e] = bad ? nan : M;
+    if (used && in) Hres[t * K * K + e] = M;
   }
 }
 
@@ -305,21 +404,23 @@ hipError_t launch_pre_coef(const float* part, int64_t nchunk, int64_t nout, int6
                            int with_res, int64_t C, const float* alpha_post, const float* alpha_res,
                            const float* b_post, const float* b_res, float eps, int iters, float delta,
                            float* Hpost, float* Hres, float* sums, float* saved, int nsave, int save_z_at,
-                           int save_stats_at, hipStream_t s, const PreFailed* failed) {
+                           int save_stats_at, hipStream_t s, const PreRedo* redo) {
   if (T == 0) return hipSuccess;
   const int NO = (int)out_blocks(nout) * 16 + 2;
   if ((k == 2 || k == 4) && Kq <= kMaxKr) {
     const dim3 g((unsigned)((T + kCoefTok - 1) / kCoefTok)), b(kCoefTok * kCoefParts);
-#define XHC_COEF(KV)                                                                                              \
-  k_pre_coef_sum<KV><<<g, b, 0, s>>>(part, nchunk, NO, T, Kq, with_res, (int64_t)k * C, alpha_post, alpha_res,      \
+#define XHC_COEF(KV, SINGLE)                                                                                      \
+  k_pre_coef_sum<KV, SINGLE><<<g, b, 0, s>>>(part, nchunk, NO, T, Kq, with_res, (int64_t)k * C, alpha_post, alpha_res,      \
                                      b_post, b_res, eps, iters, delta, Hpost, Hres, saved, nsave, save_z_at,       \
-                                     save_stats_at, failed ? *failed : PreFailed{})
-    if (k == 4) XHC_COEF(4);
-    else XHC_COEF(2);
+                                     save_stats_at, redo ? *redo : PreRedo{})
+    if (redo && (k != 4 || out_blocks(nout) != 2)) return hipErrorInvalidValue;   // (the single pass's shape)
+    if (redo) XHC_COEF(4, true);
+    else if (k == 4) XHC_COEF(4, false);
+    else XHC_COEF(2, false);
 #undef XHC_COEF
     return hipGetLastError();
   }
-  if (failed) return hipErrorInvalidValue;   // (the single pass has k = 4)
+  if (redo) return hipErrorInvalidValue;
   hipError_t e = sum_chunks(part, nchunk, NO, T, sums, s);
   if (e != hipSuccess) return e;
   k_pre_coef<<<dim3((unsigned)((T + 127) / 128)), dim3(128), 0, s>>>(

@@ -41,7 +41,8 @@
 // that waits for members not yet started; the others run to their end and
 // free their CUs, and the last team then starts (see xhc_plain_launch.h for
 // when the launch is cooperative instead, and for what it cannot count).
-// Every wait is bounded, so every wave exits.
+// Every wait is bounded, so every wave exits; after one that gave up the
+// coefficient pass forms all outputs again (redo_token in xhc_pre.hip).
 //
 // SHORT: C is no multiple of 128 or the team is larger than the width needs
 // (an instance of its own: the exact one then has no trace of the zero

@@ -155,11 +155,13 @@ hipError_t launch_pre_fused(const xhc_dims* d, const void* X, const void* packed
   e = plain ? hipLaunchKernel(f, dim3(teams * G), dim3(FNT), args, kTileLds, s)
             : hipLaunchCooperativeKernel(f, dim3(teams * G), dim3(FNT), args, kTileLds, s);
   if (e != hipSuccess) return e;
-  const PreFailed failed{a.err, a.input, p, Hpre, FN, d->C};
-  // active partials -> H^post, H^res (Sinkhorn + clamp)
+  const PreRedo redo{a.err, a.X, a.wfull, a.wact, a.act_grouped, colsum, alpha, b_pre, a.input, idx, p, Hpre, d->C,
+                     d->m, a.softmax};
+  // active partials -> H^post, H^res (Sinkhorn + clamp); after failed waits every
+  // output again
   return launch_pre_coef(a.part2, G, (int64_t)FK * d->Kr + FK * FK, d->T, FK, d->Kr, 1, d->C, alpha + 2, alpha + 1,
                          b_post, b_res, d->eps, d->sinkhorn_iters, d->clamp_delta, Hpost, Hres, sums, saved, a.nsave,
-                         2 * FN, a.nsave - 2, s, &failed);
+                         2 * FN, a.nsave - 2, s, &redo);
 }
 
 }  // namespace xhc
