@@ -142,9 +142,9 @@ xhc_status xhc_pack_active(const xhc_dims* d, int32_t Kq, const float* W_post, c
  * pieces, each of which leaves partial sums, so this does not grow with T
  * throughout (N = 16, C = 4096: POST_BWD at T = 777 names 1.4 times the bytes of
  * T = 1024); and some fast forms need much (T = 16384: PRE at N = 16, C = 2560
- * 83 MB for the single pass, 34 without; PRE of a dense sublayer at N = 4, C =
+ * 83 MB for the single pass, 33 without; PRE of a dense sublayer at N = 4, C =
  * 4096 56 MB for one projection pass, 21 for two; FLASH_PRE_BWD at N = 8, C = 1024,
- * Q = 4 182 MB for one pass over the state, 72 map by map).  With less a call
+ * Q = 4 182 MB for one pass over the state, 69 map by map).  With less a call
  * takes the longer pieces or the smaller form, the same results to the order
  * of the sums, and XHC_EWORKSPACE is returned where those do not fit either.
  * For POST_BWD, PRE_BWD and FLASH_POST_BWD, and FLASH_PRE_BWD of a bf16 state

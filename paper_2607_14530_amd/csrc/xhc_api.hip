@@ -248,7 +248,7 @@ struct FlashPreBwdWs {
 
 // The Q row passes in one pass over the state keep Q reverses' workspaces.  At N
 // = 8 that is a step of its own, taken with the fine layout (C = 1024, Q = 4, T =
-// 16384: 182 MB against 72).
+// 16384: 182 MB against 69).
 FlashPreBwdWs flash_pre_bwd_ws(const xhc_dims* d, int Q, bool fine) {
   const xhc_dims e = dims_entry(d);
   const int64_t T = d->T, N = d->N, k = d->k, C = d->C, NC = N * C, kC = k * C;
